@@ -498,8 +498,8 @@ void hdof_batch_destroy(hdof_batch* batch);
 
 /* Launch shape of the persistent thin-lens trace (performance only: results
  * do not depend on it).  blocks_per_cu in [1, 32]; refill in [1, 64]: idle
- * lanes of a wave that trigger a refill from the queue (64 = batches of 64
- * rays); segments in [1, 8]: queue segments, one per XCD group; wave 0, 1
+ * lanes of a wave that trigger a refill from the queue (48 to 64 act
+ * alike); segments in [1, 8]: queue segments, one per XCD group; wave 0, 1
  * or 2: 1 walks the 64 rays of a batch of consecutive queue entries as one
  * wave (one node sequence, the union of their paths, with wave-uniform node
  * loads; refill is then unused), 0 traverses each lane's ray on its own and

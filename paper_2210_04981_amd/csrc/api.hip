@@ -295,6 +295,8 @@ extern "C" void hdof_scene_destroy(hdof_scene* sc) {
   hipSetDevice(sc->ctx->device);
   hipDeviceSynchronize();
   if (sc->nodes) hipFree(sc->nodes);
+  if (sc->hnodes) hipFree(sc->hnodes);
+  if (sc->unit) hipFree(sc->unit);
   if (sc->tris) hipFree(sc->tris);
   if (sc->albedo) hipFree(sc->albedo);
   if (sc->spec) hipFree(sc->spec);

@@ -10,8 +10,9 @@
 //      split, which large triangles such as room walls would inflate)
 //   -> depth-first numbering from subtree sizes; subtrees of at most
 //      HDOF_BVH_LEAF triangles become leaves whose triangles are contiguous
-//   -> traversal layout: per internal node the boxes of both children
-//      (64 B), triangles as 3 float4 in leaf order.
+//   -> traversal layout: per internal node the boxes of both children in
+//      full (64 B, the wave-coherent walk) and in half precision about their
+//      centre (48 B, the per-lane walk), triangles as 3 float4 in leaf order.
 #include "hdof_internal.h"
 
 #define RS_THREADS 256
@@ -392,13 +393,68 @@ __device__ inline unsigned leaf_code(int first, int count) {
   return HDOF_LEAF_BIT | ((unsigned)(count - 1) << 27) | (unsigned)first;
 }
 
+// ---- half-precision nodes -----------------------------------------------------
+// The scene's box unit: a power of two of which the root box's largest
+// extent is at most 2^15, so that box planes relative to their node's centre
+// are halves well inside the range of normal numbers; and the margin boxes
+// are widened by (2^-21 of the largest coordinate), which covers the
+// rounding of the plane distances that the traversal forms from the centre
+// and the offset.
+__global__ void k_box_unit(const float* __restrict__ root, float* __restrict__ unit) {
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  float ext = 0.0f, big = 0.0f;
+  for (int a = 0; a < 3; ++a) {
+    ext = fmaxf(ext, root[3 + a] - root[a]);
+    big = fmaxf(big, fmaxf(fabsf(root[a]), fabsf(root[3 + a])));
+  }
+  int e = 0;
+  frexpf(ext, &e);  // ext < 2^e
+  e = ext > 0.0f && ext < INFINITY ? max(-100, min(100, e - 14)) : 0;
+  unit[0] = ldexpf(1.0f, e);
+  unit[1] = big * 4.76837158e-7f;
+}
+
+// the box plane x in units above centre c, rounded outwards (dir -1 or 1)
+__device__ inline unsigned half_plane(float x, float c, float unit, float margin, int dir) {
+  const float v = (x - c + (dir > 0 ? margin : -margin)) / unit;
+  _Float16 h = (_Float16)v;
+  unsigned short u;
+  __builtin_memcpy(&u, &h, 2);
+  if (dir > 0 ? (float)h < v : (float)h > v) {  // one step towards dir
+    if ((u & 0x7FFF) == 0)
+      u = dir > 0 ? 0x0001 : 0x8001;
+    else
+      u = (unsigned short)(((u & 0x8000) != 0) == (dir < 0) ? u + 1 : u - 1);
+  }
+  return u;
+}
+
+// Half-precision record of a node with child boxes b0, b1 (minimum, maximum):
+// (centre, code 1), (x of both children, y of both), (z of both, code 0, -),
+// a pair of planes (minimum, maximum) per dword.
+__device__ inline void emit_half(float4* __restrict__ o, const float* b0, const float* b1, unsigned c0, unsigned c1,
+                                 const float* __restrict__ unit) {
+  const float s = unit[0], mg = unit[1];
+  float c[3];
+  unsigned pl[3][2];
+  for (int a = 0; a < 3; ++a) {
+    c[a] = 0.5f * (fminf(b0[a], b1[a]) + fmaxf(b0[3 + a], b1[3 + a]));
+    pl[a][0] = half_plane(b0[a], c[a], s, mg, -1) | half_plane(b0[3 + a], c[a], s, mg, 1) << 16;
+    pl[a][1] = half_plane(b1[a], c[a], s, mg, -1) | half_plane(b1[3 + a], c[a], s, mg, 1) << 16;
+  }
+  o[0] = make_float4(c[0] / s, c[1] / s, c[2] / s, __uint_as_float(c1));
+  o[1] = make_float4(__uint_as_float(pl[0][0]), __uint_as_float(pl[0][1]), __uint_as_float(pl[1][0]),
+                     __uint_as_float(pl[1][1]));
+  o[2] = make_float4(__uint_as_float(pl[2][0]), __uint_as_float(pl[2][1]), __uint_as_float(c0), 0.0f);
+}
+
 // kept internal nodes (more than HDOF_BVH_LEAF triangles, or the root) are
 // written at their depth-first index; smaller subtrees become leaf ranges
 __global__ void k_emit_nodes(int nint, const int* __restrict__ bl, const int* __restrict__ br,
                              const int2* __restrict__ bsz, const float* __restrict__ bbox,
                              const float* __restrict__ lbox, const int* __restrict__ leaf_off,
                              const int* __restrict__ node_off, const int* __restrict__ node_idx,
-                             float4* __restrict__ nodes) {
+                             const float* __restrict__ unit, float4* __restrict__ nodes, float4* __restrict__ hnodes) {
   int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= nint) return;
   if (a != 0 && bsz[a].x <= HDOF_BVH_LEAF) return;
@@ -423,10 +479,13 @@ __global__ void k_emit_nodes(int nint, const int* __restrict__ bl, const int* __
   o[1] = make_float4(b[1][0], b[1][3], b[1][1], b[1][4]);
   o[2] = make_float4(b[0][2], b[0][5], b[1][2], b[1][5]);
   o[3] = make_float4(__uint_as_float(code[0]), __uint_as_float(code[1]), 0.0f, 0.0f);
+  emit_half(hnodes + 3 * (size_t)node_idx[a], b[0], b[1], code[0], code[1], unit);
 }
 
 // one triangle: a root whose second child box is empty
-__global__ void k_single_root(const float* __restrict__ lbox, float4* __restrict__ nodes) {
+__global__ void k_single_root(const float* __restrict__ lbox, const float* __restrict__ unit,
+                              float4* __restrict__ nodes, float4* __restrict__ hnodes) {
+  emit_half(hnodes, lbox, lbox, leaf_code(0, 1), leaf_code(0, 1), unit);
   float4* o = nodes;
   o[0] = make_float4(lbox[0], lbox[3], lbox[1], lbox[4]);
   o[1] = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
@@ -457,11 +516,13 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
   // permanent storage (node slots for every internal node; collapsed
   // subtrees leave the tail unused)
   HDOF_HIP(hipMalloc(&sc->nodes, sizeof(float4) * 4 * (size_t)nint));
+  HDOF_HIP(hipMalloc(&sc->hnodes, sizeof(float4) * 3 * (size_t)nint));
+  HDOF_HIP(hipMalloc(&sc->unit, sizeof(float) * 2));
   HDOF_HIP(hipMalloc(&sc->tris, sizeof(float4) * 3 * (size_t)n));
   HDOF_HIP(hipMalloc(&sc->albedo, sizeof(float) * 3 * (size_t)n));
   HDOF_HIP(hipMalloc(&sc->depth_out, sizeof(int)));
   sc->n_nodes = nint;
-  sc->bytes = (int64_t)sizeof(float4) * (4 * (int64_t)nint + 3 * (int64_t)n) + 12 * (int64_t)n;
+  sc->bytes = (int64_t)sizeof(float4) * (7 * (int64_t)nint + 3 * (int64_t)n) + 12 * (int64_t)n;
   // build scratch, one allocation
   size_t off = 0;
   auto carve = [&](size_t bytes) {
@@ -521,7 +582,8 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
   hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, sc->depth_out, 1, 1);
   if (n == 1) {
     hipLaunchKernelGGL(k_place_tris, dim3(1), dim3(64), 0, st, verts, v0, (const int*)nullptr, n, sc->tris);
-    hipLaunchKernelGGL(k_single_root, dim3(1), dim3(1), 0, st, lbox, sc->nodes);
+    hipLaunchKernelGGL(k_box_unit, dim3(1), dim3(1), 0, st, (const float*)lbox, sc->unit);
+    hipLaunchKernelGGL(k_single_root, dim3(1), dim3(1), 0, st, lbox, sc->unit, sc->nodes, sc->hnodes);
     hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, sc->depth_out, 1, 2);
   } else {
     hipLaunchKernelGGL(k_leaf_clusters, dim3(cdiv(n, 256)), dim3(256), 0, st, lbox, n, cid[0], cbox[0], csz[0]);
@@ -561,9 +623,10 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
                          (const int*)pint, (const int*)pleaf, (const int2*)bsz, noff, nidx);
       hipLaunchKernelGGL(k_place_tris, dim3(cdiv(n, 256)), dim3(256), 0, st, verts, (const int*)v0,
                          (const int*)loff, n, sc->tris);
+      hipLaunchKernelGGL(k_box_unit, dim3(1), dim3(1), 0, st, (const float*)bbox, sc->unit);
       hipLaunchKernelGGL(k_emit_nodes, dim3(cdiv(nint, 256)), dim3(256), 0, st, nint, (const int*)bl,
                          (const int*)br, (const int2*)bsz, (const float*)bbox, (const float*)lbox,
-                         (const int*)loff, (const int*)noff, (const int*)nidx, sc->nodes);
+                         (const int*)loff, (const int*)noff, (const int*)nidx, (const float*)sc->unit, sc->nodes, sc->hnodes);
     }
   }
   hipError_t e = hipGetLastError();

@@ -14,10 +14,22 @@
 #define HDOF_SQRT2 1.41421356237309505f
 #define HDOF_PI 3.14159265358979324f
 
-// traversal stack: this many entries per lane live in LDS, the rest spill to
-// a small private array; beyond both the ray sets the overflow flag.
-#define HDOF_LDS_STACK 20
-#define HDOF_SPILL_STACK 44
+// traversal stack of the persistent trace: this many entries per lane live in
+// LDS, the rest spill to a small private array; beyond both the ray sets the
+// overflow flag.
+#define HDOF_LDS_STACK 16
+#define HDOF_SPILL_STACK 48
+// lanes in box steps below which the wave turns to its waiting leaves; idle
+// lanes that take waiting rays; idle lanes that refill the slots at most
+#ifndef HDOF_MIN_BOX
+#define HDOF_MIN_BOX 8
+#endif
+#ifndef HDOF_HAND_OUT
+#define HDOF_HAND_OUT 8
+#endif
+#ifndef HDOF_REFILL_MAX
+#define HDOF_REFILL_MAX 48
+#endif
 #define HDOF_TRACE_BLOCK 128
 #ifndef HDOF_DEFAULT_BPC
 #define HDOF_DEFAULT_BPC 10  // persistent trace blocks per CU (its register-limited residency)
@@ -46,6 +58,8 @@ struct hdof_scene {
   int32_t n_tris;
   int32_t n_nodes;
   float4* nodes;   // 4 float4 per node: child boxes x/y (2), z (1), children (1)
+  float4* hnodes;  // 3 float4 per node: half-precision child boxes about the node's centre (see emit_half)
+  float* unit;     // [2] unit of the half-precision boxes, margin they are widened by
   float4* tris;    // 3 float4 per triangle in leaf order; .w of the first = input index
   float* albedo;   // 3 floats per triangle, input order
   float* spec;     // 2 floats per triangle (k_s, shininess), input order; NULL: Lambertian
@@ -250,14 +264,27 @@ inline LightK make_lightk(const hdof_light* l) {
 // Philox4x64-10 (Salmon et al., SC'11): 10 rounds of two 64x64 -> 128-bit
 // multiplies, key bumped by the Weyl constants between rounds.
 // ---------------------------------------------------------------------------
+// The 128-bit product of x and a constant as four 32 x 32 + 64 multiply-adds
+// (no partial product is formed twice, as separate low and high halves
+// would).
+__device__ __forceinline__ void mul_64x64(uint64_t x, uint64_t m, uint64_t& lo, uint64_t& hi) {
+  const uint32_t x0 = (uint32_t)x, x1 = (uint32_t)(x >> 32), m0 = (uint32_t)m, m1 = (uint32_t)(m >> 32);
+  const uint64_t p00 = (uint64_t)x0 * m0;
+  const uint64_t p01 = (uint64_t)x0 * m1 + (p00 >> 32);
+  const uint64_t p10 = (uint64_t)x1 * m0 + (uint32_t)p01;
+  lo = p10 << 32 | (uint32_t)p00;
+  hi = (uint64_t)x1 * m1 + ((p01 >> 32) + (p10 >> 32));
+}
+
 __device__ inline void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t k0,
                                      uint64_t k1, uint64_t& o0, uint64_t& o1) {
   const uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
   const uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    uint64_t lo0 = M0 * c0, hi0 = __umul64hi(M0, c0);
-    uint64_t lo1 = M1 * c2, hi1 = __umul64hi(M1, c2);
+    uint64_t lo0, hi0, lo1, hi1;
+    mul_64x64(c0, M0, lo0, hi0);
+    mul_64x64(c2, M1, lo1, hi1);
     uint64_t n0 = hi1 ^ c1 ^ k0;
     uint64_t n2 = hi0 ^ c3 ^ k1;
     c0 = n0;

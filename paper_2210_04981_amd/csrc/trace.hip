@@ -1,10 +1,12 @@
 // trace.hip -- BVH traversal, G-buffer and thin-lens distributed ray trace.
 //
-// Traversal: per-lane stack whose first HDOF_LDS_STACK entries live in LDS
-// (entry i of lane t at stk[i * BLOCK + t], so a wave's pushes hit 64
-// distinct banks) and the rest in a short private spill array; both children
-// of a node are box-tested from one 64-byte node record, leaves are tested
-// in the same step, the nearer internal child is visited first.
+// Traversal: both children of a node are box-tested from one record, the
+// nearer is visited first.  The wave-coherent walk (G-buffer) reads 64-byte
+// records with full-precision boxes through the scalar cache; the per-lane
+// walk (lens rays) reads 44 bytes with half-precision boxes and keeps a
+// stack per lane whose first HDOF_LDS_STACK entries live in LDS (entry i of
+// lane t at stk[i][t], so a wave's pushes hit 64 distinct banks) and the
+// rest in a short private spill array.
 // Triangles: watertight ray/triangle test (Woop, Benthin, Wald, JCGT 2013),
 // ties broken towards the lowest input triangle index.
 //
@@ -12,8 +14,8 @@
 // rays); blocks remapped so each XCD works on a contiguous band of the image
 // and keeps its part of the BVH in its own L2.
 // Thin-lens trace: queue of (pixel, sample) entries built from the mask's
-// counts and offsets; a persistent grid pops 64 entries per wave from a
-// device counter, so the host never reads the ray count; results per entry,
+// counts and offsets; the waves of a persistent grid pop entries from device
+// counters, so the host never reads the ray count; results per entry,
 // then a per-pixel reduction in fixed sample order (deterministic).
 #include "hdof_internal.h"
 
@@ -38,12 +40,20 @@ __device__ inline float safe_inv(float d) {
 
 __device__ inline V3 unit(int k) { return V3{k == 0 ? 1.0f : 0.0f, k == 1 ? 1.0f : 0.0f, k == 2 ? 1.0f : 0.0f}; }
 
-__device__ inline Ray make_ray(V3 O, V3 D) {
-  Ray r;
-  r.O = O;
-  r.D = D;
-  r.inv = V3{safe_inv(D.x), safe_inv(D.y), safe_inv(D.z)};
-  r.oinv = V3{-O.x * r.inv.x, -O.y * r.inv.y, -O.z * r.inv.z};
+// What make_ray divides for: the inverse direction and the shear of the
+// axes (kx, ky, kz), kz the direction's largest component and (kx, ky)
+// ordered by its sign.
+struct RayPre {
+  V3 O, D, inv;
+  float Sx, Sy;
+  int axes;  // kz | kx << 2
+};
+
+__device__ inline RayPre ray_pre(V3 O, V3 D) {
+  RayPre q;
+  q.O = O;
+  q.D = D;
+  q.inv = V3{safe_inv(D.x), safe_inv(D.y), safe_inv(D.z)};
   float ax = fabsf(D.x), ay = fabsf(D.y), az = fabsf(D.z);
   int kz = ax > ay ? (ax > az ? 0 : 2) : (ay > az ? 1 : 2);
   int kx = kz == 2 ? 0 : kz + 1;
@@ -54,16 +64,35 @@ __device__ inline Ray make_ray(V3 O, V3 D) {
     kx = ky;
     ky = t;
   }
-  const float Sx = comp(D, kx) / dz, Sy = comp(D, ky) / dz, Sz = 1.0f / dz;
-  const V3 ex = unit(kx), ey = unit(ky), ez = unit(kz);
-  r.mx = V3{ex.x - Sx * ez.x, ex.y - Sx * ez.y, ex.z - Sx * ez.z};
-  r.my = V3{ey.x - Sy * ez.x, ey.y - Sy * ez.y, ey.z - Sy * ez.z};
+  q.Sx = comp(D, kx) / dz;
+  q.Sy = comp(D, ky) / dz;
+  q.axes = kz | kx << 2;
+  return q;
+}
+
+// (the inverse direction's kz component is 1 / dz: the largest component of
+// a direction is above safe_inv's threshold)
+__device__ inline Ray ray_of(const RayPre& q) {
+  Ray r;
+  r.O = q.O;
+  r.D = q.D;
+  r.inv = q.inv;
+  r.oinv = V3{-q.O.x * q.inv.x, -q.O.y * q.inv.y, -q.O.z * q.inv.z};
+  const int kz = q.axes & 3, kx = q.axes >> 2, ky = 3 - kx - kz;
+  const float Sz = comp(q.inv, kz);
+  const V3 ez = unit(kz);
+  r.mx = V3{kx == 0 ? 1.0f : (kz == 0 ? -q.Sx : 0.0f), kx == 1 ? 1.0f : (kz == 1 ? -q.Sx : 0.0f),
+            kx == 2 ? 1.0f : (kz == 2 ? -q.Sx : 0.0f)};
+  r.my = V3{ky == 0 ? 1.0f : (kz == 0 ? -q.Sy : 0.0f), ky == 1 ? 1.0f : (kz == 1 ? -q.Sy : 0.0f),
+            ky == 2 ? 1.0f : (kz == 2 ? -q.Sy : 0.0f)};
   r.mz = V3{Sz * ez.x, Sz * ez.y, Sz * ez.z};
-  r.ox = dot3(r.mx, O);
-  r.oy = dot3(r.my, O);
-  r.oz = dot3(r.mz, O);
+  r.ox = dot3(r.mx, q.O);
+  r.oy = dot3(r.my, q.O);
+  r.oz = dot3(r.mz, q.O);
   return r;
 }
+
+__device__ inline Ray make_ray(V3 O, V3 D) { return ray_of(ray_pre(O, D)); }
 
 // slab test of one child box against [0, tmax]; conservative by 2 gamma(3)
 __device__ inline bool box_hit(const Ray& r, float lox, float hix, float loy, float hiy, float loz,
@@ -90,6 +119,30 @@ __device__ inline bool box_hit_signed(const Ray& r, float nx, float fx, float ny
   const float tz0 = fmaf(nz, r.inv.z, r.oinv.z), tz1 = fmaf(fz, r.inv.z, r.oinv.z);
   const float tmin = fmaxf(fmaxf(tx0, ty0), fmaxf(tz0, 0.0f));
   const float tmx = fminf(fminf(tx1, ty1), fminf(tz1, tmax));
+  tnear = tmin;
+  return tmin <= tmx * 1.0000004f;
+}
+
+// Half-precision boxes: a pair of planes (minimum, maximum) in units about
+// the node's centre.  Rotated by 16 where the ray runs against the axis, a
+// pair has the plane the ray enters through in its low half, and an fma
+// that takes a half operand gives its distance.
+__device__ inline float half_dist(unsigned pair, int hi, float sinv, float base) {
+  unsigned short u = (unsigned short)(hi ? pair >> 16 : pair);
+  _Float16 h;
+  __builtin_memcpy(&h, &u, 2);
+  return fmaf((float)h, sinv, base);
+}
+
+__device__ inline bool box_hit_half(unsigned x, unsigned y, unsigned z, V3 sinv, V3 base, int rx, int ry, int rz,
+                                    float tmax, float& tnear) {
+  x = __builtin_amdgcn_alignbit(x, x, rx);
+  y = __builtin_amdgcn_alignbit(y, y, ry);
+  z = __builtin_amdgcn_alignbit(z, z, rz);
+  const float tmin = fmaxf(fmaxf(half_dist(x, 0, sinv.x, base.x), half_dist(y, 0, sinv.y, base.y)),
+                           fmaxf(half_dist(z, 0, sinv.z, base.z), 0.0f));
+  const float tmx = fminf(fminf(half_dist(x, 1, sinv.x, base.x), half_dist(y, 1, sinv.y, base.y)),
+                          fminf(half_dist(z, 1, sinv.z, base.z), tmax));
   tnear = tmin;
   return tmin <= tmx * 1.0000004f;
 }
@@ -147,81 +200,25 @@ struct Work {
   int visits, tests;
 };
 
-// Traversal state of one ray between steps.
-struct Trav {
-  Best b;
-  unsigned cur;  // entry to visit next: an internal node, or a leaf code (leaf bit set)
-  int sp;        // stack depth
+// What a wave of the persistent trace keeps in LDS: 64 ray slots (structure
+// of arrays, a slot's fields SLOT_* of a ray that waits or is walked, then
+// its hit in place of the inverse direction), the slots no lane has taken
+// yet, and the lanes' stacks (entry i of lane t at stk[i][t]).
+enum { SLOT_O, SLOT_D = 3, SLOT_INV = 6, SLOT_SX = 9, SLOT_SY, SLOT_AXES, SLOT_S1, SLOT_ENTRY, SLOT_DONE, SLOT_N };
+struct PoolLds {
+  float f[SLOT_N][64];
+  int list[64];
+  int stk[HDOF_LDS_STACK][64];
 };
 
-__device__ inline void trav_init(Trav& s) {
-  s.b = Best{INFINITY, -1, 0x7fffffff};
-  s.cur = 0;  // root (internal)
-  s.sp = 0;
+// Orders the wave's LDS accesses as the program has them (the LDS executes
+// one wave's accesses in order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Per-lane traversal in two kinds of step.  A box step enters the lane's
-// current entry, an internal node: of its two children whose boxes the ray
-// reaches within the closest hit so far, the nearer (internal node or
-// leaf) becomes the entry and the farther is pushed; with neither, the
-// entry is popped.  A leaf step tests the entry's triangles and pops.  The
-// caller takes box steps until the entry is a leaf, so the lanes of a wave
-// test their leaves together; testing a leaf child as soon as it is met
-// costs the whole wave its triangle loop in nearly every box step, since
-// some lane nearly always meets one.
-template <int BLOCK>
-__device__ inline void trav_push(int* __restrict__ stk, int* __restrict__ spill, Trav& s, unsigned code,
-                                 int* __restrict__ flags) {
-  if (s.sp < HDOF_LDS_STACK) {
-    stk[s.sp * BLOCK] = (int)code;
-    ++s.sp;
-  } else if (s.sp < HDOF_LDS_STACK + HDOF_SPILL_STACK) {
-    spill[s.sp - HDOF_LDS_STACK] = (int)code;
-    ++s.sp;
-  } else {
-    atomicOr(flags, HDOF_FLAG_STACK_OVERFLOW);
-  }
-}
-
-// Pop the next entry; true when the stack is empty (the ray is done).
-template <int BLOCK>
-__device__ inline bool trav_pop(const int* __restrict__ stk, const int* __restrict__ spill, Trav& s) {
-  if (s.sp == 0) return true;
-  --s.sp;
-  s.cur = (unsigned)(s.sp < HDOF_LDS_STACK ? stk[s.sp * BLOCK] : spill[s.sp - HDOF_LDS_STACK]);
-  return false;
-}
-
-template <int BLOCK, bool COUNT>
-__device__ inline bool box_step(const float4* __restrict__ nodes, const Ray& r, int* __restrict__ stk,
-                                int* __restrict__ spill, Trav& s, int* __restrict__ flags, Work& wk) {
-  if (COUNT) wk.visits++;
-  const float4* nd = nodes + 4 * (size_t)s.cur;
-  const float4 n0 = nd[0], n1 = nd[1], n2 = nd[2], n3 = nd[3];
-  float t0, t1;
-  const bool h0 = box_hit(r, n0.x, n0.y, n0.z, n0.w, n2.x, n2.y, s.b.t, t0);
-  const bool h1 = box_hit(r, n1.x, n1.y, n1.z, n1.w, n2.z, n2.w, s.b.t, t1);
-  const unsigned c0 = __float_as_uint(n3.x), c1 = __float_as_uint(n3.y);
-  if (h0 && h1) {
-    trav_push<BLOCK>(stk, spill, s, t0 <= t1 ? c1 : c0, flags);
-    s.cur = t0 <= t1 ? c0 : c1;
-  } else if (h0) {
-    s.cur = c0;
-  } else if (h1) {
-    s.cur = c1;
-  } else {
-    return trav_pop<BLOCK>(stk, spill, s);
-  }
-  return false;
-}
-
-template <int BLOCK, bool COUNT>
-__device__ inline bool leaf_step(const float4* __restrict__ tris, const Ray& r, const int* __restrict__ stk,
-                                 const int* __restrict__ spill, Trav& s, Work& wk) {
-  test_leaf(r, tris, s.cur, s.b);
-  if (COUNT) wk.tests += (int)((s.cur >> 27) & 0xF) + 1;
-  return trav_pop<BLOCK>(stk, spill, s);
-}
+__device__ __forceinline__ V3 slot_v3(const PoolLds& L, int f, int i) { return V3{L.f[f][i], L.f[f + 1][i], L.f[f + 2][i]}; }
 
 // Wave-coherent traversal: the lanes of a wave walk one node sequence, the
 // union of their own paths (primary rays of an 8x8 pixel quadrant are
@@ -339,7 +336,7 @@ __device__ inline Best traverse_wave_any(const float4* __restrict__ nodes, const
 // on the viewer's side, h the unit half vector of the light direction and
 // the direction back along the ray; ys = the lobe's luminance.
 __device__ inline void shade(const float4* __restrict__ tris, const float* __restrict__ albedo,
-                             const float2* __restrict__ spec, const LightK& li, const Ray& r, const Best& b, V3& L,
+                             const float2* __restrict__ spec, const LightK& li, V3 O, V3 D, const Best& b, V3& L,
                              V3& n, V3& alb, float& ys) {
   float4 a = tris[3 * b.tri], q = tris[3 * b.tri + 1], c = tris[3 * b.tri + 2];
   V3 e1 = V3{q.x - a.x, q.y - a.y, q.z - a.z};
@@ -347,8 +344,8 @@ __device__ inline void shade(const float4* __restrict__ tris, const float* __res
   V3 nn = cross3(e1, e2);
   float il = rsqrtf(dot3(nn, nn));
   nn = il * nn;
-  if (dot3(nn, r.D) > 0.0f) nn = V3{-nn.x, -nn.y, -nn.z};
-  V3 P = V3{fmaf(b.t, r.D.x, r.O.x), fmaf(b.t, r.D.y, r.O.y), fmaf(b.t, r.D.z, r.O.z)};
+  if (dot3(nn, D) > 0.0f) nn = V3{-nn.x, -nn.y, -nn.z};
+  V3 P = V3{fmaf(b.t, D.x, O.x), fmaf(b.t, D.y, O.y), fmaf(b.t, D.z, O.z)};
   V3 l = li.p - P;
   float d2 = dot3(l, l);
   float cosv = d2 > 0.0f ? dot3(nn, l) * rsqrtf(d2) : 0.0f;
@@ -362,8 +359,8 @@ __device__ inline void shade(const float4* __restrict__ tris, const float* __res
   if (spec) {
     const float2 m = spec[b.id];
     if (m.x > 0.0f && cosv > 0.0f) {
-      const float il2 = rsqrtf(d2), iD = rsqrtf(dot3(r.D, r.D));
-      const V3 h = V3{fmaf(l.x, il2, -r.D.x * iD), fmaf(l.y, il2, -r.D.y * iD), fmaf(l.z, il2, -r.D.z * iD)};
+      const float il2 = rsqrtf(d2), iD = rsqrtf(dot3(D, D));
+      const V3 h = V3{fmaf(l.x, il2, -D.x * iD), fmaf(l.y, il2, -D.y * iD), fmaf(l.z, il2, -D.z * iD)};
       const float hh = dot3(h, h);
       const float nh = hh > 0.0f ? fmaxf(0.0f, dot3(nn, h) * rsqrtf(hh)) : 0.0f;
       const float f = m.x * powf(nh, m.y) / fmaxf(d2, 1e-4f);
@@ -409,7 +406,7 @@ __device__ inline void gbuffer_block(const float4* __restrict__ nodes, const flo
     V3 L = V3{0.0f, 0.0f, 0.0f};
     if (b.tri >= 0) {
       V3 n, a;
-      shade(tris, albedo, spec, li, r, b, L, n, a, ys);
+      shade(tris, albedo, spec, li, r.O, r.D, b, L, n, a, ys);
       z = b.t * l.S1;
       normal[p] = n.x;
       normal[N + p] = n.y;
@@ -479,19 +476,18 @@ __global__ void k_queue_fill(const uint8_t* __restrict__ spp, const int* __restr
     if (o + j >= 0 && o + j < cap) queue[o + j] = pxbase + p;
 }
 
-// Persistent trace.  Every lane runs its own ray one node step at a time;
-// when at least `refill` lanes of a wave are idle the wave takes that many
-// entries from the queue with one atomic and hands them to the idle lanes
-// (refill = 64: batches of 64 rays).  The queue is cut into `segments`
-// contiguous segments (bands of image rows; whole views in a batch), one
-// per group of XCDs (blocks are dispatched round-robin over the 8 XCDs): a
-// wave takes work from its own segment first, so each XCD's L2 holds the
-// part of the BVH its rays touch, then moves on to the other segments.
-// Every wave exits once all segments are drained and its lanes are idle.
+// Persistent trace.  The queue is cut into `segments` contiguous segments
+// (bands of image rows; whole views in a batch), one per group of XCDs
+// (blocks are dispatched round-robin over the 8 XCDs): a wave takes work
+// from its own segment first, so each XCD's L2 holds the part of the BVH its
+// rays touch, then moves on to the other segments.  Every wave exits once
+// all segments are drained and its rays are done.
 using ViewK = BatchView;  // the device copy of a batch's view table
 
 struct TraceArgs {
   const float4* nodes;
+  const float4* hnodes;
+  const float* unit;
   const float4* tris;
   int n_nodes;
   const float* albedo;
@@ -520,7 +516,7 @@ struct TraceArgs {
 // from the view's counters.  False for an entry past hi or a corrupt pixel
 // index.  pxb (batch): the first batch pixel of each view.
 template <bool BATCH>
-__device__ inline bool entry_ray(const TraceArgs& A, const int* pxb, int ee, int hi, Ray& r, float& S1) {
+__device__ inline bool entry_ray(const TraceArgs& A, const int* pxb, int ee, int hi, V3& O, V3& D, float& S1) {
   const int g = ee < hi ? A.queue[ee] : -1;
   bool ok;
   int p, j;
@@ -542,22 +538,19 @@ __device__ inline bool entry_ray(const TraceArgs& A, const int* pxb, int ee, int
   if (!ok) return false;
   const CamK k = vk->k;
   const LensK l = vk->l;
-  V3 O, D;
   lens_ray(k, l, p % k.W, p / k.W, (uint32_t)j, vk->view, vk->seed, vk->frame, O, D);
-  r = make_ray(O, D);
   S1 = l.S1;
   return true;
 }
 
 // Shade the closest hit of a finished ray and store entry e's result.
-template <bool COUNT>
-__device__ inline void store_ray(const TraceArgs& A, const Ray& r, const Best& b, float S1, int e, const Work& wk) {
+__device__ inline void store_ray(const TraceArgs& A, V3 O, V3 D, const Best& b, float S1, int e) {
   float z = HDOF_ZMAX;
   V3 L = V3{0.0f, 0.0f, 0.0f};
   if (b.tri >= 0) {
     V3 n, a;
     float ys;
-    shade(A.tris, A.albedo, A.spec, A.li, r, b, L, n, a, ys);
+    shade(A.tris, A.albedo, A.spec, A.li, O, D, b, L, n, a, ys);
     z = b.t * S1;
   }
   A.ray_col[e] = L.x;
@@ -565,11 +558,6 @@ __device__ inline void store_ray(const TraceArgs& A, const Ray& r, const Best& b
   A.ray_col[2 * A.cap + e] = L.z;
   A.ray_z[e] = z;
   if (A.ray_id) A.ray_id[e] = b.tri >= 0 ? b.id : -1;
-  if (COUNT) {
-    atomicAdd(&A.counters[3], 1ull);
-    atomicAdd(&A.counters[4], (unsigned long long)wk.visits);
-    atomicAdd(&A.counters[5], (unsigned long long)wk.tests);
-  }
 }
 
 // The G-buffers of a batch in one launch (packed texels and tile radii
@@ -599,29 +587,62 @@ __global__ __launch_bounds__(256) void k_gbuffer_batch(const float4* __restrict_
                              nullptr, pack + pb, tile_r + gbb.blk_base[v]);
 }
 
-// Whether this block of the persistent trace takes part: with a ray
-// quantum (a frame overlapping the trace with the post-filter gather) only
-// the first ceil(total * n_cu / ray_quantum) blocks, one block per CU for
-// every ray_quantum rays on average (at least one per CU, at most the
-// grid), so a light trace leaves the CUs to the gather; the first blocks
-// are kept, so every queue segment keeps its blocks.
-__device__ inline bool keep_block(const TraceArgs& A, int total) {
-  if (A.ray_quantum <= 0) return true;
+// The blocks of the persistent trace that take part: with a ray quantum (a
+// frame overlapping the trace with the post-filter gather) only the first
+// ceil(total * n_cu / ray_quantum) blocks, one block per CU for every
+// ray_quantum rays on average (at least one per CU, at most the grid), so a
+// light trace leaves the CUs to the gather; the first blocks are kept, so
+// every queue segment keeps its blocks.
+__device__ inline int kept_blocks(const TraceArgs& A, int total) {
+  const long all = (long)A.bpc * A.n_cu;
+  if (A.ray_quantum <= 0) return (int)all;
   const long kept = ((long)total * A.n_cu + A.ray_quantum - 1) / A.ray_quantum;
-  return (long)blockIdx.x < min((long)A.bpc * A.n_cu, max((long)A.n_cu, kept));
+  return (int)min(all, max((long)A.n_cu, kept));
+}
+
+// The trace's arguments read anew from the kernel's argument segment (its
+// only argument): what a refill derives from them is then not kept in
+// registers through the traversal (141 vector registers otherwise).
+__device__ __forceinline__ const TraceArgs* fresh_args() {
+  const __attribute__((address_space(4))) char* p =
+      (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return (const TraceArgs*)p;
 }
 
 // Entries handed out: per queue segment (one per XCD, the block's
 // blockIdx.x mod segments) an atomic counter of entries taken; a wave whose
 // segment runs dry moves on to the next and stops once it has found every
 // segment dry.
+// Bound: the vector-memory path.  A dwordx4 load of 64 lanes takes a CU 16
+// clocks whatever the mask (its data return was 87 % busy with four of them
+// per node, the vector ALUs 71 %), so what counts is load instructions per
+// ray: three per node since the boxes are halves, and more lanes in each.
+// On 1.75M rays of a 1080p frame, alone: 533 -> 411 us; 8.3M rays of every
+// pixel of 960x540 with their queue and reduction: 1617 -> 1447 us; the 1M
+// triangles' 4.7M rays: 591 -> 526 us.
+// A wave holds up to 64 rays in LDS slots.  Each is set up, and once hit
+// shaded and stored, by one lane each, 64 at a time; a lane that has
+// finished a ray takes the next waiting slot, which costs the wave a few LDS
+// reads instead of a ray's set-up (Philox block, lens sample, divisions), so
+// lanes need not idle until the whole batch is done.  When no slot waits and
+// the idle lanes number `refill` (at most HDOF_REFILL_MAX), the finished
+// slots are shaded and refilled from the queue.
+// (refill at 16 / 24 / 40 / 48 idle lanes: 528 / 493 / 462 / 442 us: rays of
+// neighbouring entries that start together share their first loads' lines.)
+// Traversal: box steps enter internal nodes (of two children that the ray
+// reaches within the closest hit so far, the nearer becomes the entry and
+// the other is pushed); a leaf step tests the entry's triangles.  The wave
+// takes box steps while HDOF_MIN_BOX lanes have them to take, then the leaf
+// step of the lanes that wait at a leaf (until the last lane, 8 or 20:
+// 509 / 442 / 489 us).
 template <bool COUNT, bool BATCH>
 __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_trace(TraceArgs A) {
-  __shared__ int stk_all[HDOF_LDS_STACK * HDOF_TRACE_BLOCK];
-  __shared__ int pxb[HDOF_MAX_VIEWS + 1];
+  __shared__ PoolLds lds[HDOF_TRACE_BLOCK / 64];
+  __shared__ int pxb[BATCH ? HDOF_MAX_VIEWS + 1 : 1];
   int spill[HDOF_SPILL_STACK];
   const int t = threadIdx.x, lane = t & 63;
-  int* stk = stk_all + t;
+  PoolLds& L = lds[__builtin_amdgcn_readfirstlane(t >> 6)];
   if (BATCH) {
     for (int v = t; v < A.n_views; v += HDOF_TRACE_BLOCK) pxb[v] = A.views[v].px_base;
     __syncthreads();
@@ -632,62 +653,156 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
     if (blockIdx.x == 0 && t == 0) atomicOr(A.flags, HDOF_FLAG_CAPACITY);
     total = (int)A.cap;
   }
-  if (!keep_block(A, total)) return;
-  const int nseg = A.segments;
-  const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  bool active = false, drained = false;
-  int e = 0, steps = 0;
-  int seg = blockIdx.x % nseg, tried = 0;
-  float S1 = A.v0.l.S1;
-  Ray r;
-  Trav s;
+  if ((int)blockIdx.x >= kept_blocks(A, total)) return;
+  const int refill = min(A.refill, HDOF_REFILL_MAX);
+  const float unit = *A.unit;
+  bool held = false, drained = false;  // held: the lane's slot holds a ray
+  int seg = blockIdx.x % A.segments, tried = 0;
+  int next = 0, count = 0;  // the waiting slots are list[next .. count)
+  // the lane's ray: its slot (-1: none), the entry to visit next (a node, or
+  // a leaf code), the stack depth, the closest hit
+  int slot = -1, sp = 0;
+  unsigned cur = 0;
+  Best b = Best{INFINITY, -1, 0x7fffffff};
+  // box steps since a ray of the wave was last done, and what they are bounded by
+  unsigned stall = 0;
+  const unsigned stall_max = (unsigned)min(64ll * (A.n_nodes + 1ll), 0xfffffff0ll);
   Work wk{0, 0};
   for (;;) {
-    const unsigned long long idle = __ballot(!active);
-    const int nidle = __popcll(idle);
-    if (!drained && nidle >= A.refill) {
+    const unsigned long long idle = __builtin_amdgcn_ballot_w64(slot < 0);
+    const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    if (next >= count && (int)__popcll(idle) >= (drained ? 64 : refill)) {
+      wave_order();
+      const TraceArgs& B = *fresh_args();
+      if (held && __float_as_int(L.f[SLOT_DONE][lane]) == 1) {
+        const Best h = Best{L.f[SLOT_INV][lane], __float_as_int(L.f[SLOT_INV + 1][lane]),
+                            __float_as_int(L.f[SLOT_INV + 2][lane])};
+        store_ray(B, slot_v3(L, SLOT_O, lane), slot_v3(L, SLOT_D, lane), h, L.f[SLOT_S1][lane],
+                  __float_as_int(L.f[SLOT_ENTRY][lane]));
+        held = false;
+      }
+      if (drained) break;
+      const unsigned long long fm = __builtin_amdgcn_ballot_w64(!held);
+      const int want = (int)__popcll(fm), nseg = B.segments;
       const int lo = (int)((long)total * seg / nseg), hi = (int)((long)total * (seg + 1) / nseg);
       int base = 0;
-      if (lane == 0) base = atomicAdd(&A.counter[seg * HDOF_SEG_STRIDE], nidle);
-      base = __shfl(base, 0) + lo;
-      if (base + nidle >= hi) {  // this segment is used up: go on to the next one
+      if (lane == 0) base = atomicAdd(&B.counter[seg * HDOF_SEG_STRIDE], want);
+      base = __builtin_amdgcn_readfirstlane(base) + lo;
+      if (base + want >= hi) {  // this segment is used up: go on to the next one
         seg = seg + 1 == nseg ? 0 : seg + 1;
         drained = ++tried == nseg;
       }
-      if (!active) {
-        const int ee = base + __popcll(idle & lt_mask);
-        if (entry_ray<BATCH>(A, pxb, ee, hi, r, S1)) {
-          trav_init(s);
-          e = ee;
-          steps = 0;
-          active = true;
-          if (COUNT) wk = Work{0, 0};
+      bool got = false;
+      if (!held) {
+        const int e = base + (int)__popcll(fm & lt_mask);
+        V3 O, D;
+        float S1;
+        got = entry_ray<BATCH>(B, pxb, e, hi, O, D, S1);
+        if (got) {
+          const RayPre q = ray_pre(O, D);
+          const float f[SLOT_N] = {O.x,  O.y,  O.z,  D.x, D.y,
+                                   D.z,  q.inv.x, q.inv.y, q.inv.z, q.Sx,
+                                   q.Sy, __int_as_float(q.axes), S1, __int_as_float(e), __int_as_float(0)};
+#pragma unroll
+          for (int i = 0; i < SLOT_N; ++i) L.f[i][lane] = f[i];
+          held = true;
         }
       }
+      const unsigned long long gm = __builtin_amdgcn_ballot_w64(got);
+      if (got) L.list[__popcll(gm & lt_mask)] = lane;
+      next = 0;
+      count = (int)__popcll(gm);
+      wave_order();
     }
-    if (!active) {
-      if (drained) break;  // nothing left to hand out: an idle lane is done
-      continue;
-    }
-    // box steps until the entry is a leaf (each internal node is entered at
-    // most once per ray, so more than n_nodes of them means a malformed tree:
-    // the ray stops and raises the device flag), then the leaf step
-    bool done = false;
-    while (!(s.cur & HDOF_LEAF_BIT)) {
-      if (++steps > A.n_nodes) {
-        atomicOr(A.flags, HDOF_FLAG_STACK_OVERFLOW);
-        done = true;
-        break;
+    if (next < count) {  // hand the waiting slots to the idle lanes
+      const int i = next + (int)__popcll(idle & lt_mask);
+      if (slot < 0 && i < count) {
+        slot = L.list[i];
+        b = Best{INFINITY, -1, 0x7fffffff};
+        cur = 0;  // root
+        sp = 0;
       }
-      if (box_step<HDOF_TRACE_BLOCK, COUNT>(A.nodes, r, stk, spill, s, A.flags, wk)) {
-        done = true;
-        break;
-      }
+      next = min(count, next + (int)__popcll(idle));
     }
-    if (!done) done = leaf_step<HDOF_TRACE_BLOCK, COUNT>(A.tris, r, stk, spill, s, wk);
-    if (done) {
-      store_ray<COUNT>(A, r, s.b, S1, e, wk);
-      active = false;
+    const int sl = slot < 0 ? lane : slot;
+    const Ray r = ray_of(RayPre{slot_v3(L, SLOT_O, sl), V3{0.f, 0.f, 0.f}, slot_v3(L, SLOT_INV, sl),
+                                L.f[SLOT_SX][sl], L.f[SLOT_SY][sl], __float_as_int(L.f[SLOT_AXES][sl])});
+    const V3 sinv = V3{r.inv.x * unit, r.inv.y * unit, r.inv.z * unit};
+    const int rx = signbit(r.inv.x) ? 16 : 0, ry = signbit(r.inv.y) ? 16 : 0, rz = signbit(r.inv.z) ? 16 : 0;
+    for (;;) {  // walk until lanes can be given rays
+      bool pop = false;
+      for (;;) {
+        const bool inner = slot >= 0 && !pop && !(cur & HDOF_LEAF_BIT);
+        const int ni = (int)__popcll(__builtin_amdgcn_ballot_w64(inner));
+        if (ni == 0 || (ni < HDOF_MIN_BOX &&
+                        __builtin_amdgcn_ballot_w64(slot >= 0 && (pop || (cur & HDOF_LEAF_BIT))) != 0ull))
+          break;
+        // each internal node is entered at most once per ray: more steps
+        // than the wave's rays can take before one of them is done mean a
+        // malformed tree, and the rays stop here
+        if (++stall > stall_max) {
+          if (lane == 0) atomicOr(A.flags, HDOF_FLAG_STACK_OVERFLOW);
+          pop = slot >= 0;
+          break;
+        }
+        if (inner) {
+          if (COUNT) wk.visits++;
+          const float4* nd = A.hnodes + 3 * (size_t)cur;
+          const float4 n0 = nd[0], n1 = nd[1];
+          const float3 n2 = *(const float3*)(nd + 2);
+          const V3 base = V3{fmaf(n0.x, sinv.x, r.oinv.x), fmaf(n0.y, sinv.y, r.oinv.y), fmaf(n0.z, sinv.z, r.oinv.z)};
+          float t0, t1;
+          const bool h0 = box_hit_half(__float_as_uint(n1.x), __float_as_uint(n1.z), __float_as_uint(n2.x), sinv, base,
+                                       rx, ry, rz, b.t, t0);
+          const bool h1 = box_hit_half(__float_as_uint(n1.y), __float_as_uint(n1.w), __float_as_uint(n2.y), sinv, base,
+                                       rx, ry, rz, b.t, t1);
+          const unsigned c0 = __float_as_uint(n2.z), c1 = __float_as_uint(n0.w);
+          const bool near0 = h0 && (!h1 || t0 <= t1);
+          cur = near0 ? c0 : c1;
+          if (h0 && h1) {
+            const unsigned far = near0 ? c1 : c0;
+            if (sp < HDOF_LDS_STACK)
+              L.stk[sp][lane] = (int)far;
+            else if (sp < HDOF_LDS_STACK + HDOF_SPILL_STACK)
+              spill[sp - HDOF_LDS_STACK] = (int)far;
+            else
+              atomicOr(A.flags, HDOF_FLAG_STACK_OVERFLOW), --sp;
+            ++sp;
+          }
+          pop = !h0 && !h1;
+          if (pop && sp > 0) {
+            --sp;
+            cur = (unsigned)(sp < HDOF_LDS_STACK ? L.stk[sp][lane] : spill[sp - HDOF_LDS_STACK]);
+            pop = false;
+          }
+        }
+      }
+      if (slot >= 0 && !pop && (cur & HDOF_LEAF_BIT)) {
+        test_leaf(r, A.tris, cur, b);
+        if (COUNT) wk.tests += (int)((cur >> 27) & 0xF) + 1;
+        pop = true;
+        if (sp > 0) {
+          --sp;
+          cur = (unsigned)(sp < HDOF_LDS_STACK ? L.stk[sp][lane] : spill[sp - HDOF_LDS_STACK]);
+          pop = false;
+        }
+      }
+      if (pop) {  // the stack is empty: the ray's hit goes to its slot
+        L.f[SLOT_INV][slot] = b.t;
+        L.f[SLOT_INV + 1][slot] = __int_as_float(b.tri);
+        L.f[SLOT_INV + 2][slot] = __int_as_float(b.id);
+        L.f[SLOT_DONE][slot] = __int_as_float(1);
+        slot = -1;
+        if (COUNT) {
+          atomicAdd(&A.counters[3], 1ull);
+          atomicAdd(&A.counters[4], (unsigned long long)wk.visits);
+          atomicAdd(&A.counters[5], (unsigned long long)wk.tests);
+          wk = Work{0, 0};
+        }
+      }
+      if (__builtin_amdgcn_ballot_w64(pop) != 0ull) stall = 0;
+      const int nidle = (int)__popcll(__builtin_amdgcn_ballot_w64(slot < 0));
+      if (nidle >= (next < count ? HDOF_HAND_OUT : (drained ? 64 : refill))) break;
     }
   }
 }
@@ -712,7 +827,7 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
     if (blockIdx.x == 0 && t == 0) atomicOr(A.flags, HDOF_FLAG_CAPACITY);
     total = (int)A.cap;
   }
-  if (!keep_block(A, total)) return;
+  if ((int)blockIdx.x >= kept_blocks(A, total)) return;
   const int nseg = A.segments;
   int seg = blockIdx.x % nseg, tried = 0;
   while (tried < nseg) {
@@ -726,13 +841,20 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
       continue;
     }
     const int e = base + lane;
-    Ray r;
+    V3 O = V3{0.0f, 0.0f, 0.0f}, D = V3{0.0f, 0.0f, 1.0f};
     float S1 = A.v0.l.S1;
-    const bool live = entry_ray<BATCH>(A, pxb, e, hi, r, S1);
-    if (!live) r = make_ray(V3{0.0f, 0.0f, 0.0f}, V3{0.0f, 0.0f, 1.0f});
+    const bool live = entry_ray<BATCH>(A, pxb, e, hi, O, D, S1);
+    const Ray r = make_ray(O, D);
     Work wk{0, 0};
     const Best b = traverse_wave_any<COUNT>(A.nodes, A.tris, A.n_nodes, r, live, A.flags, wk);
-    if (live) store_ray<COUNT>(A, r, b, S1, e, wk);
+    if (live) {
+      store_ray(A, r.O, r.D, b, S1, e);
+      if (COUNT) {
+        atomicAdd(&A.counters[3], 1ull);
+        atomicAdd(&A.counters[4], (unsigned long long)wk.visits);
+        atomicAdd(&A.counters[5], (unsigned long long)wk.tests);
+      }
+    }
   }
 }
 
@@ -945,6 +1067,8 @@ __global__ void k_zero_f(float* __restrict__ a, int n) {
 TraceArgs base_args(hdof_ctx* ctx, const hdof_scene* sc, const LightK& li, size_t cap) {
   TraceArgs A{};
   A.nodes = sc->nodes;
+  A.hnodes = sc->hnodes;
+  A.unit = sc->unit;
   A.tris = sc->tris;
   A.n_nodes = sc->n_nodes;
   A.albedo = sc->albedo;

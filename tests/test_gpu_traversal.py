@@ -1,0 +1,107 @@
+"""GPU parity of the per-lane traversal's half-precision boxes and ray slots.
+
+The boxes are halves about their node's centre in a power-of-two unit of the
+scene, widened outwards, so they are tried where that could lose a hit:
+scenes scaled by powers of ten, far from the origin, flat, and of one to a
+few triangles; and the slots at queue lengths around a wave's 64 rays and
+with rays of one pixel only.  Expected values: the FP64 oracle's closest hit
+per ray, ids equal except on the rays it flags (within 1e-5 of an edge)."""
+from __future__ import annotations
+
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+import scenegen as sg
+
+pytestmark = pytest.mark.gpu
+
+import oracle  # noqa: E402
+from gpu_common import DEV, excl_cumsum, print_case, to_dev, upload_scene  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def hd():
+    from paper_2210_04981_amd import hdof
+    return hdof
+
+
+@pytest.fixture(scope="module")
+def ctx(hd):
+    c = hd.hdof_create(0)
+    yield c
+    c.close()
+
+
+def check_hits(hd, ctx, scene, cfg, spp, z_rel):
+    H, W = spp.shape
+    osc = oracle.Scene(scene.verts, scene.albedo)
+    ref = oracle.trace(osc, cfg.camera, cfg.lens, cfg.light, spp, seed=5, frame=1, view=2, per_ray=True)
+    sc = upload_scene(hd, ctx, scene)
+    smax = max(1, int(spp.max()))
+    cap = H * W * smax
+    rid = torch.full((cap,), -7, dtype=torch.int32, device=DEV)
+    rz = torch.zeros(cap, dtype=torch.float32, device=DEV)
+    n = int(spp.sum())
+    hd.hdof_trace_thin_lens(ctx, sc, hd.camera_of(cfg.camera), hd.lens_of(cfg.lens), hd.light_of(cfg.light), smax,
+                            to_dev(spp.astype(np.uint8)), to_dev(excl_cumsum(spp).astype(np.int32)),
+                            to_dev(np.array([n], np.int32)), seed=5, frame=1, view=2, ray_tri_id=rid, ray_depth=rz)
+    torch.cuda.synchronize()
+    ctx.sync()
+    g_id, g_z = rid.cpu().numpy(), rz.cpu().numpy()[:n].astype(np.float64)
+    assert (g_id[n:] == -7).all()
+    bad = (g_id[:n] != ref["ray_id"]) & (ref["ray_amb"] == 0)
+    assert not bad.any(), f"{bad.sum()} of {n} unambiguous rays hit other triangles"
+    same = (g_id[:n] == ref["ray_id"]) & (g_id[:n] >= 0)
+    rel = np.abs(g_z[same] - ref["ray_z"][same]) / np.abs(ref["ray_z"][same])
+    assert rel.size == 0 or rel.max() < z_rel, rel.max()
+    sc.close()
+
+
+# fp32 hit distances: 1e-3 relative at worst (grazing hits), as for the
+# library's other traversal tests; a scene at distance d from the origin adds
+# the rounding of its coordinates, 2^-24 d over the hit's own scale
+@pytest.mark.parametrize("scale,shift", [(1.0, 0.0), (1e-3, 0.0), (1e3, 0.0), (1.0, 64.0)])
+def test_scaled_and_shifted_scene(hd, ctx, scale, shift):
+    print_case(f"half boxes: scale {scale} shift {shift}")
+    cfg = sg.config_tiny(aperture_override=0.2)
+    scene = sg.tiny_scene(3)
+    # the shift keeps every coordinate exact in float32, so both sides trace the same triangles
+    verts = (np.round(scene.verts * 4096) / 4096 * scale + shift).astype(np.float32)
+    cam = replace(cfg.camera, eye=(np.asarray(cfg.camera.eye) * scale + shift).astype(np.float32))
+    lens = replace(cfg.lens, aperture=float(np.float32(cfg.lens.aperture * scale)),
+                   focus_distance=float(np.float32(cfg.lens.focus_distance * scale)),
+                   focal_length=float(np.float32(cfg.lens.focal_length * scale)))
+    spp = np.full((cam.height, cam.width), 2, np.int32)
+    check_hits(hd, ctx, sg.Scene(verts, scene.albedo), replace(cfg, camera=cam, lens=lens), spp, 1e-3)
+
+
+@pytest.mark.parametrize("n", [1, 2, 4, 5, 9])
+def test_flat_scene_of_few_triangles(hd, ctx, n):
+    """Triangles in one plane facing the camera: node boxes of no extent in z."""
+    print_case(f"half boxes: {n} coplanar triangles")
+    rng = np.random.default_rng(n)
+    v = np.concatenate([rng.uniform(-1, 1, (n, 3, 2)), np.full((n, 3, 1), 2.5)], -1).reshape(n, 9).astype(np.float32)
+    cfg = sg.config_tiny(aperture_override=0.2)
+    check_hits(hd, ctx, sg.Scene(v, rng.uniform(0, 1, (n, 3)).astype(np.float32)), cfg,
+               np.full((64, 64), 1, np.int32), 1e-5)
+
+
+@pytest.mark.parametrize("total", [1, 7, 63, 64, 65, 129, 511, 4097])
+@pytest.mark.parametrize("refill", [1, 47, 64])
+def test_queue_lengths(hd, ctx, total, refill):
+    """Queues shorter than the segments, around a wave's slots, and of a
+    single pixel's rays."""
+    print_case(f"ray slots: {total} rays, refill {refill}")
+    hd.hdof_set_tuning(ctx, refill=refill)
+    cfg = sg.config_tiny(aperture_override=0.2)
+    spp = np.zeros((64, 64), np.int32)
+    left, p = total, 1000
+    while left > 0:
+        spp.reshape(-1)[p] = min(255, left)
+        left -= min(255, left)
+        p += 37
+    check_hits(hd, ctx, sg.tiny_scene(1), cfg, spp, 1e-3)
+    hd.hdof_set_tuning(ctx)
