@@ -236,6 +236,7 @@ extern "C" void hdof_destroy(hdof_ctx* ctx) {
                 &ctx->sp_cn, &ctx->sp_cf, &ctx->sp_coc};
   for (Buf* b : all) buf_free(*b);
   for (hipEvent_t e : ctx->prof_events) hipEventDestroy(e);
+  buf_free(ctx->bvh_scratch);
   buf_free(ctx->ppb_args);
   buf_free(ctx->ppb_partial);
   buf_free(ctx->b_arena);
@@ -294,13 +295,8 @@ extern "C" void hdof_scene_destroy(hdof_scene* sc) {
   if (!sc) return;
   hipSetDevice(sc->ctx->device);
   hipDeviceSynchronize();
-  if (sc->nodes) hipFree(sc->nodes);
-  if (sc->hnodes) hipFree(sc->hnodes);
-  if (sc->unit) hipFree(sc->unit);
-  if (sc->tris) hipFree(sc->tris);
-  if (sc->albedo) hipFree(sc->albedo);
+  if (sc->mem) hipFree(sc->mem);
   if (sc->spec) hipFree(sc->spec);
-  if (sc->depth_out) hipFree(sc->depth_out);
   delete sc;
 }
 

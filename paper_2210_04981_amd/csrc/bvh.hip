@@ -13,51 +13,45 @@
 //   -> traversal layout: per internal node the boxes of both children in
 //      full (64 B, the wave-coherent walk) and in half precision about their
 //      centre (48 B, the per-lane walk), triangles as 3 float4 in leaf order.
+#include <cmath>
+#include <utility>
+
 #include "hdof_internal.h"
 
 #define RS_THREADS 256
-#define RS_ITEMS 8
+#define RS_ITEMS 4
 #define RS_TILE (RS_THREADS * RS_ITEMS)
 #define HDOF_BVH_LEAF 4
 #define PLOC_R 16
 
 namespace {
 
-__global__ void k_centroid_bounds(const float* __restrict__ v, int n, float* __restrict__ part) {
-  __shared__ float red[6][RS_THREADS];
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+#define BOUNDS_BLOCKS 256  // partial bounds: one per thread of the kernel that reduces them
+
+// the block's minima (6 values: minimum, -maximum) of `v`, in every thread
+__device__ inline void block_min6(float v[6], float (*red)[RS_THREADS / 64]) {
+  for (int a = 0; a < 6; ++a) {
+    for (int o = 32; o > 0; o >>= 1) v[a] = fminf(v[a], __shfl_xor(v[a], o));
+    if ((threadIdx.x & 63) == 0) red[a][threadIdx.x >> 6] = v[a];
+  }
+  __syncthreads();
+  for (int a = 0; a < 6; ++a) v[a] = fminf(fminf(red[a][0], red[a][1]), fminf(red[a][2], red[a][3]));
+}
+
+__global__ __launch_bounds__(RS_THREADS) void k_centroid_bounds(const float* __restrict__ v, int n,
+                                                                float* __restrict__ part) {
+  __shared__ float red[6][RS_THREADS / 64];
+  float m[6] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
   for (int i = blockIdx.x * RS_THREADS + threadIdx.x; i < n; i += gridDim.x * RS_THREADS) {
     const float* t = v + 9 * (size_t)i;
     for (int a = 0; a < 3; ++a) {
       float c = (t[a] + t[3 + a] + t[6 + a]) * (1.0f / 3.0f);
-      lo[a] = fminf(lo[a], c);
-      hi[a] = fmaxf(hi[a], c);
+      m[a] = fminf(m[a], c);
+      m[3 + a] = fminf(m[3 + a], -c);
     }
   }
-  for (int a = 0; a < 3; ++a) {
-    red[a][threadIdx.x] = lo[a];
-    red[3 + a][threadIdx.x] = hi[a];
-  }
-  __syncthreads();
-  for (int s = RS_THREADS / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s)
-      for (int a = 0; a < 3; ++a) {
-        red[a][threadIdx.x] = fminf(red[a][threadIdx.x], red[a][threadIdx.x + s]);
-        red[3 + a][threadIdx.x] = fmaxf(red[3 + a][threadIdx.x], red[3 + a][threadIdx.x + s]);
-      }
-    __syncthreads();
-  }
-  if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
-}
-
-__global__ void k_reduce_bounds(float* __restrict__ part, int nb) {
-  // single thread: nb is small (<= 1024)
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  for (int b = 1; b < nb; ++b)
-    for (int a = 0; a < 3; ++a) {
-      part[a] = fminf(part[a], part[6 * b + a]);
-      part[3 + a] = fmaxf(part[3 + a], part[6 * b + 3 + a]);
-    }
+  block_min6(m, red);
+  if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = m[threadIdx.x];
 }
 
 __device__ inline uint64_t spread21(uint64_t x) {
@@ -70,16 +64,28 @@ __device__ inline uint64_t spread21(uint64_t x) {
   return x;
 }
 
-__global__ void k_morton(const float* __restrict__ v, int n, const float* __restrict__ bounds,
-                         uint64_t* __restrict__ keys, int* __restrict__ vals) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
+// Morton codes of the centroids in the bounds that the partial ones (nparts
+// <= 256) reduce to; the albedo's copy too
+__global__ __launch_bounds__(RS_THREADS) void k_morton(const float* __restrict__ v, int n,
+                                                       const float* __restrict__ part, int nparts,
+                                                       const float* __restrict__ albedo, uint64_t* __restrict__ keys,
+                                                       int* __restrict__ vals, float* __restrict__ alb_out) {
+  __shared__ float red[6][RS_THREADS / 64];
+  float m[6];
+  for (int a = 0; a < 6; ++a) m[a] = (int)threadIdx.x < nparts ? part[6 * threadIdx.x + a] : INFINITY;
+  block_min6(m, red);
+  const int i0 = blockIdx.x * RS_THREADS, i = i0 + threadIdx.x;
+  for (int k = 0; k < 3; ++k) {
+    const size_t j = 3 * (size_t)i0 + k * RS_THREADS + threadIdx.x;
+    if (j < 3 * (size_t)n) alb_out[j] = albedo[j];
+  }
   if (i >= n) return;
   const float* t = v + 9 * (size_t)i;
   uint64_t q[3];
   for (int a = 0; a < 3; ++a) {
     float c = (t[a] + t[3 + a] + t[6 + a]) * (1.0f / 3.0f);
-    float ext = bounds[3 + a] - bounds[a];
-    float u = ext > 0.0f ? (c - bounds[a]) / ext : 0.5f;
+    float ext = -m[3 + a] - m[a];
+    float u = ext > 0.0f ? (c - m[a]) / ext : 0.5f;
     u = fminf(fmaxf(u, 0.0f), 1.0f);
     q[a] = (uint64_t)fminf(u * 2097152.0f, 2097151.0f);
   }
@@ -99,45 +105,52 @@ __global__ void k_rs_hist(const uint64_t* __restrict__ keys, int n, int shift, i
     if (i < n) atomicAdd(&h[(keys[i] >> shift) & 255], 1);
   }
   __syncthreads();
-  hist[threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+  hist[(size_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
-// exclusive scan of m ints by one block of 1024 threads (chunked)
-__global__ void k_scan_single(int* __restrict__ a, int m, int* __restrict__ total) {
-  __shared__ int part[1024];
-  int t = threadIdx.x;
-  int chunk = (m + 1023) / 1024;
-  int lo = t * chunk, hi = min(m, lo + chunk);
-  int s = 0;
-  for (int i = lo; i < hi; ++i) s += a[i];
-  part[t] = s;
+// inclusive scan of one value per thread of a block of four waves
+__device__ inline int block_scan(int v, int* part) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(v, o);
+    if (lane >= o) v += u;
+  }
+  if (lane == 63) part[wave] = v;
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    int v = t >= off ? part[t - off] : 0;
-    __syncthreads();
-    part[t] += v;
+  for (int w = 0; w < wave; ++w) v += part[w];
+  return v;
+}
+
+// each digit's counts over the blocks, one digit per block: exclusive scan
+// in place and the digit's total (a single block over all digits' counts
+// took 35 us a pass for 200k keys)
+__global__ __launch_bounds__(RS_THREADS) void k_rs_rows(int* __restrict__ hist, int nblocks, int* __restrict__ tot) {
+  __shared__ int part[RS_THREADS / 64];
+  int* row = hist + (size_t)blockIdx.x * nblocks;
+  int run = 0;
+  for (int i0 = 0; i0 < nblocks; i0 += RS_THREADS) {
+    const int i = i0 + threadIdx.x;
+    const int c = i < nblocks ? row[i] : 0;
+    const int incl = block_scan(c, part);
+    if (i < nblocks) row[i] = run + incl - c;
+    run += part[0] + part[1] + part[2] + part[3];
     __syncthreads();
   }
-  int run = part[t] - s;
-  for (int i = lo; i < hi; ++i) {
-    int x = a[i];
-    a[i] = run;
-    run += x;
-  }
-  if (total && t == 1023) *total = part[1023];
+  if (threadIdx.x == 0) tot[blockIdx.x] = run;
 }
 
 __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const uint64_t* __restrict__ kin,
                                                            const int* __restrict__ vin, int n,
                                                            int shift, int nblocks,
-                                                           const int* __restrict__ hist,
+                                                           const int* __restrict__ hist, const int* __restrict__ tot,
                                                            uint64_t* __restrict__ kout,
                                                            int* __restrict__ vout) {
   __shared__ int gbase[256];
   __shared__ int running[256];
   __shared__ int wcount[RS_THREADS / 64][256];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  gbase[t] = hist[t * nblocks + blockIdx.x];
+  __shared__ int part[RS_THREADS / 64];
+  gbase[t] = hist[(size_t)t * nblocks + blockIdx.x] + block_scan(tot[t], part) - tot[t];
   running[t] = 0;
   for (int w = 0; w < RS_THREADS / 64; ++w) wcount[w][t] = 0;
   __syncthreads();
@@ -178,18 +191,6 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const uint64_t* __res
   }
 }
 
-// ---- leaves ------------------------------------------------------------------
-__global__ void k_leaf_boxes(const float* __restrict__ v, const int* __restrict__ order, int n,
-                             float* __restrict__ lbox) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float* p = v + 9 * (size_t)order[i];
-  for (int a = 0; a < 3; ++a) {
-    lbox[6 * (size_t)i + a] = fminf(p[a], fminf(p[3 + a], p[6 + a]));
-    lbox[6 * (size_t)i + 3 + a] = fmaxf(p[a], fmaxf(p[3 + a], p[6 + a]));
-  }
-}
-
 // ---- PLOC clustering -----------------------------------------------------------
 // cluster codes: >= 0 internal node (build numbering), < 0 ~leaf (Morton position)
 __device__ inline float half_area(float4 lo, float4 hi) {
@@ -197,65 +198,103 @@ __device__ inline float half_area(float4 lo, float4 hi) {
   return dx * dy + dy * dz + dz * dx;
 }
 
-__global__ void k_leaf_clusters(const float* __restrict__ lbox, int n, int* __restrict__ cid,
-                                float4* __restrict__ cbox, int2* __restrict__ csz) {
+// leaf boxes in Morton order, one cluster each
+__global__ void k_leaf_clusters(const float* __restrict__ v, const int* __restrict__ order, int n,
+                                float* __restrict__ lbox, int* __restrict__ cid, float4* __restrict__ cbox,
+                                int2* __restrict__ csz, int2* __restrict__ state) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) state[0] = make_int2(n, n - 2);  // clusters, next internal node
   if (i >= n) return;
-  const float* b = lbox + 6 * (size_t)i;
+  const float* p = v + 9 * (size_t)order[i];
+  float b[6];
+  for (int a = 0; a < 3; ++a) {
+    b[a] = fminf(p[a], fminf(p[3 + a], p[6 + a]));
+    b[3 + a] = fmaxf(p[a], fmaxf(p[3 + a], p[6 + a]));
+  }
+  for (int a = 0; a < 6; ++a) lbox[6 * (size_t)i + a] = b[a];
   cid[i] = ~i;
   cbox[2 * (size_t)i] = make_float4(b[0], b[1], b[2], 0.0f);
   cbox[2 * (size_t)i + 1] = make_float4(b[3], b[4], b[5], 0.0f);
   csz[i] = make_int2(1, 0);  // (triangles, kept internal nodes) of the subtree
 }
 
-// nearest neighbour within +-PLOC_R positions by merged-box area; ties go to
-// the lower index (j runs upwards with a strict comparison)
-__global__ __launch_bounds__(256) void k_ploc_nn(const float4* __restrict__ cbox, int m, int* __restrict__ nn) {
-  __shared__ float4 blo[256 + 2 * PLOC_R], bhi[256 + 2 * PLOC_R];
-  const int base = blockIdx.x * 256 - PLOC_R;
-  for (int t = threadIdx.x; t < 256 + 2 * PLOC_R; t += 256) {
-    int g = base + t;
+// the half area of the union of two boxes
+__device__ inline float merged_area(float4 lo, float4 hi, float4 l2, float4 h2) {
+  return half_area(make_float4(fminf(lo.x, l2.x), fminf(lo.y, l2.y), fminf(lo.z, l2.z), 0.f),
+                   make_float4(fmaxf(hi.x, h2.x), fmaxf(hi.y, h2.y), fmaxf(hi.z, h2.z), 0.f));
+}
+
+// One clustering round over the state's m clusters, first half: each
+// cluster's nearest neighbour within +-PLOC_R positions by merged-box area
+// (ties go to the lower index: j runs upwards with a strict comparison), and
+// whether the choice is mutual.  A block also finds its neighbours' choices
+// within the window, so no other block's result is needed.  mate[i]: the
+// mutual neighbour, else -1; count[block]: clusters that survive the round,
+// and merges (upper half).  m is read on the device, so the host enqueues
+// rounds without waiting for their outcome: with a copy and a wait per round
+// and single-block scans the 67 rounds of 200k triangles took 4 ms.
+__global__ __launch_bounds__(256) void k_ploc_find(const float4* __restrict__ cbox, const int2* __restrict__ state,
+                                                   int* __restrict__ mate, unsigned long long* __restrict__ count) {
+  __shared__ float4 blo[256 + 4 * PLOC_R], bhi[256 + 4 * PLOC_R];
+  __shared__ int nn[256 + 2 * PLOC_R];
+  __shared__ int cs[4], cl[4];
+  const int m = state->x;
+  const int first = blockIdx.x * 256;
+  if (m <= 1 || first >= m) return;
+  const int base = first - 2 * PLOC_R, t = threadIdx.x;
+  for (int k = t; k < 256 + 4 * PLOC_R; k += 256) {
+    const int g = base + k;
     if (g >= 0 && g < m) {
-      blo[t] = cbox[2 * (size_t)g];
-      bhi[t] = cbox[2 * (size_t)g + 1];
+      blo[k] = cbox[2 * (size_t)g];
+      bhi[k] = cbox[2 * (size_t)g + 1];
     }
   }
   __syncthreads();
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= m) return;
-  const int li = i - base;
-  const float4 lo = blo[li], hi = bhi[li];
-  float best = INFINITY;
-  int bj = -1;
-  for (int d = -PLOC_R; d <= PLOC_R; ++d) {
-    int j = i + d;
-    if (d == 0 || j < 0 || j >= m) continue;
-    const float4 l2 = blo[li + d], h2 = bhi[li + d];
-    float a = half_area(make_float4(fminf(lo.x, l2.x), fminf(lo.y, l2.y), fminf(lo.z, l2.z), 0.f),
-                        make_float4(fmaxf(hi.x, h2.x), fmaxf(hi.y, h2.y), fmaxf(hi.z, h2.z), 0.f));
-    if (a < best) {
-      best = a;
-      bj = j;
+  for (int k = t; k < 256 + 2 * PLOC_R; k += 256) {
+    const int i = first - PLOC_R + k, li = k + PLOC_R;
+    int bj = -1;
+    if (i >= 0 && i < m) {
+      const float4 lo = blo[li], hi = bhi[li];
+      float best = INFINITY;
+      for (int d = -PLOC_R; d <= PLOC_R; ++d) {
+        const int j = i + d;
+        if (d == 0 || j < 0 || j >= m) continue;
+        const float a = merged_area(lo, hi, blo[li + d], bhi[li + d]);
+        if (a < best) {
+          best = a;
+          bj = j;
+        }
+      }
     }
+    nn[k] = bj;
   }
-  nn[i] = bj;
+  __syncthreads();
+  const int i = first + t;
+  int j = -1;
+  if (i < m) {
+    j = nn[t + PLOC_R];
+    if (j >= 0 && nn[j - first + PLOC_R] != i) j = -1;
+    mate[i] = j;
+  }
+  const unsigned long long sv = __ballot(i < m && !(j >= 0 && i > j)), ld = __ballot(i < m && j > i);
+  if ((t & 63) == 0) {
+    cs[t >> 6] = __popcll(sv);
+    cl[t >> 6] = __popcll(ld);
+  }
+  __syncthreads();
+  if (t == 0)
+    count[blockIdx.x] = (unsigned long long)(unsigned)(cs[0] + cs[1] + cs[2] + cs[3]) |
+                        (unsigned long long)(unsigned)(cl[0] + cl[1] + cl[2] + cl[3]) << 32;
 }
 
-// bits 0..31: the cluster survives; bits 32..63: it leads a merge
-__global__ void k_ploc_flags(const int* __restrict__ nn, int m, unsigned long long* __restrict__ fl) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  int j = nn[i];
-  bool mutual = j >= 0 && nn[j] == i;
-  fl[i] = (unsigned long long)((mutual && i > j) ? 0 : 1) | ((unsigned long long)((mutual && i < j) ? 1 : 0) << 32);
-}
-
-// exclusive scan of m uint64 by one block of 1024 threads; total to *tot
-__global__ void k_scan64(unsigned long long* __restrict__ a, int m, unsigned long long* __restrict__ tot) {
+// exclusive scan of the blocks' counts in place by one block (scenes of many
+// blocks: there the merging blocks' own sums would be quadratic)
+__global__ __launch_bounds__(1024) void k_ploc_scan(unsigned long long* __restrict__ a,
+                                                    const int2* __restrict__ state) {
   __shared__ unsigned long long part[1024];
-  int t = threadIdx.x;
-  int chunk = (m + 1023) / 1024;
-  int lo = min(m, t * chunk), hi = min(m, lo + chunk);
+  const int m = (state->x + 255) / 256;
+  const int t = threadIdx.x, chunk = (m + 1023) / 1024;
+  const int lo = min(m, t * chunk), hi = min(m, lo + chunk);
   unsigned long long s = 0;
   for (int i = lo; i < hi; ++i) s += a[i];
   part[t] = s;
@@ -272,52 +311,201 @@ __global__ void k_scan64(unsigned long long* __restrict__ a, int m, unsigned lon
     a[i] = run;
     run += x;
   }
-  if (t == 1023) *tot = part[1023];
 }
 
-// merged clusters take internal node indices counting down from `next`, so
-// the last merge (the root) gets index 0
-__global__ void k_ploc_merge(const int* __restrict__ nn, int m, const unsigned long long* __restrict__ pre,
-                             const int* __restrict__ cid, const float4* __restrict__ cbox,
-                             const int2* __restrict__ csz, int next, int* __restrict__ oid,
-                             float4* __restrict__ obox, int2* __restrict__ osz, int* __restrict__ bl,
-                             int* __restrict__ br, float* __restrict__ bbox, int2* __restrict__ bsz) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  int j = nn[i];
-  bool mutual = j >= 0 && nn[j] == i;
-  if (mutual && i > j) return;
-  unsigned long long p = pre[i];
-  int pos = (int)(p & 0xffffffffull);
-  if (mutual) {
-    int node = next - (int)(p >> 32);
-    float4 l1 = cbox[2 * (size_t)i], h1 = cbox[2 * (size_t)i + 1];
-    float4 l2 = cbox[2 * (size_t)j], h2 = cbox[2 * (size_t)j + 1];
-    float4 lo = make_float4(fminf(l1.x, l2.x), fminf(l1.y, l2.y), fminf(l1.z, l2.z), 0.f);
-    float4 hi = make_float4(fmaxf(h1.x, h2.x), fmaxf(h1.y, h2.y), fmaxf(h1.z, h2.z), 0.f);
-    int2 s1 = csz[i], s2 = csz[j];
-    int cnt = s1.x + s2.x;
-    int2 sz = make_int2(cnt, s1.y + s2.y + (cnt > HDOF_BVH_LEAF ? 1 : 0));
-    bl[node] = cid[i];
-    br[node] = cid[j];
-    float* bb = bbox + 6 * (size_t)node;
-    bb[0] = lo.x;
-    bb[1] = lo.y;
-    bb[2] = lo.z;
-    bb[3] = hi.x;
-    bb[4] = hi.y;
-    bb[5] = hi.z;
-    bsz[node] = sz;
-    oid[pos] = node;
-    obox[2 * (size_t)pos] = lo;
-    obox[2 * (size_t)pos + 1] = hi;
-    osz[pos] = sz;
-  } else {
-    oid[pos] = cid[i];
-    obox[2 * (size_t)pos] = cbox[2 * (size_t)i];
-    obox[2 * (size_t)pos + 1] = cbox[2 * (size_t)i + 1];
-    osz[pos] = csz[i];
+// what a merge writes about its node; returns the subtree's size
+__device__ inline int2 ploc_node(int node, int c1, int c2, float4 lo, float4 hi, int2 s1, int2 s2,
+                                 int* __restrict__ bl, int* __restrict__ br, float* __restrict__ bbox,
+                                 int2* __restrict__ bsz) {
+  const int cnt = s1.x + s2.x;
+  const int2 sz = make_int2(cnt, s1.y + s2.y + (cnt > HDOF_BVH_LEAF ? 1 : 0));
+  bl[node] = c1;
+  br[node] = c2;
+  float* bb = bbox + 6 * (size_t)node;
+  bb[0] = lo.x;
+  bb[1] = lo.y;
+  bb[2] = lo.z;
+  bb[3] = hi.x;
+  bb[4] = hi.y;
+  bb[5] = hi.z;
+  bsz[node] = sz;
+  return sz;
+}
+
+// Second half: mutual pairs merge into the lower one's place, the survivors
+// are compacted.  Merged clusters take internal node indices counting down
+// from `next`, so the last merge (the root) gets index 0.  The block of the
+// last cluster writes the next round's state.
+__global__ __launch_bounds__(256) void k_ploc_merge(const int* __restrict__ mate,
+                                                    const unsigned long long* __restrict__ count, int scanned,
+                                                    const int2* __restrict__ state, int2* __restrict__ state_out,
+                                                    const int* __restrict__ cid, const float4* __restrict__ cbox,
+                                                    const int2* __restrict__ csz, int* __restrict__ oid,
+                                                    float4* __restrict__ obox, int2* __restrict__ osz,
+                                                    int* __restrict__ bl, int* __restrict__ br,
+                                                    float* __restrict__ bbox, int2* __restrict__ bsz) {
+  __shared__ int2 red[4], wave_n[4];
+  const int m = state->x, next = state->y;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, blk = blockIdx.x;
+  const int nblk = (m + 255) / 256;
+  if (m <= 1) {
+    if (blk == 0 && t == 0) *state_out = make_int2(m, next);
+    return;
   }
+  if (blk >= nblk) return;
+  int2 before = make_int2(0, 0);
+  if (scanned) {
+    before = make_int2((int)(count[blk] & 0xffffffffull), (int)(count[blk] >> 32));
+  } else {
+    for (int b = t; b < blk; b += 256) {
+      const unsigned long long c = count[b];
+      before.x += (int)(c & 0xffffffffull);
+      before.y += (int)(c >> 32);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      before.x += __shfl_xor(before.x, o);
+      before.y += __shfl_xor(before.y, o);
+    }
+    if (lane == 0) red[wave] = before;
+  }
+  const int i = blk * 256 + t;
+  const int j = i < m ? mate[i] : -1;
+  const bool lead = i < m && j > i, keep = i < m && !(j >= 0 && i > j);
+  const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  const unsigned long long km = __ballot(keep), lm = __ballot(lead);
+  if (lane == 0) wave_n[wave] = make_int2(__popcll(km), __popcll(lm));
+  __syncthreads();
+  if (!scanned)
+    before = make_int2(red[0].x + red[1].x + red[2].x + red[3].x, red[0].y + red[1].y + red[2].y + red[3].y);
+  if (blk == nblk - 1 && t == 0)
+    *state_out = make_int2(before.x + wave_n[0].x + wave_n[1].x + wave_n[2].x + wave_n[3].x,
+                           next - (before.y + wave_n[0].y + wave_n[1].y + wave_n[2].y + wave_n[3].y));
+  for (int w = 0; w < wave; ++w) {
+    before.x += wave_n[w].x;
+    before.y += wave_n[w].y;
+  }
+  if (!keep) return;
+  const int pos = before.x + (int)__popcll(km & lt);
+  float4 lo = cbox[2 * (size_t)i], hi = cbox[2 * (size_t)i + 1];
+  int id = cid[i];
+  int2 sz = csz[i];
+  if (lead) {
+    const int node = next - (before.y + (int)__popcll(lm & lt));
+    const float4 l2 = cbox[2 * (size_t)j], h2 = cbox[2 * (size_t)j + 1];
+    lo = make_float4(fminf(lo.x, l2.x), fminf(lo.y, l2.y), fminf(lo.z, l2.z), 0.f);
+    hi = make_float4(fmaxf(hi.x, h2.x), fmaxf(hi.y, h2.y), fmaxf(hi.z, h2.z), 0.f);
+    sz = ploc_node(node, id, cid[j], lo, hi, sz, csz[j], bl, br, bbox, bsz);
+    id = node;
+  }
+  oid[pos] = id;
+  obox[2 * (size_t)pos] = lo;
+  obox[2 * (size_t)pos + 1] = hi;
+  osz[pos] = sz;
+}
+
+// The remaining rounds of at most PLOC_TAIL clusters in one block, which
+// keeps them in LDS: most rounds of a build have few clusters, and two
+// launches each would cost more than their work.  A cluster's search is
+// shared by up to eight threads once the clusters leave that many idle.
+// Stops at one cluster, or at a round without a merge.
+#define PLOC_TAIL 1024
+__global__ __launch_bounds__(PLOC_TAIL) void k_ploc_tail(const int* __restrict__ cid, const float4* __restrict__ cbox,
+                                                         const int2* __restrict__ csz, int2* __restrict__ state,
+                                                         int* __restrict__ bl, int* __restrict__ br,
+                                                         float* __restrict__ bbox, int2* __restrict__ bsz) {
+  __shared__ float lox[PLOC_TAIL], loy[PLOC_TAIL], loz[PLOC_TAIL], hix[PLOC_TAIL], hiy[PLOC_TAIL], hiz[PLOC_TAIL];
+  __shared__ int nn[PLOC_TAIL], ids[PLOC_TAIL];
+  __shared__ int2 szs[PLOC_TAIL];
+  __shared__ int2 wave_n[PLOC_TAIL / 64];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int m = state->x, next = state->y;
+  if (m > PLOC_TAIL) return;
+  if (t < m) {
+    const float4 lo = cbox[2 * (size_t)t], hi = cbox[2 * (size_t)t + 1];
+    lox[t] = lo.x, loy[t] = lo.y, loz[t] = lo.z;
+    hix[t] = hi.x, hiy[t] = hi.y, hiz[t] = hi.z;
+    ids[t] = cid[t];
+    szs[t] = csz[t];
+  }
+  __syncthreads();
+  const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  while (m > 1) {
+    // nearest neighbours; window position w stands for the neighbour at
+    // w - PLOC_R below PLOC_R and w - PLOC_R + 1 above
+    const int sh = m <= PLOC_TAIL / 8 ? 3 : (m <= PLOC_TAIL / 4 ? 2 : (m <= PLOC_TAIL / 2 ? 1 : 0));
+    {
+      const int i = t >> sh, sub = t & ((1 << sh) - 1), per = (2 * PLOC_R) >> sh;
+      float best = INFINITY;
+      int bj = -1;
+      if (i < m) {
+        const float4 lo = make_float4(lox[i], loy[i], loz[i], 0.f), hi = make_float4(hix[i], hiy[i], hiz[i], 0.f);
+        for (int w = sub * per; w < (sub + 1) * per; ++w) {
+          const int j = i + w - PLOC_R + (w >= PLOC_R ? 1 : 0);
+          if (j < 0 || j >= m) continue;
+          const float a = merged_area(lo, hi, make_float4(lox[j], loy[j], loz[j], 0.f),
+                                      make_float4(hix[j], hiy[j], hiz[j], 0.f));
+          if (a < best) {
+            best = a;
+            bj = j;
+          }
+        }
+      }
+      for (int o = 1; o < 1 << sh; o <<= 1) {  // ties to the lower index
+        const float a = __shfl_xor(best, o);
+        const int j = __shfl_xor(bj, o);
+        if (j >= 0 && (bj < 0 || a < best || (a == best && j < bj))) {
+          best = a;
+          bj = j;
+        }
+      }
+      if (i < m && sub == 0) nn[i] = bj;
+    }
+    __syncthreads();
+    int j = -1;
+    if (t < m) {
+      j = nn[t];
+      if (j >= 0 && nn[j] != t) j = -1;
+    }
+    const bool lead = t < m && j > t, keep = t < m && !(j >= 0 && t > j);
+    const unsigned long long km = __ballot(keep), lm = __ballot(lead);
+    if (lane == 0) wave_n[wave] = make_int2(__popcll(km), __popcll(lm));
+    __syncthreads();
+    int2 before = make_int2(0, 0), all = make_int2(0, 0);
+    for (int w = 0; w < PLOC_TAIL / 64; ++w) {
+      const int2 c = wave_n[w];
+      if (w < wave) before.x += c.x, before.y += c.y;
+      all.x += c.x, all.y += c.y;
+    }
+    const int pos = before.x + (int)__popcll(km & lt);
+    float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
+    int id = 0;
+    int2 sz = make_int2(0, 0);
+    if (keep) {
+      lo = make_float4(lox[t], loy[t], loz[t], 0.f);
+      hi = make_float4(hix[t], hiy[t], hiz[t], 0.f);
+      id = ids[t];
+      sz = szs[t];
+      if (lead) {
+        const int node = next - (before.y + (int)__popcll(lm & lt));
+        lo = make_float4(fminf(lo.x, lox[j]), fminf(lo.y, loy[j]), fminf(lo.z, loz[j]), 0.f);
+        hi = make_float4(fmaxf(hi.x, hix[j]), fmaxf(hi.y, hiy[j]), fmaxf(hi.z, hiz[j]), 0.f);
+        sz = ploc_node(node, id, ids[j], lo, hi, sz, szs[j], bl, br, bbox, bsz);
+        id = node;
+      }
+    }
+    __syncthreads();
+    if (keep) {
+      lox[pos] = lo.x, loy[pos] = lo.y, loz[pos] = lo.z;
+      hix[pos] = hi.x, hiy[pos] = hi.y, hiz[pos] = hi.z;
+      ids[pos] = id;
+      szs[pos] = sz;
+    }
+    if (all.y == 0) break;
+    m = all.x;
+    next -= all.y;
+    __syncthreads();
+  }
+  if (t == 0) *state = make_int2(m, next);
 }
 
 __global__ void k_parents(int nint, const int* __restrict__ bl, const int* __restrict__ br,
@@ -356,26 +544,26 @@ __device__ inline void dfs_place(int code, int n, const int* __restrict__ bl, co
   }
 }
 
-__global__ void k_place_leaves(int n, const int* __restrict__ bl, const int* __restrict__ pint,
-                               const int* __restrict__ pleaf, const int2* __restrict__ bsz,
-                               int* __restrict__ leaf_off, int* __restrict__ depth_out) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int off, idx, d;
-  dfs_place(~i, n, bl, pint, pleaf, bsz, off, idx, d);
-  leaf_off[i] = off;
-  atomicMax(depth_out, d + 1);
-}
-
-__global__ void k_place_nodes(int nint, int n, const int* __restrict__ bl, const int* __restrict__ pint,
-                              const int* __restrict__ pleaf, const int2* __restrict__ bsz,
-                              int* __restrict__ node_off, int* __restrict__ node_idx) {
-  int a = blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= nint) return;
+// threads 0..n-1 place the leaves, the others the internal nodes; the tree
+// depth is reduced over a wave before the atomic (one per triangle took 37 us
+// of the pass for 200k triangles)
+__global__ void k_place(int n, int nint, const int* __restrict__ bl, const int* __restrict__ pint,
+                        const int* __restrict__ pleaf, const int2* __restrict__ bsz, int* __restrict__ leaf_off,
+                        int* __restrict__ node_off, int* __restrict__ node_idx, int* __restrict__ depth_out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
   int off = 0, idx = 0, d = 0;
-  if (a != 0) dfs_place(a, n, bl, pint, pleaf, bsz, off, idx, d);
-  node_off[a] = off;
-  node_idx[a] = idx;
+  if (i < n) {
+    dfs_place(~i, n, bl, pint, pleaf, bsz, off, idx, d);
+    leaf_off[i] = off;
+  } else if (i - n < nint) {
+    const int a = i - n;
+    if (a != 0) dfs_place(a, n, bl, pint, pleaf, bsz, off, idx, d);
+    node_off[a] = off;
+    node_idx[a] = idx;
+    d = 0;
+  }
+  for (int o = 32; o > 0; o >>= 1) d = max(d, __shfl_xor(d, o));
+  if ((threadIdx.x & 63) == 0 && d > 0) atomicMax(depth_out, d + 1);
 }
 
 __global__ void k_place_tris(const float* __restrict__ v, const int* __restrict__ order,
@@ -400,8 +588,7 @@ __device__ inline unsigned leaf_code(int first, int count) {
 // are widened by (2^-21 of the largest coordinate), which covers the
 // rounding of the plane distances that the traversal forms from the centre
 // and the offset.
-__global__ void k_box_unit(const float* __restrict__ root, float* __restrict__ unit) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__device__ inline float2 box_unit(const float* __restrict__ root) {
   float ext = 0.0f, big = 0.0f;
   for (int a = 0; a < 3; ++a) {
     ext = fmaxf(ext, root[3 + a] - root[a]);
@@ -410,8 +597,7 @@ __global__ void k_box_unit(const float* __restrict__ root, float* __restrict__ u
   int e = 0;
   frexpf(ext, &e);  // ext < 2^e
   e = ext > 0.0f && ext < INFINITY ? max(-100, min(100, e - 14)) : 0;
-  unit[0] = ldexpf(1.0f, e);
-  unit[1] = big * 4.76837158e-7f;
+  return make_float2(ldexpf(1.0f, e), big * 4.76837158e-7f);
 }
 
 // the box plane x in units above centre c, rounded outwards (dir -1 or 1)
@@ -433,8 +619,8 @@ __device__ inline unsigned half_plane(float x, float c, float unit, float margin
 // (centre, code 1), (x of both children, y of both), (z of both, code 0, -),
 // a pair of planes (minimum, maximum) per dword.
 __device__ inline void emit_half(float4* __restrict__ o, const float* b0, const float* b1, unsigned c0, unsigned c1,
-                                 const float* __restrict__ unit) {
-  const float s = unit[0], mg = unit[1];
+                                 float2 unit) {
+  const float s = unit.x, mg = unit.y;
   float c[3];
   unsigned pl[3][2];
   for (int a = 0; a < 3; ++a) {
@@ -454,9 +640,11 @@ __global__ void k_emit_nodes(int nint, const int* __restrict__ bl, const int* __
                              const int2* __restrict__ bsz, const float* __restrict__ bbox,
                              const float* __restrict__ lbox, const int* __restrict__ leaf_off,
                              const int* __restrict__ node_off, const int* __restrict__ node_idx,
-                             const float* __restrict__ unit, float4* __restrict__ nodes, float4* __restrict__ hnodes) {
+                             float* __restrict__ unit, float4* __restrict__ nodes, float4* __restrict__ hnodes) {
   int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= nint) return;
+  const float2 u = box_unit(bbox);  // node 0 is the root
+  if (a == 0) *unit = u.x;
   if (a != 0 && bsz[a].x <= HDOF_BVH_LEAF) return;
   int ch[2] = {bl[a], br[a]};
   float b[2][6];
@@ -479,13 +667,15 @@ __global__ void k_emit_nodes(int nint, const int* __restrict__ bl, const int* __
   o[1] = make_float4(b[1][0], b[1][3], b[1][1], b[1][4]);
   o[2] = make_float4(b[0][2], b[0][5], b[1][2], b[1][5]);
   o[3] = make_float4(__uint_as_float(code[0]), __uint_as_float(code[1]), 0.0f, 0.0f);
-  emit_half(hnodes + 3 * (size_t)node_idx[a], b[0], b[1], code[0], code[1], unit);
+  emit_half(hnodes + 3 * (size_t)node_idx[a], b[0], b[1], code[0], code[1], u);
 }
 
 // one triangle: a root whose second child box is empty
-__global__ void k_single_root(const float* __restrict__ lbox, const float* __restrict__ unit,
-                              float4* __restrict__ nodes, float4* __restrict__ hnodes) {
-  emit_half(hnodes, lbox, lbox, leaf_code(0, 1), leaf_code(0, 1), unit);
+__global__ void k_single_root(const float* __restrict__ lbox, float* __restrict__ unit, float4* __restrict__ nodes,
+                              float4* __restrict__ hnodes) {
+  const float2 u = box_unit(lbox);
+  *unit = u.x;
+  emit_half(hnodes, lbox, lbox, leaf_code(0, 1), leaf_code(0, 1), u);
   float4* o = nodes;
   o[0] = make_float4(lbox[0], lbox[3], lbox[1], lbox[4]);
   o[1] = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
@@ -498,143 +688,150 @@ __global__ void k_fill_int(int* p, int n, int v) {
   if (i < n) p[i] = v;
 }
 
-__global__ void k_copy_albedo(const float* __restrict__ a, int n3, float* __restrict__ o) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n3) o[i] = a[i];
-}
-
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
 }  // namespace
 
 hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* albedo, int n,
                              hdof_scene* sc, hipStream_t st) {
-  (void)ctx;
   const int nint = n > 1 ? n - 1 : 1;
   const int nb = cdiv(n, RS_TILE);
-  const int nbounds = min(1024, max(1, cdiv(n, RS_THREADS)));
-  // permanent storage (node slots for every internal node; collapsed
-  // subtrees leave the tail unused)
-  HDOF_HIP(hipMalloc(&sc->nodes, sizeof(float4) * 4 * (size_t)nint));
-  HDOF_HIP(hipMalloc(&sc->hnodes, sizeof(float4) * 3 * (size_t)nint));
-  HDOF_HIP(hipMalloc(&sc->unit, sizeof(float) * 2));
-  HDOF_HIP(hipMalloc(&sc->tris, sizeof(float4) * 3 * (size_t)n));
-  HDOF_HIP(hipMalloc(&sc->albedo, sizeof(float) * 3 * (size_t)n));
-  HDOF_HIP(hipMalloc(&sc->depth_out, sizeof(int)));
-  sc->n_nodes = nint;
-  sc->bytes = (int64_t)sizeof(float4) * (7 * (int64_t)nint + 3 * (int64_t)n) + 12 * (int64_t)n;
-  // build scratch, one allocation
+  const int nbounds = min(BOUNDS_BLOCKS, cdiv(n, RS_THREADS));
   size_t off = 0;
   auto carve = [&](size_t bytes) {
     size_t o = off;
     off += (bytes + 255) & ~(size_t)255;
     return o;
   };
+  // permanent storage, one allocation (node slots for every internal node;
+  // collapsed subtrees leave the tail unused)
+  const size_t p_nodes = carve(sizeof(float4) * 4 * (size_t)nint), p_half = carve(sizeof(float4) * 3 * (size_t)nint);
+  const size_t p_tris = carve(sizeof(float4) * 3 * (size_t)n), p_alb = carve(sizeof(float) * 3 * (size_t)n);
+  const size_t p_depth = carve(sizeof(int)), p_unit = carve(sizeof(float));
+  HDOF_HIP(hipMalloc(&sc->mem, off));
+  sc->nodes = (float4*)(sc->mem + p_nodes);
+  sc->hnodes = (float4*)(sc->mem + p_half);
+  sc->tris = (float4*)(sc->mem + p_tris);
+  sc->albedo = (float*)(sc->mem + p_alb);
+  sc->depth_out = (int32_t*)(sc->mem + p_depth);
+  sc->unit = (float*)(sc->mem + p_unit);
+  sc->n_nodes = nint;
+  sc->bytes = (int64_t)sizeof(float4) * (7 * (int64_t)nint + 3 * (int64_t)n) + 12 * (int64_t)n;
+  // build scratch, one buffer of the context
+  off = 0;
   size_t o_bounds = carve(sizeof(float) * 6 * nbounds);
   size_t o_k0 = carve(sizeof(uint64_t) * n), o_k1 = carve(sizeof(uint64_t) * n);
   size_t o_v0 = carve(sizeof(int) * n), o_v1 = carve(sizeof(int) * n);
-  size_t o_hist = carve(sizeof(int) * 256 * (size_t)nb);
+  size_t o_hist = carve(sizeof(int) * 256 * (size_t)nb), o_dig = carve(sizeof(int) * 256);
   size_t o_lbox = carve(sizeof(float) * 6 * (size_t)n);
   size_t o_cid0 = carve(sizeof(int) * n), o_cid1 = carve(sizeof(int) * n);
   size_t o_cb0 = carve(sizeof(float4) * 2 * (size_t)n), o_cb1 = carve(sizeof(float4) * 2 * (size_t)n);
   size_t o_cs0 = carve(sizeof(int2) * n), o_cs1 = carve(sizeof(int2) * n);
-  size_t o_nn = carve(sizeof(int) * n), o_fl = carve(sizeof(unsigned long long) * n);
-  size_t o_tot = carve(sizeof(unsigned long long));
+  size_t o_mate = carve(sizeof(int) * n), o_cnt = carve(sizeof(unsigned long long) * cdiv(n, 256));
+  size_t o_state = carve(sizeof(int2) * 2);
   size_t o_bl = carve(sizeof(int) * nint), o_br = carve(sizeof(int) * nint);
   size_t o_bbox = carve(sizeof(float) * 6 * (size_t)nint), o_bsz = carve(sizeof(int2) * nint);
   size_t o_pint = carve(sizeof(int) * nint), o_pleaf = carve(sizeof(int) * n);
   size_t o_loff = carve(sizeof(int) * n), o_noff = carve(sizeof(int) * nint), o_nidx = carve(sizeof(int) * nint);
-  char* s = nullptr;
-  HDOF_HIP(hipMalloc(&s, off));
+  hdof_status status = hdof_ensure(ctx->bvh_scratch, off);
+  if (status != HDOF_OK) return status;
+  char* s = (char*)ctx->bvh_scratch.p;
   float* bounds = (float*)(s + o_bounds);
   uint64_t* k0 = (uint64_t*)(s + o_k0);
   uint64_t* k1 = (uint64_t*)(s + o_k1);
   int* v0 = (int*)(s + o_v0);
   int* v1 = (int*)(s + o_v1);
-  int* hist = (int*)(s + o_hist);
+  int *hist = (int*)(s + o_hist), *dig = (int*)(s + o_dig);
   float* lbox = (float*)(s + o_lbox);
   int* cid[2] = {(int*)(s + o_cid0), (int*)(s + o_cid1)};
   float4* cbox[2] = {(float4*)(s + o_cb0), (float4*)(s + o_cb1)};
   int2* csz[2] = {(int2*)(s + o_cs0), (int2*)(s + o_cs1)};
-  int* nn = (int*)(s + o_nn);
-  unsigned long long* fl = (unsigned long long*)(s + o_fl);
-  unsigned long long* tot = (unsigned long long*)(s + o_tot);
+  int* mate = (int*)(s + o_mate);
+  unsigned long long* cnt = (unsigned long long*)(s + o_cnt);
+  int2* state = (int2*)(s + o_state);
   int *bl = (int*)(s + o_bl), *br = (int*)(s + o_br);
   float* bbox = (float*)(s + o_bbox);
   int2* bsz = (int2*)(s + o_bsz);
   int *pint = (int*)(s + o_pint), *pleaf = (int*)(s + o_pleaf);
   int *loff = (int*)(s + o_loff), *noff = (int*)(s + o_noff), *nidx = (int*)(s + o_nidx);
 
-  hdof_status status = HDOF_OK;
-  hipLaunchKernelGGL(k_copy_albedo, dim3(cdiv(3L * n, 256)), dim3(256), 0, st, albedo, 3 * n, sc->albedo);
   hipLaunchKernelGGL(k_centroid_bounds, dim3(nbounds), dim3(RS_THREADS), 0, st, verts, n, bounds);
-  hipLaunchKernelGGL(k_reduce_bounds, dim3(1), dim3(64), 0, st, bounds, nbounds);
-  hipLaunchKernelGGL(k_morton, dim3(cdiv(n, 256)), dim3(256), 0, st, verts, n, bounds, k0, v0);
+  hipLaunchKernelGGL(k_morton, dim3(cdiv(n, RS_THREADS)), dim3(RS_THREADS), 0, st, verts, n, (const float*)bounds,
+                     nbounds, albedo, k0, v0, sc->albedo);
   for (int pass = 0; pass < 8; ++pass) {
     int shift = 8 * pass;
     hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(RS_THREADS), 0, st, k0, n, shift, nb, hist);
-    hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(1024), 0, st, hist, 256 * nb, (int*)nullptr);
-    hipLaunchKernelGGL(k_rs_scatter, dim3(nb), dim3(RS_THREADS), 0, st, k0, v0, n, shift, nb, hist, k1, v1);
-    uint64_t* tk = k0; k0 = k1; k1 = tk;
-    int* tv = v0; v0 = v1; v1 = tv;
+    hipLaunchKernelGGL(k_rs_rows, dim3(256), dim3(RS_THREADS), 0, st, hist, nb, dig);
+    hipLaunchKernelGGL(k_rs_scatter, dim3(nb), dim3(RS_THREADS), 0, st, k0, v0, n, shift, nb, (const int*)hist,
+                       (const int*)dig, k1, v1);
+    std::swap(k0, k1);
+    std::swap(v0, v1);
   }
-  hipLaunchKernelGGL(k_leaf_boxes, dim3(cdiv(n, 256)), dim3(256), 0, st, verts, v0, n, lbox);
-  hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, sc->depth_out, 1, 1);
+  hipLaunchKernelGGL(k_leaf_clusters, dim3(cdiv(n, 256)), dim3(256), 0, st, verts, (const int*)v0, n, lbox, cid[0],
+                     cbox[0], csz[0], state);
+  hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, sc->depth_out, 1, n == 1 ? 2 : 1);
   if (n == 1) {
-    hipLaunchKernelGGL(k_place_tris, dim3(1), dim3(64), 0, st, verts, v0, (const int*)nullptr, n, sc->tris);
-    hipLaunchKernelGGL(k_box_unit, dim3(1), dim3(1), 0, st, (const float*)lbox, sc->unit);
-    hipLaunchKernelGGL(k_single_root, dim3(1), dim3(1), 0, st, lbox, sc->unit, sc->nodes, sc->hnodes);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, sc->depth_out, 1, 2);
+    hipLaunchKernelGGL(k_place_tris, dim3(1), dim3(64), 0, st, verts, (const int*)v0, (const int*)nullptr, n, sc->tris);
+    hipLaunchKernelGGL(k_single_root, dim3(1), dim3(1), 0, st, (const float*)lbox, sc->unit, sc->nodes, sc->hnodes);
   } else {
-    hipLaunchKernelGGL(k_leaf_clusters, dim3(cdiv(n, 256)), dim3(256), 0, st, lbox, n, cid[0], cbox[0], csz[0]);
-    int m = n, next = n - 2, cur = 0;
-    for (int iter = 0; m > 1 && iter < 4 * 64 + n; ++iter) {
-      hipLaunchKernelGGL(k_ploc_nn, dim3(cdiv(m, 256)), dim3(256), 0, st, (const float4*)cbox[cur], m, nn);
-      hipLaunchKernelGGL(k_ploc_flags, dim3(cdiv(m, 256)), dim3(256), 0, st, (const int*)nn, m, fl);
-      hipLaunchKernelGGL(k_scan64, dim3(1), dim3(1024), 0, st, fl, m, tot);
-      hipLaunchKernelGGL(k_ploc_merge, dim3(cdiv(m, 256)), dim3(256), 0, st, (const int*)nn, m,
-                         (const unsigned long long*)fl, (const int*)cid[cur], (const float4*)cbox[cur],
-                         (const int2*)csz[cur], next, cid[cur ^ 1], cbox[cur ^ 1], csz[cur ^ 1], bl, br, bbox, bsz);
-      unsigned long long t = 0;
-      hipError_t e = hipMemcpyAsync(&t, tot, sizeof t, hipMemcpyDeviceToHost, st);
+    // rounds over grids sized by the last count the host has read, a few at
+    // a time (a round shrinks m to about two thirds); from PLOC_TAIL
+    // clusters on one block does the rest
+    int m = n, cur = 0;
+    while (m > 1) {
+      const int nblk = cdiv(m, 256), m0 = m;
+      if (m > PLOC_TAIL) {
+        const int scanned = nblk > 8192;
+        const int rounds = (int)ceil(log((double)m / PLOC_TAIL) / log(1.5)) / 2 + 1;
+        for (int r = 0; r < rounds; ++r) {
+          hipLaunchKernelGGL(k_ploc_find, dim3(nblk), dim3(256), 0, st, (const float4*)cbox[cur],
+                             (const int2*)(state + cur), mate, cnt);
+          if (scanned) hipLaunchKernelGGL(k_ploc_scan, dim3(1), dim3(1024), 0, st, cnt, (const int2*)(state + cur));
+          hipLaunchKernelGGL(k_ploc_merge, dim3(nblk), dim3(256), 0, st, (const int*)mate,
+                             (const unsigned long long*)cnt, scanned, (const int2*)(state + cur), state + (cur ^ 1),
+                             (const int*)cid[cur], (const float4*)cbox[cur], (const int2*)csz[cur], cid[cur ^ 1],
+                             cbox[cur ^ 1], csz[cur ^ 1], bl, br, bbox, bsz);
+          cur ^= 1;
+        }
+      }
+      // (returns at once when more clusters are left than it takes)
+      hipLaunchKernelGGL(k_ploc_tail, dim3(1), dim3(PLOC_TAIL), 0, st, (const int*)cid[cur],
+                         (const float4*)cbox[cur], (const int2*)csz[cur], state + cur, bl, br, bbox, bsz);
+      int2 h = make_int2(0, 0);
+      hipError_t e = hipMemcpyAsync(&h, state + cur, sizeof h, hipMemcpyDeviceToHost, st);
       if (e == hipSuccess) e = hipStreamSynchronize(st);
       if (e != hipSuccess) {
         status = hdof_set_error(HDOF_ERR_HIP, "BVH clustering: %s", hipGetErrorString(e));
         break;
       }
-      int m_new = (int)(t & 0xffffffffull), merges = (int)(t >> 32);
-      if (merges <= 0 || m_new != m - merges) {
-        status = hdof_set_error(HDOF_ERR_HIP, "BVH clustering made no progress (%d clusters)", m);
+      m = h.x;
+      if (m < 1 || m >= m0 || h.y != m - 2) {  // every merge takes one cluster and one node
+        status = hdof_set_error(HDOF_ERR_HIP, "BVH clustering made no progress (%d clusters)", m0);
         break;
       }
-      next -= merges;
-      m = m_new;
-      cur ^= 1;
     }
-    if (status == HDOF_OK && (m != 1 || next != -1))
-      status = hdof_set_error(HDOF_ERR_HIP, "BVH clustering ended with %d clusters", m);
     if (status == HDOF_OK) {
-      hipLaunchKernelGGL(k_fill_int, dim3(cdiv(nint, 256)), dim3(256), 0, st, pint, nint, -1);
       hipLaunchKernelGGL(k_parents, dim3(cdiv(nint, 256)), dim3(256), 0, st, nint, (const int*)bl, (const int*)br,
                          pint, pleaf);
-      hipLaunchKernelGGL(k_place_leaves, dim3(cdiv(n, 256)), dim3(256), 0, st, n, (const int*)bl,
-                         (const int*)pint, (const int*)pleaf, (const int2*)bsz, loff, sc->depth_out);
-      hipLaunchKernelGGL(k_place_nodes, dim3(cdiv(nint, 256)), dim3(256), 0, st, nint, n, (const int*)bl,
-                         (const int*)pint, (const int*)pleaf, (const int2*)bsz, noff, nidx);
+      hipLaunchKernelGGL(k_place, dim3(cdiv((long)n + nint, 256)), dim3(256), 0, st, n, nint, (const int*)bl,
+                         (const int*)pint, (const int*)pleaf, (const int2*)bsz, loff, noff, nidx, sc->depth_out);
       hipLaunchKernelGGL(k_place_tris, dim3(cdiv(n, 256)), dim3(256), 0, st, verts, (const int*)v0,
                          (const int*)loff, n, sc->tris);
-      hipLaunchKernelGGL(k_box_unit, dim3(1), dim3(1), 0, st, (const float*)bbox, sc->unit);
       hipLaunchKernelGGL(k_emit_nodes, dim3(cdiv(nint, 256)), dim3(256), 0, st, nint, (const int*)bl,
                          (const int*)br, (const int2*)bsz, (const float*)bbox, (const float*)lbox,
-                         (const int*)loff, (const int*)noff, (const int*)nidx, (const float*)sc->unit, sc->nodes, sc->hnodes);
+                         (const int*)loff, (const int*)noff, (const int*)nidx, sc->unit, sc->nodes, sc->hnodes);
     }
   }
   hipError_t e = hipGetLastError();
   if (status == HDOF_OK && e != hipSuccess)
     status = hdof_set_error(HDOF_ERR_HIP, "BVH build launch: %s", hipGetErrorString(e));
-  // scratch is released once the stream has consumed it
+  // the scene may be used on any stream from here on, the scratch by the
+  // context's next build
   e = hipStreamSynchronize(st);
   if (status == HDOF_OK && e != hipSuccess) status = hdof_set_error(HDOF_ERR_HIP, "BVH build: %s", hipGetErrorString(e));
-  hipFree(s);
+  if (ctx->bvh_scratch.bytes > HDOF_BVH_KEEP_BYTES) {  // a large scene's scratch is not kept for the next
+    hipFree(ctx->bvh_scratch.p);
+    ctx->bvh_scratch = Buf{};
+  }
   return status;
 }

@@ -53,13 +53,18 @@
 #define HDOF_LEAF_BIT 0x80000000u
 #define HDOF_LEAF_FIRST_MASK 0x07FFFFFFu
 
+// build scratch that a context keeps between builds (about 260 bytes per
+// triangle: one million triangles)
+#define HDOF_BVH_KEEP_BYTES ((size_t)288 << 20)
+
 struct hdof_scene {
   hdof_ctx* ctx;
   int32_t n_tris;
   int32_t n_nodes;
+  char* mem;       // the one allocation that the arrays below (but spec) lie in
   float4* nodes;   // 4 float4 per node: child boxes x/y (2), z (1), children (1)
   float4* hnodes;  // 3 float4 per node: half-precision child boxes about the node's centre (see emit_half)
-  float* unit;     // [2] unit of the half-precision boxes, margin they are widened by
+  float* unit;     // [1] unit of the half-precision boxes
   float4* tris;    // 3 float4 per triangle in leaf order; .w of the first = input index
   float* albedo;   // 3 floats per triangle, input order
   float* spec;     // 2 floats per triangle (k_s, shininess), input order; NULL: Lambertian
@@ -79,6 +84,8 @@ struct hdof_ctx {
   int device = 0;
   int n_cu = 0;
   int* d_flags = nullptr;  // device-side fault flags
+  // BVH build scratch, kept for the next build up to HDOF_BVH_KEEP_BYTES
+  Buf bvh_scratch;
   // trace scratch
   Buf queue, ray_col, ray_z, work_counter;
   // mask scratch

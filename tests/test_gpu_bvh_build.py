@@ -1,0 +1,77 @@
+"""GPU BVH build at the triangle counts where its passes change form: the
+sort's blocks of 1024 keys, the clustering rounds' blocks of 256, the one
+block that does the last rounds (1024 clusters) with its split searches, and
+degenerate inputs (equal triangles, all Morton codes alike).  Each build's
+G-buffer against the FP64 oracle: ids equal except on the rays it flags."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import scenegen as sg
+from gpu_common import print_case, upload_scene
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hd():
+    from paper_2210_04981_amd import hdof
+    return hdof
+
+
+@pytest.fixture(scope="module")
+def ctx(hd):
+    c = hd.hdof_create(0)
+    yield c
+    c.close()
+
+
+def soup(n, seed, size):
+    rng = np.random.default_rng(seed)
+    c = np.concatenate([rng.uniform(-1, 1, (n, 1, 2)), rng.uniform(1, 4, (n, 1, 1))], -1)
+    v = (c + rng.uniform(-size, size, (n, 3, 3))).reshape(n, 9).astype(np.float32)
+    return sg.Scene(v, rng.uniform(0, 1, (n, 3)).astype(np.float32))
+
+
+def check(hd, ctx, scene):
+    cfg = sg.config_tiny()
+    sc = upload_scene(hd, ctx, scene)
+    st = sc.stats()
+    assert st["n_tris"] == scene.n_tris and 1 <= st["max_depth"] <= 64
+    gb = hd.hdof_gbuffer(ctx, sc, hd.camera_of(cfg.camera), hd.lens_of(cfg.lens), hd.light_of(cfg.light))
+    torch.cuda.synchronize()
+    ctx.sync()
+    ref = oracle.gbuffer(oracle.Scene(scene.verts, scene.albedo), cfg.camera, cfg.lens, cfg.light)
+    bad = (gb.tri_id.cpu().numpy() != ref["tri_id"]) & (ref["amb"] == 0)
+    assert not bad.any(), f"{bad.sum()} unambiguous hits differ"
+    sc.close()
+
+
+@pytest.mark.parametrize("n", [2, 3, 17, 128, 129, 255, 257, 512, 1023, 1024, 1025, 2049, 5000, 70001])
+def test_counts(hd, ctx, n):
+    print_case(f"build of {n} triangles")
+    check(hd, ctx, soup(n, n, 0.9 / n ** (1 / 3)))
+
+
+def test_builds_in_turn_share_scratch(hd, ctx):
+    """A large build between two small ones: the context's kept scratch."""
+    print_case("builds in turn")
+    for n in (300, 40000, 301):
+        check(hd, ctx, soup(n, n + 1, 0.05))
+
+
+def test_equal_triangles(hd, ctx):
+    """Every triangle the same: all codes and areas tie, each ray hits the lowest index."""
+    print_case("equal triangles")
+    one = soup(1, 5, 0.8)
+    scene = sg.Scene(np.repeat(one.verts, 1500, 0), np.repeat(one.albedo, 1500, 0))
+    cfg = sg.config_tiny()
+    sc = upload_scene(hd, ctx, scene)
+    gb = hd.hdof_gbuffer(ctx, sc, hd.camera_of(cfg.camera), hd.lens_of(cfg.lens), hd.light_of(cfg.light))
+    torch.cuda.synchronize()
+    ctx.sync()
+    assert set(np.unique(gb.tri_id.cpu().numpy())) <= {-1, 0}
+    sc.close()
