@@ -26,7 +26,7 @@
 
 namespace {
 
-#define BOUNDS_BLOCKS 256  // partial bounds: one per thread of the kernel that reduces them
+#define BOUNDS_BLOCKS 1024  // partial bounds at most
 
 // the block's minima (6 values: minimum, -maximum) of `v`, in every thread
 __device__ inline void block_min6(float v[6], float (*red)[RS_THREADS / 64]) {
@@ -64,15 +64,16 @@ __device__ inline uint64_t spread21(uint64_t x) {
   return x;
 }
 
-// Morton codes of the centroids in the bounds that the partial ones (nparts
-// <= 256) reduce to; the albedo's copy too
+// Morton codes of the centroids in the bounds that the partial ones reduce
+// to; the albedo's copy too
 __global__ __launch_bounds__(RS_THREADS) void k_morton(const float* __restrict__ v, int n,
                                                        const float* __restrict__ part, int nparts,
                                                        const float* __restrict__ albedo, uint64_t* __restrict__ keys,
                                                        int* __restrict__ vals, float* __restrict__ alb_out) {
   __shared__ float red[6][RS_THREADS / 64];
-  float m[6];
-  for (int a = 0; a < 6; ++a) m[a] = (int)threadIdx.x < nparts ? part[6 * threadIdx.x + a] : INFINITY;
+  float m[6] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
+  for (int k = threadIdx.x; k < nparts; k += RS_THREADS)
+    for (int a = 0; a < 6; ++a) m[a] = fminf(m[a], part[6 * k + a]);
   block_min6(m, red);
   const int i0 = blockIdx.x * RS_THREADS, i = i0 + threadIdx.x;
   for (int k = 0; k < 3; ++k) {
@@ -233,7 +234,10 @@ __device__ inline float merged_area(float4 lo, float4 hi, float4 l2, float4 h2) 
 // and merges (upper half).  m is read on the device, so the host enqueues
 // rounds without waiting for their outcome: with a copy and a wait per round
 // and single-block scans the 67 rounds of 200k triangles took 4 ms.
-__global__ __launch_bounds__(256) void k_ploc_find(const float4* __restrict__ cbox, const int2* __restrict__ state,
+// (five waves, the window's 288 clusters in one pass; the neighbours' areas
+// of a group are formed before any is compared, so their LDS reads overlap)
+#define PLOC_FIND_THREADS 320
+__global__ __launch_bounds__(PLOC_FIND_THREADS) void k_ploc_find(const float4* __restrict__ cbox, const int2* __restrict__ state,
                                                    int* __restrict__ mate, unsigned long long* __restrict__ count) {
   __shared__ float4 blo[256 + 4 * PLOC_R], bhi[256 + 4 * PLOC_R];
   __shared__ int nn[256 + 2 * PLOC_R];
@@ -242,42 +246,47 @@ __global__ __launch_bounds__(256) void k_ploc_find(const float4* __restrict__ cb
   const int first = blockIdx.x * 256;
   if (m <= 1 || first >= m) return;
   const int base = first - 2 * PLOC_R, t = threadIdx.x;
-  for (int k = t; k < 256 + 4 * PLOC_R; k += 256) {
-    const int g = base + k;
-    if (g >= 0 && g < m) {
-      blo[k] = cbox[2 * (size_t)g];
-      bhi[k] = cbox[2 * (size_t)g + 1];
+  {
+    static_assert(256 + 4 * PLOC_R <= PLOC_FIND_THREADS, "one thread per staged cluster");
+    const int g = base + t;
+    if (t < 256 + 4 * PLOC_R && g >= 0 && g < m) {
+      blo[t] = cbox[2 * (size_t)g];
+      bhi[t] = cbox[2 * (size_t)g + 1];
     }
   }
   __syncthreads();
-  for (int k = t; k < 256 + 2 * PLOC_R; k += 256) {
-    const int i = first - PLOC_R + k, li = k + PLOC_R;
+  if (t < 256 + 2 * PLOC_R) {
+    const int i = first - PLOC_R + t, li = t + PLOC_R;
     int bj = -1;
     if (i >= 0 && i < m) {
       const float4 lo = blo[li], hi = bhi[li];
       float best = INFINITY;
-      for (int d = -PLOC_R; d <= PLOC_R; ++d) {
-        const int j = i + d;
-        if (d == 0 || j < 0 || j >= m) continue;
-        const float a = merged_area(lo, hi, blo[li + d], bhi[li + d]);
-        if (a < best) {
-          best = a;
-          bj = j;
+      for (int d0 = -PLOC_R; d0 <= PLOC_R; d0 += 11) {
+        float a[11];
+#pragma unroll
+        for (int k = 0; k < 11; ++k) a[k] = merged_area(lo, hi, blo[li + d0 + k], bhi[li + d0 + k]);
+#pragma unroll
+        for (int k = 0; k < 11; ++k) {
+          const int j = i + d0 + k;
+          if (d0 + k != 0 && j >= 0 && j < m && a[k] < best) {
+            best = a[k];
+            bj = j;
+          }
         }
       }
     }
-    nn[k] = bj;
+    nn[t] = bj;
   }
   __syncthreads();
   const int i = first + t;
   int j = -1;
-  if (i < m) {
+  if (t < 256 && i < m) {
     j = nn[t + PLOC_R];
     if (j >= 0 && nn[j - first + PLOC_R] != i) j = -1;
     mate[i] = j;
   }
-  const unsigned long long sv = __ballot(i < m && !(j >= 0 && i > j)), ld = __ballot(i < m && j > i);
-  if ((t & 63) == 0) {
+  const unsigned long long sv = __ballot(t < 256 && i < m && !(j >= 0 && i > j)), ld = __ballot(t < 256 && i < m && j > i);
+  if ((t & 63) == 0 && t < 256) {
     cs[t >> 6] = __popcll(sv);
     cl[t >> 6] = __popcll(ld);
   }
@@ -413,23 +422,28 @@ __global__ __launch_bounds__(PLOC_TAIL) void k_ploc_tail(const int* __restrict__
                                                          const int2* __restrict__ csz, int2* __restrict__ state,
                                                          int* __restrict__ bl, int* __restrict__ br,
                                                          float* __restrict__ bbox, int2* __restrict__ bsz) {
-  __shared__ float lox[PLOC_TAIL], loy[PLOC_TAIL], loz[PLOC_TAIL], hix[PLOC_TAIL], hiy[PLOC_TAIL], hiz[PLOC_TAIL];
-  __shared__ int nn[PLOC_TAIL], ids[PLOC_TAIL];
-  __shared__ int2 szs[PLOC_TAIL];
+  // two buffers of the clusters (a round reads one and writes the other)
+  __shared__ float box[2][6][PLOC_TAIL];
+  __shared__ int nn[PLOC_TAIL], idb[2][PLOC_TAIL];
+  __shared__ int2 szb[2][PLOC_TAIL];
   __shared__ int2 wave_n[PLOC_TAIL / 64];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   int m = state->x, next = state->y;
   if (m > PLOC_TAIL) return;
   if (t < m) {
     const float4 lo = cbox[2 * (size_t)t], hi = cbox[2 * (size_t)t + 1];
-    lox[t] = lo.x, loy[t] = lo.y, loz[t] = lo.z;
-    hix[t] = hi.x, hiy[t] = hi.y, hiz[t] = hi.z;
-    ids[t] = cid[t];
-    szs[t] = csz[t];
+    box[0][0][t] = lo.x, box[0][1][t] = lo.y, box[0][2][t] = lo.z;
+    box[0][3][t] = hi.x, box[0][4][t] = hi.y, box[0][5][t] = hi.z;
+    idb[0][t] = cid[t];
+    szb[0][t] = csz[t];
   }
   __syncthreads();
   const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  while (m > 1) {
+  for (int cur = 0; m > 1; cur ^= 1) {
+    const float *lox = box[cur][0], *loy = box[cur][1], *loz = box[cur][2];
+    const float *hix = box[cur][3], *hiy = box[cur][4], *hiz = box[cur][5];
+    const int* ids = idb[cur];
+    const int2* szs = szb[cur];
     // nearest neighbours; window position w stands for the neighbour at
     // w - PLOC_R below PLOC_R and w - PLOC_R + 1 above
     const int sh = m <= PLOC_TAIL / 8 ? 3 : (m <= PLOC_TAIL / 4 ? 2 : (m <= PLOC_TAIL / 2 ? 1 : 0));
@@ -493,12 +507,12 @@ __global__ __launch_bounds__(PLOC_TAIL) void k_ploc_tail(const int* __restrict__
         id = node;
       }
     }
-    __syncthreads();
     if (keep) {
-      lox[pos] = lo.x, loy[pos] = lo.y, loz[pos] = lo.z;
-      hix[pos] = hi.x, hiy[pos] = hi.y, hiz[pos] = hi.z;
-      ids[pos] = id;
-      szs[pos] = sz;
+      float(*ob)[PLOC_TAIL] = box[cur ^ 1];
+      ob[0][pos] = lo.x, ob[1][pos] = lo.y, ob[2][pos] = lo.z;
+      ob[3][pos] = hi.x, ob[4][pos] = hi.y, ob[5][pos] = hi.z;
+      idb[cur ^ 1][pos] = id;
+      szb[cur ^ 1][pos] = sz;
     }
     if (all.y == 0) break;
     m = all.x;
@@ -508,62 +522,74 @@ __global__ __launch_bounds__(PLOC_TAIL) void k_ploc_tail(const int* __restrict__
   if (t == 0) *state = make_int2(m, next);
 }
 
+// what a step from a node to its parent adds to the placement below: the
+// left sibling's triangles, and one node per level plus the left sibling's
+// kept ones
 __global__ void k_parents(int nint, const int* __restrict__ bl, const int* __restrict__ br,
-                          int* __restrict__ pint, int* __restrict__ pleaf) {
+                          const int2* __restrict__ bsz, int4* __restrict__ up_int, int4* __restrict__ up_leaf) {
   int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= nint) return;
-  int c[2] = {bl[a], br[a]};
-  for (int k = 0; k < 2; ++k) {
-    if (c[k] < 0) pleaf[~c[k]] = a;
-    else pint[c[k]] = a;
-  }
+  const int l = bl[a], r = br[a];
+  const int2 ls = l < 0 ? make_int2(1, 0) : bsz[l];
+  *(l < 0 ? up_leaf + ~l : up_int + l) = make_int4(a, 0, 1, 0);
+  *(r < 0 ? up_leaf + ~r : up_int + r) = make_int4(a, ls.x, 1 + ls.y, 0);
+  if (a == 0) up_int[0] = make_int4(-1, 0, 0, 0);
 }
 
-// depth-first placement by walking to the root: the first triangle slot of a
-// subtree (sum of left-sibling sizes on the way up) and a kept internal
-// node's index (one per level, plus the kept nodes of left siblings)
-__device__ inline void dfs_place(int code, int n, const int* __restrict__ bl, const int* __restrict__ pint,
-                                 const int* __restrict__ pleaf, const int2* __restrict__ bsz, int& off,
-                                 int& idx, int& depth) {
+// depth-first placement by walking to the root, one record per level: the
+// first triangle slot of a subtree and a kept internal node's index
+__device__ inline void dfs_place(int4 up, int n, const int4* __restrict__ up_int, int& off, int& idx, int& depth) {
   off = 0;
   idx = 0;
   depth = 0;
-  int a = code < 0 ? pleaf[~code] : pint[code];
-  for (int guard = 0; a >= 0 && guard < n; ++guard) {
-    int left = bl[a];
-    if (code != left) {  // right child
-      int2 ls = left < 0 ? make_int2(1, 0) : bsz[left];
-      off += ls.x;
-      idx += 1 + ls.y;
-    } else {
-      idx += 1;
-    }
+  for (int guard = 0; up.x >= 0 && guard < n; ++guard) {
+    off += up.y;
+    idx += up.z;
     ++depth;
-    code = a;
-    a = a == 0 ? -1 : pint[a];
+    up = up_int[up.x];
   }
 }
 
-// threads 0..n-1 place the leaves, the others the internal nodes; the tree
-// depth is reduced over a wave before the atomic (one per triangle took 37 us
-// of the pass for 200k triangles)
-__global__ void k_place(int n, int nint, const int* __restrict__ bl, const int* __restrict__ pint,
-                        const int* __restrict__ pleaf, const int2* __restrict__ bsz, int* __restrict__ leaf_off,
-                        int* __restrict__ node_off, int* __restrict__ node_idx, int* __restrict__ depth_out) {
+// Places the kept nodes by their walks to the root; the
+// rest takes a step or two from there (walks from every triangle and node:
+// 50 us for 200k triangles, bound by their random 16-byte reads).
+__global__ void k_place_nodes(int n, int nint, const int4* __restrict__ up_int, const int2* __restrict__ bsz,
+                              int* __restrict__ node_off, int* __restrict__ node_idx, int* __restrict__ node_dep) {
+  const int a = blockIdx.x * blockDim.x + threadIdx.x;
+  if (a >= nint || (a != 0 && bsz[a].x <= HDOF_BVH_LEAF)) return;
+  int off, idx, d;
+  dfs_place(up_int[a], n, up_int, off, idx, d);
+  node_off[a] = off;
+  node_idx[a] = idx;
+  node_dep[a] = d;
+}
+
+// threads 0..n-1 place the leaves, the others the small internal nodes; a
+// wave adds its depth to the tree's only where it is the largest so far (an
+// atomic per triangle took 37 us for 200k triangles, one per wave 33)
+__global__ void k_place_rest(int n, int nint, const int4* __restrict__ up_int, const int4* __restrict__ up_leaf,
+                             const int2* __restrict__ bsz, const int* __restrict__ node_dep,
+                             int* __restrict__ leaf_off, int* __restrict__ node_off, int* __restrict__ depth_out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  int off = 0, idx = 0, d = 0;
-  if (i < n) {
-    dfs_place(~i, n, bl, pint, pleaf, bsz, off, idx, d);
-    leaf_off[i] = off;
-  } else if (i - n < nint) {
-    const int a = i - n;
-    if (a != 0) dfs_place(a, n, bl, pint, pleaf, bsz, off, idx, d);
-    node_off[a] = off;
-    node_idx[a] = idx;
-    d = 0;
+  const bool leaf = i < n, small = !leaf && i - n < nint && i != n && bsz[i - n].x <= HDOF_BVH_LEAF;
+  int d = 0;
+  if (leaf || small) {
+    int4 up = leaf ? up_leaf[i] : up_int[i - n];
+    int off = up.y;
+    for (d = 1; up.x != 0 && bsz[up.x].x <= HDOF_BVH_LEAF; ++d) {  // at most HDOF_BVH_LEAF small ancestors
+      up = up_int[up.x];
+      off += up.y;
+    }
+    off += node_off[up.x];
+    d += node_dep[up.x];
+    if (leaf)
+      leaf_off[i] = off;
+    else
+      node_off[i - n] = off, d = 0;
   }
   for (int o = 32; o > 0; o >>= 1) d = max(d, __shfl_xor(d, o));
-  if ((threadIdx.x & 63) == 0 && d > 0) atomicMax(depth_out, d + 1);
+  if ((threadIdx.x & 63) == 0 && d + 1 > __hip_atomic_load(depth_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(depth_out, d + 1);
 }
 
 __global__ void k_place_tris(const float* __restrict__ v, const int* __restrict__ order,
@@ -731,8 +757,9 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
   size_t o_state = carve(sizeof(int2) * 2);
   size_t o_bl = carve(sizeof(int) * nint), o_br = carve(sizeof(int) * nint);
   size_t o_bbox = carve(sizeof(float) * 6 * (size_t)nint), o_bsz = carve(sizeof(int2) * nint);
-  size_t o_pint = carve(sizeof(int) * nint), o_pleaf = carve(sizeof(int) * n);
+  size_t o_pint = carve(sizeof(int4) * nint), o_pleaf = carve(sizeof(int4) * n);
   size_t o_loff = carve(sizeof(int) * n), o_noff = carve(sizeof(int) * nint), o_nidx = carve(sizeof(int) * nint);
+  size_t o_ndep = carve(sizeof(int) * nint);
   hdof_status status = hdof_ensure(ctx->bvh_scratch, off);
   if (status != HDOF_OK) return status;
   char* s = (char*)ctx->bvh_scratch.p;
@@ -752,8 +779,9 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
   int *bl = (int*)(s + o_bl), *br = (int*)(s + o_br);
   float* bbox = (float*)(s + o_bbox);
   int2* bsz = (int2*)(s + o_bsz);
-  int *pint = (int*)(s + o_pint), *pleaf = (int*)(s + o_pleaf);
+  int4 *up_int = (int4*)(s + o_pint), *up_leaf = (int4*)(s + o_pleaf);
   int *loff = (int*)(s + o_loff), *noff = (int*)(s + o_noff), *nidx = (int*)(s + o_nidx);
+  int* ndep = (int*)(s + o_ndep);
 
   hipLaunchKernelGGL(k_centroid_bounds, dim3(nbounds), dim3(RS_THREADS), 0, st, verts, n, bounds);
   hipLaunchKernelGGL(k_morton, dim3(cdiv(n, RS_THREADS)), dim3(RS_THREADS), 0, st, verts, n, (const float*)bounds,
@@ -774,17 +802,17 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
     hipLaunchKernelGGL(k_place_tris, dim3(1), dim3(64), 0, st, verts, (const int*)v0, (const int*)nullptr, n, sc->tris);
     hipLaunchKernelGGL(k_single_root, dim3(1), dim3(1), 0, st, (const float*)lbox, sc->unit, sc->nodes, sc->hnodes);
   } else {
-    // rounds over grids sized by the last count the host has read, a few at
-    // a time (a round shrinks m to about two thirds); from PLOC_TAIL
-    // clusters on one block does the rest
+    // rounds over grids sized by the last count the host has read, as many
+    // at a time as should leave PLOC_TAIL clusters (a round leaves between
+    // 0.75 and 0.82 of them on the scenes measured); one block does the rest
     int m = n, cur = 0;
     while (m > 1) {
       const int nblk = cdiv(m, 256), m0 = m;
       if (m > PLOC_TAIL) {
         const int scanned = nblk > 8192;
-        const int rounds = (int)ceil(log((double)m / PLOC_TAIL) / log(1.5)) / 2 + 1;
+        const int rounds = (int)ceil(log((double)m / PLOC_TAIL) / log(1.25));
         for (int r = 0; r < rounds; ++r) {
-          hipLaunchKernelGGL(k_ploc_find, dim3(nblk), dim3(256), 0, st, (const float4*)cbox[cur],
+          hipLaunchKernelGGL(k_ploc_find, dim3(nblk), dim3(PLOC_FIND_THREADS), 0, st, (const float4*)cbox[cur],
                              (const int2*)(state + cur), mate, cnt);
           if (scanned) hipLaunchKernelGGL(k_ploc_scan, dim3(1), dim3(1024), 0, st, cnt, (const int2*)(state + cur));
           hipLaunchKernelGGL(k_ploc_merge, dim3(nblk), dim3(256), 0, st, (const int*)mate,
@@ -812,9 +840,12 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
     }
     if (status == HDOF_OK) {
       hipLaunchKernelGGL(k_parents, dim3(cdiv(nint, 256)), dim3(256), 0, st, nint, (const int*)bl, (const int*)br,
-                         pint, pleaf);
-      hipLaunchKernelGGL(k_place, dim3(cdiv((long)n + nint, 256)), dim3(256), 0, st, n, nint, (const int*)bl,
-                         (const int*)pint, (const int*)pleaf, (const int2*)bsz, loff, noff, nidx, sc->depth_out);
+                         (const int2*)bsz, up_int, up_leaf);
+      hipLaunchKernelGGL(k_place_nodes, dim3(cdiv(nint, 256)), dim3(256), 0, st, n, nint, (const int4*)up_int,
+                         (const int2*)bsz, noff, nidx, ndep);
+      hipLaunchKernelGGL(k_place_rest, dim3(cdiv((long)n + nint, 256)), dim3(256), 0, st, n, nint,
+                         (const int4*)up_int, (const int4*)up_leaf, (const int2*)bsz, (const int*)ndep, loff, noff,
+                         sc->depth_out);
       hipLaunchKernelGGL(k_place_tris, dim3(cdiv(n, 256)), dim3(256), 0, st, verts, (const int*)v0,
                          (const int*)loff, n, sc->tris);
       hipLaunchKernelGGL(k_emit_nodes, dim3(cdiv(nint, 256)), dim3(256), 0, st, nint, (const int*)bl,
