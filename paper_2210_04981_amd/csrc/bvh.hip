@@ -643,7 +643,8 @@ __device__ inline unsigned half_plane(float x, float c, float unit, float margin
 
 // Half-precision record of a node with child boxes b0, b1 (minimum, maximum):
 // (centre, code 1), (x of both children, y of both), (z of both, code 0, -),
-// a pair of planes (minimum, maximum) per dword.
+// a pair of planes (minimum, maximum) per dword; a node's code is its
+// record's position in float4s, three times its index.
 __device__ inline void emit_half(float4* __restrict__ o, const float* b0, const float* b1, unsigned c0, unsigned c1,
                                  float2 unit) {
   const float s = unit.x, mg = unit.y;
@@ -693,6 +694,8 @@ __global__ void k_emit_nodes(int nint, const int* __restrict__ bl, const int* __
   o[1] = make_float4(b[1][0], b[1][3], b[1][1], b[1][4]);
   o[2] = make_float4(b[0][2], b[0][5], b[1][2], b[1][5]);
   o[3] = make_float4(__uint_as_float(code[0]), __uint_as_float(code[1]), 0.0f, 0.0f);
+  for (int k = 0; k < 2; ++k)
+    if (!(code[k] & HDOF_LEAF_BIT)) code[k] *= 3u;
   emit_half(hnodes + 3 * (size_t)node_idx[a], b[0], b[1], code[0], code[1], u);
 }
 

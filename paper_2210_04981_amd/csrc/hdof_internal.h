@@ -17,8 +17,8 @@
 // traversal stack of the persistent trace: this many entries per lane live in
 // LDS, the rest spill to a small private array; beyond both the ray sets the
 // overflow flag.
-#define HDOF_LDS_STACK 16
-#define HDOF_SPILL_STACK 48
+#define HDOF_LDS_STACK 13
+#define HDOF_SPILL_STACK 51
 // lanes in box steps below which the wave turns to its waiting leaves; idle
 // lanes that take waiting rays; idle lanes that refill the slots at most
 #ifndef HDOF_MIN_BOX

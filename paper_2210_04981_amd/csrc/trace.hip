@@ -203,13 +203,15 @@ struct Work {
 // What a wave of the persistent trace keeps in LDS: 64 ray slots (structure
 // of arrays, a slot's fields SLOT_* of a ray that waits or is walked, then
 // its hit in place of the inverse direction), the slots no lane has taken
-// yet, and the lanes' stacks (entry i of lane t at stk[i][t]).
+// yet, and the lanes' stacks (entry i of lane t at stk[i + 1][t], below it
+// TRAV_DONE; one row more takes what a full stack is written in vain).
 enum { SLOT_O, SLOT_D = 3, SLOT_INV = 6, SLOT_SX = 9, SLOT_SY, SLOT_AXES, SLOT_S1, SLOT_ENTRY, SLOT_DONE, SLOT_N };
 struct PoolLds {
   float f[SLOT_N][64];
   int list[64];
-  int stk[HDOF_LDS_STACK][64];
+  int stk[HDOF_LDS_STACK + 2][64];
 };
+#define TRAV_DONE 0xFFFFFFFFu  // entry of a lane without a ray, or with a finished one (no leaf has this code)
 
 // Orders the wave's LDS accesses as the program has them (the LDS executes
 // one wave's accesses in order; this keeps the compiler from moving them).
@@ -217,6 +219,9 @@ __device__ __forceinline__ void wave_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
+
+// this lane's bit of a wave's mask
+__device__ __forceinline__ bool lane_of(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 __device__ __forceinline__ V3 slot_v3(const PoolLds& L, int f, int i) { return V3{L.f[f][i], L.f[f + 1][i], L.f[f + 2][i]}; }
 
@@ -590,14 +595,25 @@ __global__ __launch_bounds__(256) void k_gbuffer_batch(const float4* __restrict_
 // The blocks of the persistent trace that take part: with a ray quantum (a
 // frame overlapping the trace with the post-filter gather) only the first
 // ceil(total * n_cu / ray_quantum) blocks, one block per CU for every
-// ray_quantum rays on average (at least one per CU, at most the grid), so a
-// light trace leaves the CUs to the gather; the first blocks are kept, so
-// every queue segment keeps its blocks.
+// ray_quantum rays on average, so a light trace leaves CUs to the gather,
+// but at least one block per CU and one per 64 rays (half a batch for each
+// wave) while that is no more than 7 per CU, or while all blocks' waves can
+// hold the whole queue as one batch each: fewer blocks make a longer trace,
+// which the frame then waits for.  (Frames of 640x360 with 218k rays at 1.6 /
+// 3.6 / 10 blocks per CU: 337 / 279 / 250 us; 1400x1050 with 693k at 5 / 7 /
+// 10: 483 / 454 / 462; 400x300 with 73k at 1 / 3.6 / 4.5: 157 / 117 / 119.)
+// The first blocks are kept, so every queue segment keeps its blocks.
 __device__ inline int kept_blocks(const TraceArgs& A, int total) {
   const long all = (long)A.bpc * A.n_cu;
   if (A.ray_quantum <= 0) return (int)all;
-  const long kept = ((long)total * A.n_cu + A.ray_quantum - 1) / A.ray_quantum;
-  return (int)min(all, max((long)A.n_cu, kept));
+  const long light = ((long)total * A.n_cu + A.ray_quantum - 1) / A.ray_quantum;
+  const long most = total <= HDOF_TRACE_BLOCK * all ? all : 7l * A.n_cu;
+  return (int)min(all, max(max((long)A.n_cu, light), min(most, (long)total / 64)));
+}
+
+// the kept blocks' waves whose own queue segment is seg
+__device__ inline int waves_of(int kept, int segments, int seg) {
+  return (kept - seg + segments - 1) / segments * (HDOF_TRACE_BLOCK / 64);
 }
 
 // The trace's arguments read anew from the kernel's argument segment (its
@@ -613,14 +629,19 @@ __device__ __forceinline__ const TraceArgs* fresh_args() {
 // Entries handed out: per queue segment (one per XCD, the block's
 // blockIdx.x mod segments) an atomic counter of entries taken; a wave whose
 // segment runs dry moves on to the next and stops once it has found every
-// segment dry.
+// segment dry.  (A look at all counters before each take, to skip the dry
+// ones, makes every wave read the same lines: 241 -> 377 us on 947k rays.)
 // Bound: the vector-memory path.  A dwordx4 load of 64 lanes takes a CU 16
 // clocks whatever the mask (its data return was 87 % busy with four of them
 // per node, the vector ALUs 71 %), so what counts is load instructions per
 // ray: three per node since the boxes are halves, and more lanes in each.
 // On 1.75M rays of a 1080p frame, alone: 533 -> 411 us; 8.3M rays of every
 // pixel of 960x540 with their queue and reduction: 1617 -> 1447 us; the 1M
-// triangles' 4.7M rays: 591 -> 526 us.
+// triangles' 4.7M rays: 591 -> 526 us.  With the stack's top read beside the
+// node, the far child written unconditionally and the choice between near,
+// far and top made by masks instead of branches (each was a compare, a
+// change of the exec mask and, for the pop, a second LDS wait): 368, 1304
+// and 456 us.
 // A wave holds up to 64 rays in LDS slots.  Each is set up, and once hit
 // shaded and stored, by one lane each, 64 at a time; a lane that has
 // finished a ray takes the next waiting slot, which costs the wave a few LDS
@@ -653,21 +674,31 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
     if (blockIdx.x == 0 && t == 0) atomicOr(A.flags, HDOF_FLAG_CAPACITY);
     total = (int)A.cap;
   }
-  if ((int)blockIdx.x >= kept_blocks(A, total)) return;
+  const int kept = kept_blocks(A, total);
+  if ((int)blockIdx.x >= kept) return;
+  // A queue of which no wave gets more than one batch is shared out evenly,
+  // without the counters (28k rays of 96x64 pixels: 148 -> 100 us; 218k of
+  // 640x360: 163 -> 129): the largest segment over the fewest waves.
+  const bool single = kept >= A.segments && ((long)total + A.segments - 1) / A.segments <=
+                                                64l * waves_of(kept, A.segments, A.segments - 1);
+  const int share = ((int)blockIdx.x / A.segments) * (HDOF_TRACE_BLOCK / 64) + __builtin_amdgcn_readfirstlane(t >> 6);
   const int refill = min(A.refill, HDOF_REFILL_MAX);
   const float unit = *A.unit;
   bool held = false, drained = false;  // held: the lane's slot holds a ray
   int seg = blockIdx.x % A.segments, tried = 0;
   int next = 0, count = 0;  // the waiting slots are list[next .. count)
   // the lane's ray: its slot (-1: none), the entry to visit next (a node, or
-  // a leaf code), the stack depth, the closest hit
-  int slot = -1, sp = 0;
-  unsigned cur = 0;
+  // a leaf code), the stack's top (row tp / 64 of stk, row 0 its bottom), the
+  // closest hit
+  int slot = -1, tp = lane;
+  unsigned cur = TRAV_DONE;
   Best b = Best{INFINITY, -1, 0x7fffffff};
   // box steps since a ray of the wave was last done, and what they are bounded by
   unsigned stall = 0;
   const unsigned stall_max = (unsigned)min(64ll * (A.n_nodes + 1ll), 0xfffffff0ll);
   Work wk{0, 0};
+  int* const stk = &L.stk[0][0];
+  stk[lane] = (int)TRAV_DONE;
   for (;;) {
     const unsigned long long idle = __builtin_amdgcn_ballot_w64(slot < 0);
     const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
@@ -683,18 +714,28 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
       }
       if (drained) break;
       const unsigned long long fm = __builtin_amdgcn_ballot_w64(!held);
-      const int want = (int)__popcll(fm), nseg = B.segments;
+      int want = (int)__popcll(fm);
+      const int nseg = B.segments;
       const int lo = (int)((long)total * seg / nseg), hi = (int)((long)total * (seg + 1) / nseg);
       int base = 0;
-      if (lane == 0) base = atomicAdd(&B.counter[seg * HDOF_SEG_STRIDE], want);
-      base = __builtin_amdgcn_readfirstlane(base) + lo;
-      if (base + want >= hi) {  // this segment is used up: go on to the next one
-        seg = seg + 1 == nseg ? 0 : seg + 1;
-        drained = ++tried == nseg;
+      if (single) {
+        // the wave's only batch: its share of the segment
+        const int nw = waves_of(kept, nseg, seg);
+        base = lo + (int)((long)(hi - lo) * share / nw);
+        want = min(want, lo + (int)((long)(hi - lo) * (share + 1) / nw) - base);
+        drained = true;
+      } else {
+        if (lane == 0) base = atomicAdd(&B.counter[seg * HDOF_SEG_STRIDE], want);
+        base = __builtin_amdgcn_readfirstlane(base) + lo;
+        if (base + want >= hi) {  // this segment is used up: go on to the next one
+          seg = seg + 1 == nseg ? 0 : seg + 1;
+          drained = ++tried == nseg;
+        }
       }
       bool got = false;
-      if (!held) {
-        const int e = base + (int)__popcll(fm & lt_mask);
+      const int nth = (int)__popcll(fm & lt_mask);
+      if (!held && nth < want) {
+        const int e = base + nth;
         V3 O, D;
         float S1;
         got = entry_ray<BATCH>(B, pxb, e, hi, O, D, S1);
@@ -720,7 +761,7 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
         slot = L.list[i];
         b = Best{INFINITY, -1, 0x7fffffff};
         cur = 0;  // root
-        sp = 0;
+        tp = lane;
       }
       next = min(count, next + (int)__popcll(idle));
     }
@@ -730,64 +771,70 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
     const V3 sinv = V3{r.inv.x * unit, r.inv.y * unit, r.inv.z * unit};
     const int rx = signbit(r.inv.x) ? 16 : 0, ry = signbit(r.inv.y) ? 16 : 0, rz = signbit(r.inv.z) ? 16 : 0;
     for (;;) {  // walk until lanes can be given rays
-      bool pop = false;
+      const unsigned long long busy = __builtin_amdgcn_ballot_w64(slot >= 0);
       for (;;) {
-        const bool inner = slot >= 0 && !pop && !(cur & HDOF_LEAF_BIT);
-        const int ni = (int)__popcll(__builtin_amdgcn_ballot_w64(inner));
-        if (ni == 0 || (ni < HDOF_MIN_BOX &&
-                        __builtin_amdgcn_ballot_w64(slot >= 0 && (pop || (cur & HDOF_LEAF_BIT))) != 0ull))
-          break;
+        const bool inner = !(cur & HDOF_LEAF_BIT);
+        const unsigned long long im = __builtin_amdgcn_ballot_w64(inner);
+        if (im == 0ull || (im != busy && (int)__popcll(im) < HDOF_MIN_BOX)) break;
         // each internal node is entered at most once per ray: more steps
         // than the wave's rays can take before one of them is done mean a
         // malformed tree, and the rays stop here
         if (++stall > stall_max) {
           if (lane == 0) atomicOr(A.flags, HDOF_FLAG_STACK_OVERFLOW);
-          pop = slot >= 0;
+          cur = TRAV_DONE;
           break;
         }
         if (inner) {
+          // no branch but a uniform one: the stack's top (below the first
+          // entry: TRAV_DONE) is read with the node, and the other child is
+          // written above it whether it will be used or not
           if (COUNT) wk.visits++;
-          const float4* nd = A.hnodes + 3 * (size_t)cur;
-          const float4 n0 = nd[0], n1 = nd[1];
-          const float3 n2 = *(const float3*)(nd + 2);
+          const char* nd = (const char*)A.hnodes + (cur << 4);
+          const float4 n0 = *(const float4*)nd, n1 = *(const float4*)(nd + 16);
+          const float3 n2 = *(const float3*)(nd + 32);
+          const bool deep = __builtin_amdgcn_ballot_w64(tp >= HDOF_LDS_STACK * 64) != 0ull;
+          int ti = tp;
+          if (deep) ti = min(tp, HDOF_LDS_STACK * 64 + lane);  // the lane's own column of the last row
+          unsigned top = (unsigned)stk[ti];
           const V3 base = V3{fmaf(n0.x, sinv.x, r.oinv.x), fmaf(n0.y, sinv.y, r.oinv.y), fmaf(n0.z, sinv.z, r.oinv.z)};
           float t0, t1;
-          const bool h0 = box_hit_half(__float_as_uint(n1.x), __float_as_uint(n1.z), __float_as_uint(n2.x), sinv, base,
-                                       rx, ry, rz, b.t, t0);
-          const bool h1 = box_hit_half(__float_as_uint(n1.y), __float_as_uint(n1.w), __float_as_uint(n2.y), sinv, base,
-                                       rx, ry, rz, b.t, t1);
+          const unsigned long long h0 = __builtin_amdgcn_ballot_w64(
+              box_hit_half(__float_as_uint(n1.x), __float_as_uint(n1.z), __float_as_uint(n2.x), sinv, base, rx, ry, rz,
+                           b.t, t0));
+          const unsigned long long h1 = __builtin_amdgcn_ballot_w64(
+              box_hit_half(__float_as_uint(n1.y), __float_as_uint(n1.w), __float_as_uint(n2.y), sinv, base, rx, ry, rz,
+                           b.t, t1));
+          const unsigned long long le = __builtin_amdgcn_ballot_w64(t0 <= t1);
+          const bool near0 = lane_of(h0 & (~h1 | le)), both = lane_of(h0 & h1), any = lane_of(h0 | h1);
           const unsigned c0 = __float_as_uint(n2.z), c1 = __float_as_uint(n0.w);
-          const bool near0 = h0 && (!h1 || t0 <= t1);
-          cur = near0 ? c0 : c1;
-          if (h0 && h1) {
-            const unsigned far = near0 ? c1 : c0;
-            if (sp < HDOF_LDS_STACK)
-              L.stk[sp][lane] = (int)far;
-            else if (sp < HDOF_LDS_STACK + HDOF_SPILL_STACK)
-              spill[sp - HDOF_LDS_STACK] = (int)far;
-            else
-              atomicOr(A.flags, HDOF_FLAG_STACK_OVERFLOW), --sp;
-            ++sp;
+          const unsigned far = near0 ? c1 : c0;
+          stk[ti + 64] = (int)far;
+          if (deep) {  // entries in the spill array
+            const int e = (tp >> 6) - HDOF_LDS_STACK;
+            if (e > 0) top = (unsigned)spill[e - 1];
+            if (both && e >= 0) {
+              if (e < HDOF_SPILL_STACK)
+                spill[e] = (int)far;
+              else
+                atomicOr(A.flags, HDOF_FLAG_STACK_OVERFLOW), tp -= 64;
+            }
           }
-          pop = !h0 && !h1;
-          if (pop && sp > 0) {
-            --sp;
-            cur = (unsigned)(sp < HDOF_LDS_STACK ? L.stk[sp][lane] : spill[sp - HDOF_LDS_STACK]);
-            pop = false;
-          }
+          cur = any ? (near0 ? c0 : c1) : top;
+          tp += both ? 64 : 0;
+          tp -= any ? 0 : 64;
         }
       }
-      if (slot >= 0 && !pop && (cur & HDOF_LEAF_BIT)) {
+      if ((cur & HDOF_LEAF_BIT) && cur != TRAV_DONE) {
+        unsigned top = (unsigned)stk[min(tp, HDOF_LDS_STACK * 64 + lane)];
         test_leaf(r, A.tris, cur, b);
         if (COUNT) wk.tests += (int)((cur >> 27) & 0xF) + 1;
-        pop = true;
-        if (sp > 0) {
-          --sp;
-          cur = (unsigned)(sp < HDOF_LDS_STACK ? L.stk[sp][lane] : spill[sp - HDOF_LDS_STACK]);
-          pop = false;
-        }
+        const int e = (tp >> 6) - HDOF_LDS_STACK;
+        if (e > 0) top = (unsigned)spill[e - 1];
+        cur = top;
+        tp -= 64;
       }
-      if (pop) {  // the stack is empty: the ray's hit goes to its slot
+      const bool done = slot >= 0 && cur == TRAV_DONE;
+      if (done) {  // the stack is empty: the ray's hit goes to its slot
         L.f[SLOT_INV][slot] = b.t;
         L.f[SLOT_INV + 1][slot] = __int_as_float(b.tri);
         L.f[SLOT_INV + 2][slot] = __int_as_float(b.id);
@@ -800,7 +847,8 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
           wk = Work{0, 0};
         }
       }
-      if (__builtin_amdgcn_ballot_w64(pop) != 0ull) stall = 0;
+      if (__builtin_amdgcn_ballot_w64(done) != 0ull) stall = 0;
+      // (also met by a wave that was given no ray at all)
       const int nidle = (int)__popcll(__builtin_amdgcn_ballot_w64(slot < 0));
       if (nidle >= (next < count ? HDOF_HAND_OUT : (drained ? 64 : refill))) break;
     }

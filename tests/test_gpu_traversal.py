@@ -105,3 +105,18 @@ def test_queue_lengths(hd, ctx, total, refill):
         p += 37
     check_hits(hd, ctx, sg.tiny_scene(1), cfg, spp, 1e-3)
     hd.hdof_set_tuning(ctx)
+
+
+@pytest.mark.parametrize("n", [300, 20000])
+def test_deep_stacks(hd, ctx, n):
+    """Large overlapping triangles: nearly every ray reaches both children of
+    every node on its way, so the stacks of all lanes grow to the tree's depth
+    (about 9 and 17 levels and more), past the rows kept in LDS."""
+    print_case(f"deep stacks: {n} overlapping triangles")
+    rng = np.random.default_rng(n)
+    z = rng.uniform(1, 4, (n, 1, 1))
+    v = np.concatenate([rng.uniform(-2.5, 2.5, (n, 3, 2)), z + rng.uniform(-0.3, 0.3, (n, 3, 1))], -1)
+    scene = sg.Scene(v.reshape(n, 9).astype(np.float32), rng.uniform(0, 1, (n, 3)).astype(np.float32))
+    cfg = sg.config_tiny(aperture_override=0.2)
+    cam = replace(cfg.camera, width=16, height=16)
+    check_hits(hd, ctx, scene, replace(cfg, camera=cam), np.full((16, 16), 3, np.int32), 1e-3)
