@@ -239,6 +239,7 @@ extern "C" void hdof_destroy(hdof_ctx* ctx) {
   buf_free(ctx->bvh_scratch);
   buf_free(ctx->ppb_args);
   buf_free(ctx->ppb_partial);
+  buf_free(ctx->ppb_coc);
   buf_free(ctx->b_arena);
   buf_free(ctx->b_views);
   buf_free(ctx->b_totals);

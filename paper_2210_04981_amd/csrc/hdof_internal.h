@@ -100,7 +100,7 @@ struct hdof_ctx {
   int pp_taps_blades = 0;
   float pp_taps_rot = 0.0f, pp_taps_sa = 0.0f;  // and the aperture it was built for
   // adjoint scratch: CoC per unit aperture, tile / radius arg pixels, block partials
-  Buf ppb_args, ppb_partial;
+  Buf ppb_args, ppb_partial, ppb_coc;
   // variance history (previous frame) and its reprojection into this frame
   int hist_w = 0, hist_h = 0;
   bool hist_any = false;

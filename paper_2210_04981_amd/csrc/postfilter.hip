@@ -918,10 +918,11 @@ __device__ inline D3 dclamp(D3 x, float lo, float hi) { return x.v <= lo ? dc(lo
 __device__ inline D3 dmaxc(D3 x, float c) { return x.v > c ? x : dc(c); }
 __device__ inline D3 dabs(D3 x) { return x.v >= 0.f ? x : D3{-x.v, -x.s, -x.a}; }
 
-// pack (rgb, c), tile max with its pixel
+// pack (rgb, c), the CoCs by themselves, tile max with its pixel
 __global__ __launch_bounds__(256) void k_ppb_pack(const float* __restrict__ color, const float* __restrict__ depth,
                                                   CamK k, LensK l, int tile, float4* __restrict__ pack,
-                                                  float* __restrict__ tile_r, int* __restrict__ tile_arg) {
+                                                  float* __restrict__ coc, float* __restrict__ tile_r,
+                                                  int* __restrict__ tile_arg) {
   __shared__ float red[256];
   __shared__ int redi[256];
   const int tid = threadIdx.x;
@@ -934,6 +935,7 @@ __global__ __launch_bounds__(256) void k_ppb_pack(const float* __restrict__ colo
     size_t p = (size_t)y * k.W + x;
     float c = coc_px(l, depth[p]);
     pack[p] = make_float4(color[p], color[N + p], color[2 * N + p], c);
+    coc[p] = c;
     r = 0.5f * fabsf(c);
     idx = (int)p;
   }
@@ -1007,14 +1009,7 @@ __global__ void k_fill_f(float* __restrict__ p, size_t n, float v) {
   if (i < n) p[i] = v;
 }
 
-#ifndef PPB_WIN_E
-#define PPB_WIN_E 21                     // largest ceil(R) accumulated in one LDS window per block
-#endif
-#define PPB_WIN (17 + 2 * PPB_WIN_E)     // window side at that radius
-#define PPB_FOOT (PPG_SIDE * PPG_SIDE)   // one tap's 17x17 footprint
-#define PPB_PAD 18                       // the posts' 16x16 grid with a zero border
-
-// Sample geometry of tap u at radius R relative to a pixel's texel grid: the
+// Sample geometry of a tap at radius R relative to a pixel's texel grid: the
 // footprint corner offset (floor R u) and the bilinear fractions.
 struct TapGeo {
   int ix, iy;
@@ -1026,324 +1021,600 @@ __device__ __forceinline__ TapGeo tap_geo(float R, float4 u) {
   return TapGeo{(int)fx, (int)fy, ox - fx, oy - fy};
 }
 
-// texels_clamped with 32-bit byte offsets (images below 2^28 pixels)
-__device__ __forceinline__ void texels_clamped32(const float4* __restrict__ pack, int W, int H, int xa, int ya,
-                                                 float4& v00, float4& v10, float4& v01, float4& v11) {
-  const unsigned xa_ = (unsigned)clampi(xa, 0, W - 1), xb_ = (unsigned)clampi(xa + 1, 0, W - 1);
-  const unsigned ya_ = (unsigned)clampi(ya, 0, H - 1) * (unsigned)W, yb_ = (unsigned)clampi(ya + 1, 0, H - 1) * (unsigned)W;
-  const char* pb = (const char*)pack;
-  v00 = *(const float4*)(pb + ((ya_ + xa_) << 4));
-  v10 = *(const float4*)(pb + ((ya_ + xb_) << 4));
-  v01 = *(const float4*)(pb + ((yb_ + xa_) << 4));
-  v11 = *(const float4*)(pb + ((yb_ + xb_) << 4));
-}
+#ifndef PPB_WIN_E
+#define PPB_WIN_E 20                            // largest |offset| accumulated in a block's LDS window
+#endif
+static_assert(17 + 2 * PPB_WIN_E <= 64, "a window row per wave");
+#ifndef PPB_MINW
+#define PPB_MINW 1
+#endif
+#ifndef PPB_G
+#define PPB_G 6                                 // taps whose weights are exchanged at a time
+#endif
+#define PPB_WIN (17 + 2 * PPB_WIN_E)            // the window's side
+#define PPB_WS ((PPB_WIN + 3) / 8 * 8 + 4)      // its row stride: the four rows a wave adds to at a time lie in different banks
+#define PPB_SUMS 9
+enum { S_W, S_C, S_A, S_R, S_GW, S_GC, S_GA, S_GR, S_GM };
 
-// The forward-mode gather's taps of one pixel (value, d/dS1, d/dA).  SLOPE:
-// the tile radius R moves with S1 and A, so every sample moves with it and
-// its spatial slopes enter the derivatives.
-template <bool SLOPE>
-__device__ __forceinline__ void fwd_taps(const float4* __restrict__ pack, const float4* __restrict__ taps, int ntap,
-                                         int n_taps, int W, int H, int x, int y, const D3& R, const D3& cpv,
-                                         const D3& rp, float dcs, float inv_A, float inv_ramp, D3& nr, D3& ng,
-                                         D3& nb, D3& den) {
-  if (ntap <= 0) return;
-  // each tap's texels are requested one tap ahead, so their latency overlaps
-  // the previous tap's arithmetic (the last tap's are requested twice)
-  float4 v00, v10, v01, v11;
-  {
-    const TapGeo t0 = tap_geo(R.v, taps[0]);
-    texels_clamped32(pack, W, H, x + t0.ix, y + t0.iy, v00, v10, v01, v11);
-  }
-  for (int kk = 0; kk < ntap; ++kk) {
-    const float4 u = taps[kk];
-    const TapGeo tg = tap_geo(R.v, u);
-    const float ax = tg.ax, ay = tg.ay, bx = 1.f - ax, by = 1.f - ay;
-    float4 n00, n10, n01, n11;
-    {
-      const TapGeo tn = tap_geo(R.v, taps[kk + 1 < ntap ? kk + 1 : kk]);
-      texels_clamped32(pack, W, H, x + tn.ix, y + tn.iy, n00, n10, n01, n11);
-    }
-    const float w00 = bx * by, w10 = ax * by, w01 = bx * ay, w11 = ax * ay;
-    // samples, their spatial slopes, and their motion with R
-    const float dxs = u.x * R.s, dxa = u.x * R.a, dys = u.y * R.s, dya = u.y * R.a;
-#define SAMPLE(c)                                                                                   \
-  const float s_##c = w00 * v00.c + w10 * v10.c + w01 * v01.c + w11 * v11.c;                        \
-  const float sx_##c = SLOPE ? by * (v10.c - v00.c) + ay * (v11.c - v01.c) : 0.f;                    \
-  const float sy_##c = SLOPE ? bx * (v01.c - v00.c) + ax * (v11.c - v10.c) : 0.f;
-    SAMPLE(x) SAMPLE(y) SAMPLE(z) SAMPLE(w)
-#undef SAMPLE
-    const D3 cq = SLOPE ? dk(s_w, dcs + sx_w * dxs + sy_w * dys, s_w * inv_A + sx_w * dxa + sy_w * dya)
-                        : dk(s_w, dcs, s_w * inv_A);
-    const D3 rq = 0.5f * dabs(cq);
-    const D3 tk = dclamp(inv_ramp * (cq - cpv), 0.f, 1.f);
-    const D3 dpos = dmaxc(rq - rp, 0.f);
-    const D3 reff = rq - tk * dpos;
-    const D3 a = dclamp(reff - u.z * R + dc(0.5f), 0.f, 1.f);
-    const D3 rq5 = dmaxc(rq, 0.5f);
-    const D3 w = dquot(a * ((1.0f / (float)n_taps) * (R * R)), rq5 * rq5);
-    if (SLOPE) {
-      nr = nr + w * dk(s_x, sx_x * dxs + sy_x * dys, sx_x * dxa + sy_x * dya);
-      ng = ng + w * dk(s_y, sx_y * dxs + sy_y * dys, sx_y * dxa + sy_y * dya);
-      nb = nb + w * dk(s_z, sx_z * dxs + sy_z * dys, sx_z * dxa + sy_z * dya);
+// The 5x2 texels whose corner is (x, y), clamped to the edge: packed texels,
+// or the CoCs alone.  INTERIOR: none lies outside the image (buffer loads,
+// their row in the scalar offset).
+template <bool INTERIOR>
+struct FootRows {
+  int W, H, ya;
+  unsigned xa, xb;  // INTERIOR: xa is the corner's index
+  __device__ __forceinline__ FootRows(int W_, int H_, int x, int y) : W(W_), H(H_), ya(y) {
+    if (INTERIOR) {
+      xa = __umul24((unsigned)y, (unsigned)W) + (unsigned)x;
+      xb = xa + 1;
     } else {
-      nr = nr + s_x * w;
-      ng = ng + s_y * w;
-      nb = nb + s_z * w;
+      xa = (unsigned)clampi(x, 0, W - 1);
+      xb = (unsigned)clampi(x + 1, 0, W - 1);
     }
-    den = den + w;
-    v00 = n00;
-    v10 = n10;
-    v01 = n01;
-    v11 = n11;
+  }
+  __device__ __forceinline__ void texels(const float4* __restrict__ pack, int j, float4& v0, float4& v1) const {
+    if (INTERIOR) {
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float4*>(pack), (short)0, W * H * 16, HDOF_BUFFER_WORD3);
+      v0 = buffer_texel(rs, xa << 4, j * W * 16);
+      v1 = buffer_texel(rs, (xa << 4) + 16, j * W * 16);
+    } else {
+      const unsigned row = __umul24((unsigned)clampi(ya + j, 0, H - 1), (unsigned)W);
+      v0 = *(const float4*)((const char*)pack + ((row + xa) << 4));
+      v1 = *(const float4*)((const char*)pack + ((row + xb) << 4));
+    }
+  }
+  __device__ __forceinline__ float2 cocs(const float* __restrict__ coc, int j) const {
+    if (INTERIOR) {
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(coc), (short)0, W * H * 4, HDOF_BUFFER_WORD3);
+      const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(xa << 2), j * W * 4, 0);
+      float2 f;
+      __builtin_memcpy(&f, &v, sizeof f);
+      return f;
+    }
+    const unsigned row = __umul24((unsigned)clampi(ya + j, 0, H - 1), (unsigned)W);
+    return make_float2(*(const float*)((const char*)coc + ((row + xa) << 2)),
+                       *(const float*)((const char*)coc + ((row + xb) << 2)));
+  }
+};
+
+// What one lane keeps of its four pixels for pass 1.
+struct PpbPx {
+  float c[4], g[3][4], gc[4];  // CoC, incoming gradient, and the pixel's own colour projected on it
+};
+
+// Pass 1: the sums of one lane's four pixels over the wave's taps.  A tap's
+// weight w = a / max(c_q^2, 1) (see GatherAcc) depends on the sample's CoC
+// c_q, the pixel's CoC c_p and the tile radius R, of which S1 and A move all
+// CoCs by dcs and c / A and the radius by R.s and R.a, and the samples along
+// u with it.  So four sums of the weight and of its partial derivatives
+// (S_C: d/dc_q + d/dc_p; S_A: the same times the CoCs; S_R: by R, area and
+// motion along u included but for 2 w / R), the same four times the sample's
+// colour projected on the pixel's incoming gradient (S_G*), and the motion of
+// that projection (S_GM) give both derivatives of the composite: nine
+// scalar sums in place of four values of three channels and their weight.
+// MOVES: the tile radius moves (it is not at its cap).
+template <bool MOVES>
+__device__ __forceinline__ void ppb_sums(const float4 (&v0)[5], const float4 (&v1)[5], const float4& u, float ax,
+                                         float ay, float R, float inv_ramp, const PpbPx& px,
+                                         float (&S)[PPB_SUMS][4]) {
+  const float d = fmaf(-R, u.z, 0.5f), uz2 = 2.f * u.z;
+  const float dxb = u.x * (1.f - ay), dxa = u.x * ay;
+  // a row's slope along x, and its interpolation
+  float4 e0 = make_float4(v1[0].x - v0[0].x, v1[0].y - v0[0].y, v1[0].z - v0[0].z, v1[0].w - v0[0].w);
+  const float bx = 1.f - ax, by = 1.f - ay;
+  float4 h0 = make_float4(fmaf(ax, v1[0].x, bx * v0[0].x), fmaf(ax, v1[0].y, bx * v0[0].y), fmaf(ax, v1[0].z, bx * v0[0].z),
+                          fmaf(ax, v1[0].w, bx * v0[0].w));
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 a0 = v0[q + 1], a1 = v1[q + 1];
+    const float4 e1 = make_float4(a1.x - a0.x, a1.y - a0.y, a1.z - a0.z, a1.w - a0.w);
+    const float4 h1 = make_float4(fmaf(ax, a1.x, bx * a0.x), fmaf(ax, a1.y, bx * a0.y), fmaf(ax, a1.z, bx * a0.z),
+                                  fmaf(ax, a1.w, bx * a0.w));
+    const float4 f1 = make_float4(h1.x - h0.x, h1.y - h0.y, h1.z - h0.z, h1.w - h0.w);  // slope along y
+    const float g0 = px.g[0][q], g1 = px.g[1][q], g2 = px.g[2][q];
+    const float cq = fmaf(ay, h1.w, by * h0.w);
+    const float gy = fmaf(g2, f1.z, fmaf(g1, f1.y, g0 * f1.x));
+    const float sg = fmaf(g2, fmaf(ay, h1.z, by * h0.z), fmaf(g1, fmaf(ay, h1.y, by * h0.y), fmaf(g0, fmaf(ay, h1.x, by * h0.x), -px.gc[q])));
+    const float cp = px.c[q];
+    const float aq = fabsf(cq), raw = (cq - cp) * inv_ramp;
+    const float tk = clamp01(raw), dp = fmaxf(0.f, aq - fabsf(cp));
+    const float reff = fmaf(-tk, dp, aq);
+    const float araw = fmaf(reff, 0.5f, d);
+    const float c2 = cq * cq, irq = __builtin_amdgcn_rcpf(fmaxf(c2, 1.f));
+    const float w = clamp01(araw) * irq;
+    const float kh = araw > 0.f && araw < 1.f ? 0.5f * irq : 0.f;
+    const bool ramp = raw > 0.f && raw < 1.f;
+    const float tm = dp > 0.f ? tk : 0.f;
+    const float f = copysignf(1.f - tm, cq);
+    const float w2 = c2 > 1.f ? 2.f * w : 0.f, T = w2 * (irq * cq);
+    const float wc = fmaf(kh, fmaf(copysignf(1.f, cp), tm, f), -T);
+    const float wa = fmaf(kh, fmaf(-(ramp ? raw : 0.f), dp, reff), -w2);
+    S[S_W][q] += w;
+    S[S_C][q] += wc;
+    S[S_A][q] += wa;
+    S[S_GW][q] = fmaf(w, sg, S[S_GW][q]);
+    S[S_GC][q] = fmaf(wc, sg, S[S_GC][q]);
+    S[S_GA][q] = fmaf(wa, sg, S[S_GA][q]);
+    if (MOVES) {
+      // slopes along u: of the CoC, and of the projected colour
+      const float mc = fmaf(u.y, f1.w, fmaf(dxa, e1.w, dxb * e0.w));
+      const float mx = fmaf(dxa, e1.x, dxb * e0.x), my = fmaf(dxa, e1.y, dxb * e0.y),
+                  mz = fmaf(dxa, e1.z, dxb * e0.z);
+      const float mg = fmaf(u.y, gy, fmaf(g2, mz, fmaf(g1, my, g0 * mx)));
+      const float wq = fmaf(kh, fmaf(ramp ? -inv_ramp : 0.f, dp, f), -T);
+      const float wr = fmaf(wq, mc, -kh * uz2);
+      S[S_R][q] += wr;
+      S[S_GR][q] = fmaf(wr, sg, S[S_GR][q]);
+      S[S_GM][q] = fmaf(w, mg, S[S_GM][q]);
+      e0 = e1;
+    }
+    h0 = h1;
   }
 }
 
-// The CoCs (w) of the four clamp-to-edge texels of the bilinear footprint
-// whose corner is (xa, ya), in the order 00, 10, 01, 11 (images below 2^28
-// pixels: 32-bit byte offsets).
-__device__ __forceinline__ float4 cocs_clamped(const float4* __restrict__ pack, int W, int H, int xa, int ya) {
-  const unsigned xa_ = (unsigned)clampi(xa, 0, W - 1), xb_ = (unsigned)clampi(xa + 1, 0, W - 1);
-  const unsigned ya_ = (unsigned)clampi(ya, 0, H - 1) * (unsigned)W, yb_ = (unsigned)clampi(ya + 1, 0, H - 1) * (unsigned)W;
-  const char* pw = (const char*)pack + 12;
-  return make_float4(*(const float*)(pw + ((ya_ + xa_) << 4)), *(const float*)(pw + ((ya_ + xb_) << 4)),
-                     *(const float*)(pw + ((yb_ + xa_) << 4)), *(const float*)(pw + ((yb_ + xb_) << 4)));
-}
-
-// Footprint texel t = (r, q) of one tap collects the posts of pixels
-// (r - dy, q - dx) with the block-uniform bilinear weight of corner (dx, dy);
-// kb is the padded post grid (zero border), so no bounds checks.  MODE 1:
-// added to the block's LDS window; MODE 2: added to the image (clamped to
-// the edge) with global atomics.
-template <int MODE>
-__device__ __forceinline__ void foot_texel(const float4* kb, int t, float w00, float w10, float w01, float w11,
-                                           const TapGeo& tg, int E, int wd, float* acc, float* __restrict__ gcol,
-                                           int x0, int y0, int W, int H, size_t N) {
-  const int r = t / PPG_SIDE, q = t - r * PPG_SIDE;
-  const float4* b = kb + r * PPB_PAD + q;  // padded (r - dy + 1, q - dx + 1) = b[(1 - dy) PPB_PAD + 1 - dx]
-  const float4 k00 = b[PPB_PAD + 1], k01 = b[PPB_PAD], k10 = b[1], k11 = b[0];
-  float3 v;
-  v.x = fmaf(w11, k11.x, fmaf(w01, k10.x, fmaf(w10, k01.x, w00 * k00.x)));
-  v.y = fmaf(w11, k11.y, fmaf(w01, k10.y, fmaf(w10, k01.y, w00 * k00.y)));
-  v.z = fmaf(w11, k11.z, fmaf(w01, k10.z, fmaf(w10, k01.z, w00 * k00.z)));
-  if (MODE == 1) {
-    float* wp = acc + (tg.iy + E + r) * wd + tg.ix + E + q;
-    wp[0] += v.x;
-    wp[wd * wd] += v.y;
-    wp[2 * wd * wd] += v.z;
-  } else if (v.x != 0.f || v.y != 0.f || v.z != 0.f) {
-    // footprint texel (r, q) is image texel (y0 + iy + r, x0 + ix + q), clamped to the edge
-    const size_t gi = (size_t)clampi(y0 + tg.iy + r, 0, H - 1) * W + clampi(x0 + tg.ix + q, 0, W - 1);
-    atomicAdd(&gcol[gi], v.x);
-    atomicAdd(&gcol[N + gi], v.y);
-    atomicAdd(&gcol[2 * N + gi], v.z);
+// Pass 1 over the wave's taps, texels read from the image (tiles of 4 or 8
+// pixels: the footprint differs between the lanes).
+template <bool INTERIOR>
+__device__ __forceinline__ void ppb_pass1(const float4* __restrict__ pack, const float4* __restrict__ taps, int k0,
+                                          int n_taps, int W, int H, int x, int yb, float R, float inv_ramp,
+                                          const PpbPx& px, float (&S)[PPB_SUMS][4]) {
+  for (int k = k0; k < n_taps; k += 4) {
+    const float4 u = taps[k];
+    const TapGeo tg = tap_geo(R, u);
+    const FootRows<INTERIOR> rows(W, H, x + tg.ix, yb + tg.iy);
+    float4 v0[5], v1[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) rows.texels(pack, j, v0[j], v1[j]);
+    ppb_sums<true>(v0, v1, u, tg.ax, tg.ay, R, inv_ramp, px, S);
   }
 }
 
-// Adjoint of post-filter + composite.  Pass 1 per pixel: the gather again in
-// forward mode (value, d/dS1, d/dA through the CoC, the tile radius and the
-// sample positions), then the composite backward, which gives the focus and
-// aperture gradients (block partials) and the colour gradient of the pixel
-// itself.  Pass 2: the colour gradient flowing through the gather weights,
-// scattered to the four texels of every tap.  16-pixel tiles (UNI) share
-// one tap geometry per block: per tap the block's contributions land on one
-// 17x17 footprint, which is formed in LDS as a transposed bilinear gather of
-// the pixels' posts (no LDS atomics) and then added to one
-// (17 + 2 ceil R)^2 LDS window for ceil R <= PPB_WIN_E (flushed once with
-// global atomics) or straight to global memory (larger R); window and
-// footprint texels are image texels clamped to the edge, as in the gather.
-// Other tile sizes add straight to global memory per pixel and tap.
+// The same for 16-pixel tiles: the wave stages each of its taps' 17x17
+// texels in its own two-buffer LDS ring (see gather_taps_quad), a tap ahead.
+template <bool MOVES, bool INTERIOR>
+__device__ __forceinline__ void ppb_pass1_staged(float4* stg, const float4* __restrict__ pack,
+                                                 const float4* __restrict__ taps, int k0, int n_taps, int W, int H,
+                                                 int x0, int y0, int lane, float R, float inv_ramp, const PpbPx& px,
+                                                 float (&S)[PPB_SUMS][4]) {
+  if (k0 >= n_taps) return;
+  StageLane sl;
+#pragma unroll
+  for (int s = 0; s < PPG_SLOTS; ++s) {
+    const int idx = s * 64 + lane < PPG_TEX ? s * 64 + lane : s * 64 + lane - 64;
+    sl.sr[s] = idx / PPG_SIDE;
+    sl.sc[s] = idx - sl.sr[s] * PPG_SIDE;
+    sl.so[s] = (unsigned)(sl.sr[s] * W + sl.sc[s]) * 16u;
+    sl.lo[s] = sl.sr[s] * PPG_STRIDE + sl.sc[s];
+  }
+  sl.last = lane < PPG_TEX - 4 * 64;
+  const int lofs = (lane >> 4) * 4 * PPG_STRIDE + (lane & 15);
+  float4 u = taps[k0];
+  stage_store_texels(stg, stage_load<INTERIOR>(pack, u, R, x0, y0, W, H, sl), sl);
+  for (int k = k0, b = 0; k < n_taps; k += 4, b ^= 1) {
+    wave_lds_sync();  // tap k's texels stored; tap k - 4's reads done
+    const float4 un = taps[min(k + 4, n_taps - 1)];
+    const Stage sn = stage_load<INTERIOR>(pack, un, R, x0, y0, W, H, sl);
+    const float4* a = stg + b * PPG_TAPSZ + lofs;
+    float4 v0[5], v1[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+      v0[j] = a[j * PPG_STRIDE];
+      v1[j] = a[j * PPG_STRIDE + 1];
+    }
+    const TapGeo tg = tap_geo(R, u);
+    ppb_sums<MOVES>(v0, v1, u, tg.ax, tg.ay, R, inv_ramp, px, S);
+    stage_store_texels(stg + (b ^ 1) * PPG_TAPSZ, sn, sl);
+    u = un;
+  }
+}
+
+// Pass 2's weights of one lane's four pixels for the tap with geometry tg
+// and distance term d.
+template <bool INTERIOR>
+__device__ __forceinline__ float4 ppb_weights(const float* __restrict__ coc, int W, int H, int x, int yb,
+                                              const TapGeo& tg, float d, float inv_ramp, const PpbPx& px) {
+  const FootRows<INTERIOR> rows(W, H, x + tg.ix, yb + tg.iy);
+  float h[5], wv[4];
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    const float2 c = rows.cocs(coc, j);
+    h[j] = fmaf(tg.ax, c.y, (1.f - tg.ax) * c.x);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float cq = fmaf(tg.ay, h[q + 1], (1.f - tg.ay) * h[q]);
+    const float aq = fabsf(cq), cp = px.c[q];
+    const float tk = clamp01((cq - cp) * inv_ramp);
+    const float reff = fmaf(-tk, fmaxf(0.f, aq - fabsf(cp)), aq);
+    wv[q] = clamp01(fmaf(reff, 0.5f, d)) * __builtin_amdgcn_rcpf(fmaxf(cq * cq, 1.f));
+  }
+  return make_float4(wv[0], wv[1], wv[2], wv[3]);
+}
+
+// a block barrier that orders LDS accesses only (global loads and atomics
+// stay in flight)
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// lane i's value of lane i - 1 of its row of 16 lanes, 0 in lane 0
+__device__ __forceinline__ float row_left(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, true));
+}
+
+// Adds one channel of a tile's footprint to the window (w: the lane's texel
+// of it): a lane's rows r[0..3] and, in the tile's last rows, r[4], joined
+// with the left neighbour's (one rounded sum per tap and texel), and the
+// tile's last column.  Lanes of one tile meet in no texel, and a wave's LDS
+// accesses run in order; the `nt` tiles of a block take turns.
+__device__ __forceinline__ void win_add(float* w, const float (&r)[5], float ax, bool on, bool firstc, bool lastc,
+                                        bool lastr, int mine, int nt) {
+  float v[5];
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    const float left = row_left(r[j]);
+    v[j] = fmaf(ax, firstc ? 0.f : left, (1.f - ax) * r[j]);
+  }
+  for (int t = 0; t < nt; ++t) {
+    if (on && (nt == 1 || mine == t)) {
+      float a[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = w[j * PPB_WS];
+      if (lastc)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j * PPB_WS + 1] = fmaf(ax, r[j], w[j * PPB_WS + 1]);
+      if (lastr) {
+        w[4 * PPB_WS] += v[4];
+        if (lastc) w[4 * PPB_WS + 1] = fmaf(ax, r[4], w[4 * PPB_WS + 1]);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w[j * PPB_WS] = a[j] + v[j];
+    }
+    // (keeps the compiler from moving the next reads, of other lanes'
+    // texels, before these writes)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Adds it to the image instead.
+__device__ __forceinline__ void image_add(float* __restrict__ gc, const float (&r)[5], int xt, int yt, int W, int H,
+                                          float ax, bool on, bool firstc, bool lastc, bool lastr) {
+  const unsigned xa = (unsigned)clampi(xt, 0, W - 1), xb = (unsigned)clampi(xt + 1, 0, W - 1);
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    const float left = row_left(r[q]);
+    const float t = fmaf(ax, firstc ? 0.f : left, (1.f - ax) * r[q]);
+    float* const row = gc + __umul24((unsigned)clampi(yt + q, 0, H - 1), (unsigned)W);
+    if (on && (q < 4 || lastr)) {
+      if (t != 0.f) atomicAdd(row + xa, t);
+      if (lastc && r[q] != 0.f) atomicAdd(row + xb, ax * r[q]);
+    }
+  }
+}
+
+// Pass 2 of one channel for n <= PPB_G taps: their weights times the pixels'
+// kc (and kup of the pixel above the lane's first), joined along the column.
+template <bool UNI, class Geo>
+__device__ __forceinline__ void ppb_scatter(const float4* wts, int lane, int n, const float (&kc)[4], float kup, int E,
+                                            float* win, float* __restrict__ gc, int x, int yb, int W, int H,
+                                            bool firstc, bool lastc, bool lastr, int mine, int nt, Geo geo) {
+  float4 w4[PPB_G];
+  float wu[PPB_G];
+#pragma unroll
+  for (int j = 0; j < PPB_G; ++j) {
+    w4[j] = wts[j * 64 + lane];
+    wu[j] = wts[j * 64 + (lane < 16 ? lane : lane - 16)].w;
+  }
+#pragma unroll
+  for (int j = 0; j < PPB_G; ++j) {
+    if (j < n) {
+      const TapGeo tg = geo(j);
+      const float post[4] = {kc[0] * w4[j].x, kc[1] * w4[j].y, kc[2] * w4[j].z, kc[3] * w4[j].w};
+      const float ay = tg.ay, by = 1.f - ay;
+      const float r[5] = {fmaf(by, post[0], ay * (kup * wu[j])), fmaf(by, post[1], ay * post[0]),
+                          fmaf(by, post[2], ay * post[1]), fmaf(by, post[3], ay * post[2]), ay * post[3]};
+      const bool in = tg.ix >= -E && tg.ix <= E && tg.iy >= -E && tg.iy <= E;
+      if (!UNI || in) win_add(win + tg.iy * PPB_WS + tg.ix, r, tg.ax, in, firstc, lastc, lastr, mine, nt);
+      if (UNI ? !in : __builtin_amdgcn_ballot_w64(!in) != 0ull)
+        image_add(gc, r, x + tg.ix, yb + tg.iy, W, H, tg.ax, !in, firstc, lastc, lastr);
+    }
+  }
+}
+
+// Adjoint of post-filter + composite.  One block per 16x16 pixels; each of
+// its four waves takes every fourth tap of all 256 pixels, a lane four
+// vertically adjacent ones (one tile's: tiles are 4, 8 or 16 pixels), whose
+// footprints of a tap share 5x2 texels, so a tap's geometry and texels are
+// read once per four pixels.  Pass 1: the gather with the sums of its
+// derivatives (ppb_sums), joined over the waves in LDS; then one pixel per
+// thread: the composite backward, which gives the focus and aperture
+// gradients (block partials) and the colour gradient of the pixel itself.
+// Pass 2: the colour gradient flowing through the gather weights (recomputed
+// from the CoC plane: 48 weights of 256 pixels would take 48 KB of LDS),
+// transposed to the texels of every tap: the lanes' posts are joined to the
+// tile's footprint in registers and added to the block's LDS window if the
+// tap's offset is at most PPB_WIN_E (flushed once with global atomics; window
+// texels are image texels clamped to the edge, as in the gather), or to the
+// image.  Of PPB_G taps at a time three waves add a channel each to the
+// window, without barriers between the taps, and the fourth forms half of
+// the weights.  (LDS float atomics would let every wave add to all channels,
+// but take 190 clocks each: 4.1 ms for the 1080p image below; four waves'
+// channels in turns with a barrier each: 0.74.)
+// Bound at 1080p, 48 taps, 16-pixel tiles: vector arithmetic (65 %), the rest
+// waiting for LDS and, on the quarter of the tiles with R of 46, for global
+// atomics (0.14 ms): 0.92 -> 0.68 ms.  1708x923 with 4-pixel tiles, whose
+// radii differ within a block: 5.0 -> 1.8 ms, of it 1.5 the tiles' turns.
+// The window's limit: a third block per CU fits up to 20 (24: 0.2 ms slower).
+struct PpbArgs {
+  const float4* pack;
+  const float *coc, *rad;
+  const int* rad_arg;
+  const float4* taps;
+  int n_taps, W, H, tile;
+  float inv_ramp;
+  LensK l;
+  float spx;
+  const uint8_t* spp;
+  const float *cn, *cf, *hr;
+  float inv_ht;
+  int rt_override;
+  const float* g;
+  float* gcol;
+  float2* partial;
+};
+
+struct PpbLds {
+  // the waves' rings of staged texels, then their sums, then the window and
+  // behind it two buffers of the weights of a group of taps
+  static constexpr int WIN = 3 * PPB_WIN * PPB_WS, WTS = 2 * PPB_G * 256, SUMS = 4 * PPB_SUMS * 256,
+                       RING = 4 * 2 * 4 * PPG_TAPSZ;
+  static constexpr int MAX1 = SUMS > RING ? SUMS : RING;
+  float buf[WIN + WTS > MAX1 ? WIN + WTS : MAX1];
+  float2 red[4];
+};
+
+// The tile of pixel (x, y), -1 where there is none (tile: a power of two).
+__device__ __forceinline__ int ppb_tile(const PpbArgs& A, int x, int y) {
+  const int sh = 31 - __clz(A.tile), TW = (A.W + A.tile - 1) >> sh;
+  return (x >> sh) < TW && (y >> sh) < (A.H + A.tile - 1) >> sh ? (y >> sh) * TW + (x >> sh) : -1;
+}
+
+// One block.  UNI: one radius R for all its pixels (a tile of 16 pixels, or
+// smaller tiles of equal radius): the taps' geometry is the wave's, their
+// texels are staged and the footprint is one of 16x16 pixels.
 template <bool UNI>
-__global__ __launch_bounds__(256) void k_ppc_backward(
-    const float4* __restrict__ pack, const float* __restrict__ rad, const int* __restrict__ rad_arg,
-    const float4* __restrict__ taps, int n_taps, int W, int H, int tile, float inv_ramp, LensK l, float spx,
-    const uint8_t* __restrict__ spp, const float* __restrict__ cn, const float* __restrict__ cf,
-    const float* __restrict__ hr, float inv_ht, int rt_override, const float* __restrict__ g,
-    float* __restrict__ gcol, float2* __restrict__ partial) {
-  __shared__ float acc[UNI ? 3 * PPB_WIN * PPB_WIN : 1];
-  // two buffers of the 16x16 pixels' posts, each with a zero border (18x18)
-  __shared__ float4 posts[UNI ? 2 : 1][UNI ? PPB_PAD * PPB_PAD : 128];
-  float2* red = (float2*)&posts[0][0];  // the partials' reduction, after pass 2
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int TWb = (W + 15) >> 4, THb = (H + 15) >> 4;
-  const int blk = UNI ? xcd_block(blockIdx.x, TWb * THb) : blockIdx.x;
+__device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk, float R) {
+  const float4* __restrict__ pack = A.pack;
+  const float* __restrict__ coc = A.coc;
+  const float4* __restrict__ taps = A.taps;
+  const float* __restrict__ g = A.g;
+  float* __restrict__ gcol = A.gcol;
+  const int n_taps = A.n_taps, W = A.W, H = A.H, tile = A.tile;
+  const float inv_ramp = A.inv_ramp;
+  const LensK& l = A.l;
+  float* const buf = lds.buf;
+  float4 (*const wts)[PPB_G * 64] = (float4 (*)[PPB_G * 64])(buf + PpbLds::WIN);
+  float2* const red = lds.red;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int TWb = (W + 15) >> 4;
   const int x0 = (blk % TWb) * 16, y0 = (blk / TWb) * 16;
-  const int lx = lane & 15, ly = wave * 4 + (lane >> 4);
-  const int x = x0 + lx, y = y0 + ly;
-  float gs = 0.0f, ga = 0.0f;
+  const int lx = lane & 15, ly = (lane >> 4) * 4;
+  const int x = x0 + lx, yb = y0 + ly;
   const size_t N = (size_t)W * H;
-  const float dcs = -l.A * spx * l.invS1 * l.invS1;  // dc/dS1 (every pixel)
+  const float dcs = -l.A * A.spx * l.invS1 * l.invS1;    // dc/dS1 (every pixel)
   const float inv_A = l.A > 0.0f ? 1.0f / l.A : 0.0f;  // unit CoC = c / A
+  // the radius' derivatives through the pixel that sets it
+  const int ti = ppb_tile(A, x, yb), m = ti >= 0 ? A.rad_arg[ti] : -1;
+  float Rs = 0.f, Ra = 0.f;
+  if (m >= 0) {
+    const float cm = pack[m].w, sg = cm >= 0.f ? 0.5f : -0.5f;
+    Rs = sg * dcs;
+    Ra = sg * cm * inv_A;
+  }
+  const bool some = __builtin_amdgcn_ballot_w64(R > 0.f) != 0ull;
+  float Rm = R;
+  if (!UNI)
+    for (int o = 32; o > 0; o >>= 1) Rm = fmaxf(Rm, __shfl_xor(Rm, o));
+  const int ER = __builtin_amdgcn_readfirstlane((int)ceilf(Rm));
+  const bool interior = x0 - ER - 1 >= 0 && x0 + 16 + ER < W && y0 - ER - 1 >= 0 && y0 + 16 + ER < H &&
+                        (long long)W * H * 16 < (1ll << 31);
+  const bool moves = __builtin_amdgcn_ballot_w64(Rs != 0.f || Ra != 0.f) != 0ull;
+  PpbPx px;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const bool ok = x < W && yb + q < H;
+    const size_t p = ok ? (size_t)(yb + q) * W + x : 0;
+    const float4 t = pack[p];
+    px.c[q] = ok ? t.w : 0.f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) px.g[c][q] = ok ? g[c * N + p] : 0.f;
+    px.gc[q] = fmaf(px.g[2][q], t.z, fmaf(px.g[1][q], t.y, px.g[0][q] * t.x));
+  }
+  float S[PPB_SUMS][4] = {};
+  if (some) {
+    if (UNI) {
+      float4* const stg = (float4*)buf + wave * 2 * PPG_TAPSZ;
+      if (moves && interior)
+        ppb_pass1_staged<true, true>(stg, pack, taps, wave, n_taps, W, H, x0, y0, lane, R, inv_ramp, px, S);
+      else if (moves)
+        ppb_pass1_staged<true, false>(stg, pack, taps, wave, n_taps, W, H, x0, y0, lane, R, inv_ramp, px, S);
+      else
+        ppb_pass1_staged<false, false>(stg, pack, taps, wave, n_taps, W, H, x0, y0, lane, R, inv_ramp, px, S);
+      __syncthreads();  // the ring's space takes the sums
+    } else if (interior) {
+      ppb_pass1<true>(pack, taps, wave, n_taps, W, H, x, yb, R, inv_ramp, px, S);
+    } else {
+      ppb_pass1<false>(pack, taps, wave, n_taps, W, H, x, yb, R, inv_ramp, px, S);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PPB_SUMS; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) buf[(wave * PPB_SUMS + i) * 256 + q * 64 + lane] = S[i][q];
+  __syncthreads();
+  // one pixel per thread: row `wave` of its lane's four
+  float gs = 0.f, ga = 0.f, own[3] = {0.f, 0.f, 0.f}, gpp[3] = {0.f, 0.f, 0.f};
+  const int y = yb + wave;
   const bool inside = x < W && y < H;
   const size_t p = inside ? (size_t)y * W + x : 0;
-  const bool traced = inside && spp[p] > 0;
-  const bool active = inside && !(rt_override && traced);
-  const int TW = (W + tile - 1) / tile;
-  const int ti = UNI ? blk : (inside ? (y / tile) * TW + x / tile : 0);
-  const float Rv = rad[ti];
-  const int E = (int)ceilf(Rv);
-  // scatter mode of the block (UNI): 0 global, 1 window, 2 per-tap footprint
-  int mode = 0;
-  if (UNI && Rv > 0.0f) mode = E <= PPB_WIN_E ? 1 : 2;
-  const int wd = 17 + 2 * E;
-  if (UNI && mode == 1)
-    for (int i = tid; i < 3 * wd * wd; i += 256) acc[i] = 0.0f;
-  if (UNI && mode != 0) {
-    for (int i = tid; i < 2 * PPB_PAD * PPB_PAD; i += 256) (&posts[0][0])[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();
-  }
-  const int ntap = Rv > 0.0f ? n_taps : 0;
-  float4 cp4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  float gpp[3] = {0.f, 0.f, 0.f};
-  float area = 0.0f;
-  if (active) {
-    cp4 = pack[p];
+  const bool traced = inside && A.spp[p] > 0;
+  if (inside && !(A.rt_override && traced)) {
+    float s[PPB_SUMS];
+#pragma unroll
+    for (int i = 0; i < PPB_SUMS; ++i) {
+      s[i] = 0.f;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s[i] += buf[(v * PPB_SUMS + i) * 256 + tid];
+    }
+    const float4 cp4 = pack[p];
     const D3 cpv = dk(cp4.w, dcs, cp4.w * inv_A);
     // composite weights
     const D3 phi = dclamp(dabs(cpv) - dc(HDOF_SQRT2), 0.f, 1.f);
     const D3 nu = dclamp(dc(0.5f) - 0.35355339059327376f * cpv, 0.f, 1.f);
-    const float h = hr[p];
+    const float h = A.hr[p];
     const float rho = traced ? 1.0f : 0.0f;
-    const float beta = traced ? clamp01(1.0f - h * inv_ht) : 0.0f;
+    const float beta = traced ? clamp01(1.0f - h * A.inv_ht) : 0.0f;
     const D3 acoef = rho * nu + beta * (dc(1.f) - nu);
     const D3 bcoef = (1.f - rho) * nu + (1.f - beta) * (dc(1.f) - nu);
-    // forward-mode gather
-    const D3 rp = 0.5f * dabs(cpv);
-    const D3 rp5 = dmaxc(rp, 0.5f);
-    const D3 w0 = dquot(dc(1.f), rp5 * rp5);
-    D3 R = dc(Rv);
-    const int m = rad_arg[ti];
-    if (m >= 0) {
-      const float cm = pack[m].w;
-      const float sg = cm >= 0.f ? 0.5f : -0.5f;
-      R = dk(R.v, sg * dcs, sg * cm * inv_A);
-    }
-    D3 nr = w0 * dc(cp4.x), ng = w0 * dc(cp4.y), nb = w0 * dc(cp4.z), den = w0;
-    // a tile radius at the cap does not move with S1 or A: the samples stay
-    // put and their spatial slopes drop out
-    if (R.s != 0.0f || R.a != 0.0f)
-      fwd_taps<true>(pack, taps, ntap, n_taps, W, H, x, y, R, cpv, rp, dcs, inv_A, inv_ramp, nr, ng, nb, den);
-    else
-      fwd_taps<false>(pack, taps, ntap, n_taps, W, H, x, y, R, cpv, rp, dcs, inv_A, inv_ramp, nr, ng, nb, den);
-    // composite backward per channel; post-filter transpose for the colour
+    // the filtered colour, projected on the incoming gradient
     const float gq[3] = {g[p], g[N + p], g[2 * N + p]};
-    const D3 num[3] = {nr, ng, nb};
     const float cr[3] = {cp4.x, cp4.y, cp4.z};
-    const float iden = 1.0f / den.v;
+    const float gcr = fmaf(gq[2], cr[2], fmaf(gq[1], cr[1], gq[0] * cr[0]));  // (as px.gc)
+    float gct = 0.f;
     for (int c = 0; c < 3; ++c) {
-      const float crt = h * cn[c * N + p] + (1.f - h) * cf[c * N + p];
-      const D3 cpp = dquot(num[c], den);
-      const D3 oof = crt * acoef + bcoef * cpp;
-      const D3 out = (dc(1.f) - phi) * dc(cr[c]) + phi * oof;
-      gs = fmaf(gq[c], out.s, gs);
-      ga = fmaf(gq[c], out.a, ga);
-      gpp[c] = gq[c] * phi.v * bcoef.v * iden;
-      const float own = fmaf(gq[c], 1.f - phi.v, gpp[c] * w0.v);
-      if (mode == 1)
-        acc[(c * wd + ly + E) * wd + lx + E] += own;  // this pixel's own window texel
-      else
-        atomicAdd(&gcol[c * N + p], own);
+      gct = fmaf(gq[c], h * A.cn[c * N + p] + (1.f - h) * A.cf[c * N + p], gct);
     }
-    area = R.v * R.v / (float)n_taps;
-  }
-  // pass 2: the weights again (value only) and the scatter of gpp * weight
-  const bool scat = active && (gpp[0] != 0.f || gpp[1] != 0.f || gpp[2] != 0.f);
-  const float rpv = 0.5f * fabsf(cp4.w);
-  if (UNI && mode != 0) {
-    // per tap: every pixel posts gpp * weight, then footprint texel (r, q)
-    // collects the posts of pixels (r - dy, q - dx) with the block-uniform
-    // bilinear weight of corner (dx, dy)
-    // each tap's texel CoCs are requested one tap ahead (see fwd_taps)
-    float4 cw = make_float4(0.f, 0.f, 0.f, 0.f);
-    // blocks start at different taps, so neighbouring blocks' atomics land
-    // on different texels at a time
-    const int rot = ntap > 0 ? (int)((blk * 17u) % (unsigned)ntap) : 0;
-    if (scat && ntap > 0) {
-      const TapGeo t0 = tap_geo(Rv, taps[rot]);
-      cw = cocs_clamped(pack, W, H, x + t0.ix, y + t0.iy);
-    }
-    for (int kk = 0; kk < ntap; ++kk) {
-      const int ki = kk + rot < ntap ? kk + rot : kk + rot - ntap;
-      const float4 u = taps[ki];
-      const TapGeo tg = tap_geo(Rv, u);
-      const float ax = tg.ax, ay = tg.ay, bx = 1.f - ax, by = 1.f - ay;
-      float4 cwn = cw;
-      if (scat && kk + 1 < ntap) {
-        const int kn = ki + 1 < ntap ? ki + 1 : 0;
-        const TapGeo tn = tap_geo(Rv, taps[kn]);
-        cwn = cocs_clamped(pack, W, H, x + tn.ix, y + tn.iy);
-      }
-      float4 post = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (scat) {
-        const float cq = bx * by * cw.x + ax * by * cw.y + bx * ay * cw.z + ax * ay * cw.w;
-        const float rq = 0.5f * fabsf(cq);
-        const float tk = clamp01((cq - cp4.w) * inv_ramp);
-        const float a = clamp01(rq - tk * fmaxf(0.f, rq - rpv) - Rv * u.z + 0.5f);
-        const float rq5 = fmaxf(rq, 0.5f);
-        const float wv = a * area * __builtin_amdgcn_rcpf(rq5 * rq5);
-        post = make_float4(gpp[0] * wv, gpp[1] * wv, gpp[2] * wv, 0.f);
-      }
-      cw = cwn;
-      float4* kb = posts[kk & 1];
-      kb[(ly + 1) * PPB_PAD + lx + 1] = post;
-      __syncthreads();
-      // footprint texel t of the 17x17 (two per thread for t < 33)
-      const float w00 = bx * by, w10 = ax * by, w01 = bx * ay, w11 = ax * ay;
-      if (mode == 1) {
-        foot_texel<1>(kb, tid, w00, w10, w01, w11, tg, E, wd, acc, gcol, x0, y0, W, H, N);
-        if (tid < PPB_FOOT - 256) foot_texel<1>(kb, tid + 256, w00, w10, w01, w11, tg, E, wd, acc, gcol, x0, y0, W, H, N);
-      } else {
-        foot_texel<2>(kb, tid, w00, w10, w01, w11, tg, E, wd, acc, gcol, x0, y0, W, H, N);
-        if (tid < PPB_FOOT - 256) foot_texel<2>(kb, tid + 256, w00, w10, w01, w11, tg, E, wd, acc, gcol, x0, y0, W, H, N);
-      }
-    }
-  } else if (scat) {
-    for (int kk = 0; kk < ntap; ++kk) {
-      const float4 u = taps[kk];
-      const TapGeo tg = tap_geo(Rv, u);
-      const float ax = tg.ax, ay = tg.ay, bx = 1.f - ax, by = 1.f - ay;
-      const int xa = x + tg.ix, ya = y + tg.iy;
-      const int xa_ = clampi(xa, 0, W - 1), xb_ = clampi(xa + 1, 0, W - 1);
-      const int ya_ = clampi(ya, 0, H - 1), yb_ = clampi(ya + 1, 0, H - 1);
-      const size_t i00 = (size_t)ya_ * W + xa_, i10 = (size_t)ya_ * W + xb_, i01 = (size_t)yb_ * W + xa_,
-                   i11 = (size_t)yb_ * W + xb_;
-      const float w00 = bx * by, w10 = ax * by, w01 = bx * ay, w11 = ax * ay;
-      const float cq = w00 * pack[i00].w + w10 * pack[i10].w + w01 * pack[i01].w + w11 * pack[i11].w;
-      const float rq = 0.5f * fabsf(cq);
-      const float tk = clamp01((cq - cp4.w) * inv_ramp);
-      const float a = clamp01(rq - tk * fmaxf(0.f, rq - rpv) - Rv * u.z + 0.5f);
-      if (a == 0.f) continue;
-      const float rq5 = fmaxf(rq, 0.5f);
-      const float wv = a * area * __builtin_amdgcn_rcpf(rq5 * rq5);
-      for (int c = 0; c < 3; ++c) {
-        const float k = gpp[c] * wv;
-        float* gc = gcol + c * N;
-        atomicAdd(&gc[i00], k * w00);
-        atomicAdd(&gc[i10], k * w10);
-        atomicAdd(&gc[i01], k * w01);
-        atomicAdd(&gc[i11], k * w11);
-      }
+    const D3 cp1 = dmaxc(dabs(cpv), 1.f);
+    const D3 w0 = dquot(dc(1.f), cp1 * cp1);
+    const float area = R * R / (float)n_taps, i2R = R > 0.f ? 2.f / R : 0.f;
+    const float dr = fmaf(i2R, s[S_W], s[S_R]), gr = fmaf(i2R, s[S_GW], s[S_GR] + s[S_GM]);
+    const D3 den = w0 + area * dk(s[S_W], fmaf(dcs, s[S_C], Rs * dr), fmaf(inv_A, s[S_A], Ra * dr));
+    const D3 num = area * dk(s[S_GW], fmaf(dcs, s[S_GC], Rs * gr), fmaf(inv_A, s[S_GA], Ra * gr));
+    const D3 oof = gct * acoef + bcoef * (dc(gcr) + dquot(num, den));
+    const D3 out = gcr * (dc(1.f) - phi) + phi * oof;
+    gs = out.s;
+    ga = out.a;
+    const float iden = phi.v * bcoef.v / den.v;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      gpp[c] = gq[c] * iden;
+      own[c] = fmaf(gq[c], 1.f - phi.v, gpp[c] * w0.v);
+      gpp[c] *= area;
     }
   }
-  if (UNI && mode == 1) {
-    __syncthreads();
-    const int n2 = wd * wd;
-    for (int i = tid; i < 3 * n2; i += 256) {
-      const float v = acc[i];
-      if (v != 0.f) {
-        const int c = i / n2, t = i - c * n2, r = t / wd;
-        const int gy = clampi(y0 - E + r, 0, H - 1), gx = clampi(x0 - E + t - r * wd, 0, W - 1);
-        atomicAdd(&gcol[c * N + (size_t)gy * W + gx], v);
-      }
-    }
-  }
-  __syncthreads();  // the posts' last readers are done
-  red[tid] = make_float2(gs, ga);
+  // the window: texel (r, s) of a channel is image texel (y0 - E + r, x0 - E + s)
+  const int E = min(PPB_WIN_E, ER), wd = 17 + 2 * E;
+  constexpr int PL = PPB_WIN * PPB_WS;  // a channel's plane
+  float* const gp = (float*)wts;
+  __syncthreads();  // all sums read
+#pragma unroll
+  for (int c = 0; c < 3; ++c) gp[c * 256 + tid] = gpp[c];
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o) red[tid] = make_float2(red[tid].x + red[tid + o].x, red[tid].y + red[tid + o].y);
-    __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    for (int i = tid; i < wd * (PPB_WS / 4); i += 256) ((float4*)(buf + c * PL))[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  // the pixels' gpp of the wave's channel, and of the one above them (0 if
+  // that is another footprint's)
+  float kc[4];
+  const float kup = (ly & ((UNI ? 16 : tile) - 1)) == 0 ? 0.f : gp[(wave < 3 ? wave : 0) * 256 + 3 * 64 + lane - 16];
+  bool scat = false;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    kc[q] = gp[(wave < 3 ? wave : 0) * 256 + q * 64 + lane];
+    scat |= gp[q * 64 + lane] != 0.f || gp[256 + q * 64 + lane] != 0.f || gp[512 + q * 64 + lane] != 0.f;
   }
-  if (tid == 0) partial[blockIdx.x] = red[0];
+  scat = __builtin_amdgcn_ballot_w64(scat) != 0ull;
+  lds_barrier();
+#pragma unroll
+  for (int c = 0; c < 3; ++c) buf[c * PL + (ly + wave + E) * PPB_WS + lx + E] = own[c];
+  lds_barrier();
+  // pass 2: the weights again (value only) and the transpose of gpp * weight
+  if (some && scat) {
+    const int tl = UNI ? 16 : tile, nt = UNI ? 1 : (16 / tl) * (16 / tl);
+    const bool firstc = (lx & (tl - 1)) == 0, lastc = (lx & (tl - 1)) == tl - 1;
+    const bool lastr = (ly & (tl - 1)) == tl - 4;
+    const int mine = (ly / tl) * (16 / tl) + lx / tl;
+    float* const win = buf + wave * PL + (ly + E) * PPB_WS + lx + E;
+    float* const gc = gcol + wave * N;
+    // (UNI) lane i keeps the geometry and distance term of tap kl + i
+    TapGeo lg{0, 0, 0.f, 0.f};
+    float ld = 0.f;
+    for (int k0 = 0, kl = 0, b = 0; k0 < n_taps; k0 += PPB_G, b ^= 1) {
+      if (UNI && (k0 == 0 || k0 + PPB_G > kl + 64)) {
+        kl = k0;
+        const float4 u = taps[min(k0 + lane, n_taps - 1)];
+        lg = tap_geo(R, u);
+        ld = fmaf(-R, u.z, 0.5f);
+      }
+      const auto geo = [&](int j) {
+        if (!UNI) return tap_geo(R, taps[k0 + j]);
+        const int i = k0 - kl + j;
+        return TapGeo{__builtin_amdgcn_readlane(lg.ix, i), __builtin_amdgcn_readlane(lg.iy, i),
+                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lg.ax), i)),
+                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lg.ay), i))};
+      };
+      // the fourth wave, which has no channel, forms half of the weights
+      const int n = min(PPB_G, n_taps - k0), j1 = wave < 3 ? wave + 1 : PPB_G;
+      for (int j = wave; j < j1 && j < n; ++j) {
+        const float d = UNI ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ld), k0 - kl + j))
+                            : fmaf(-R, taps[k0 + j].z, 0.5f);
+        const TapGeo tg = geo(j);
+        wts[b][j * 64 + lane] = interior ? ppb_weights<true>(coc, W, H, x, yb, tg, d, inv_ramp, px)
+                                         : ppb_weights<false>(coc, W, H, x, yb, tg, d, inv_ramp, px);
+      }
+      lds_barrier();
+      if (wave < 3)
+        ppb_scatter<UNI>(wts[b], lane, n, kc, kup, E, win, gc, x, yb, W, H, firstc, lastc, lastr, mine, nt, geo);
+    }
+  }
+  __syncthreads();
+  {  // (a window row is no longer than a wave)
+    const int gx = clampi(x0 - E + lane, 0, W - 1);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll 4
+      for (int r = wave; r < wd; r += 4) {
+        const float v = lane < wd ? buf[c * PL + r * PPB_WS + lane] : 0.f;
+        if (v != 0.f) atomicAdd(gcol + c * N + (size_t)clampi(y0 - E + r, 0, H - 1) * W + gx, v);
+      }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    gs += __shfl_xor(gs, o);
+    ga += __shfl_xor(ga, o);
+  }
+  if (lane == 0) red[wave] = make_float2(gs, ga);
+  __syncthreads();
+  if (tid == 0)
+    A.partial[blockIdx.x] = make_float2((red[0].x + red[1].x) + (red[2].x + red[3].x),
+                                      (red[0].y + red[1].y) + (red[2].y + red[3].y));
+}
+
+template <bool T16>
+__global__ __launch_bounds__(256, PPB_MINW) void k_ppc_backward(PpbArgs A) {
+  __shared__ __attribute__((aligned(16))) PpbLds lds;
+  const int TWb = (A.W + 15) >> 4, blk = xcd_block(blockIdx.x, TWb * ((A.H + 15) >> 4));
+  if (T16) {
+    ppb_block<true>(A, lds, blk, A.rad[blk]);
+    return;
+  }
+  // lanes of a tile that lies partly outside the image have its radius too
+  // (they carry the inner ones' last texels in pass 2); those of no tile, the
+  // first lane's
+  const int lane = threadIdx.x & 63;
+  const int ti = ppb_tile(A, (blk % TWb) * 16 + (lane & 15), (blk / TWb) * 16 + (lane >> 4) * 4);
+  float R = ti >= 0 ? A.rad[ti] : 0.f;
+  const float R0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(R)));
+  if (ti < 0) R = R0;
+  if (__builtin_amdgcn_ballot_w64(R != R0) == 0ull)
+    ppb_block<true>(A, lds, blk, R0);
+  else
+    ppb_block<false>(A, lds, blk, R);
 }
 
 // block partials summed in a fixed order (deterministic), in double
@@ -1612,28 +1883,25 @@ hdof_status launch_ppc_backward(hdof_ctx* ctx, const float* color, const float* 
   if ((s = hdof_ensure(ctx->pp_tile, sizeof(float) * (size_t)TW * TH)) != HDOF_OK) return s;
   if ((s = hdof_ensure(ctx->pp_rad, sizeof(float) * (size_t)TW * TH)) != HDOF_OK) return s;
   if ((s = hdof_ensure(ctx->pp_taps, sizeof(float4) * 256)) != HDOF_OK) return s;
+  if ((s = hdof_ensure(ctx->ppb_coc, sizeof(float) * N)) != HDOF_OK) return s;
   if ((s = hdof_ensure(ctx->ppb_args, sizeof(int) * 2 * (size_t)TW * TH)) != HDOF_OK) return s;
   if ((s = hdof_ensure(ctx->ppb_partial, sizeof(float2) * (size_t)nblk)) != HDOF_OK) return s;
   pp_taps_ensure(ctx, pp.n_taps, l, st);
   int* tile_arg = (int*)ctx->ppb_args.p;
   int* rad_arg = tile_arg + (size_t)TW * TH;
   hipLaunchKernelGGL(k_ppb_pack, dim3(nblk), dim3(256), 0, st, color, depth, k, l, t, (float4*)ctx->pp_pack.p,
-                     (float*)ctx->pp_tile.p, tile_arg);
+                     (float*)ctx->ppb_coc.p, (float*)ctx->pp_tile.p, tile_arg);
   hipLaunchKernelGGL(k_ppb_dilate, dim3(cdiv(TW, 64), TH), dim3(64), 0, st, (const float*)ctx->pp_tile.p,
                      (const int*)tile_arg, TW, TH, K, pp.r_cap, (float*)ctx->pp_rad.p, rad_arg);
   hipLaunchKernelGGL(k_fill_f, dim3(cdiv(3 * (long)N, 256)), dim3(256), 0, st, grad_color, 3 * N, 0.0f);
+  const PpbArgs A{(const float4*)ctx->pp_pack.p, (const float*)ctx->ppb_coc.p, (const float*)ctx->pp_rad.p, rad_arg,
+                  (const float4*)ctx->pp_taps.p, pp.n_taps, W, H, t, 1.0f / pp.bg_ramp_px, l, k.spx, spp, rt.c_near,
+                  rt.c_far, rt.hit_ratio, 1.0f / cp.h_t, cp.rt_override, grad_out, grad_color,
+                  (float2*)ctx->ppb_partial.p};
   if (t == 16)
-    hipLaunchKernelGGL(k_ppc_backward<true>, dim3(nblk), dim3(256), 0, st, (const float4*)ctx->pp_pack.p,
-                       (const float*)ctx->pp_rad.p, (const int*)rad_arg, (const float4*)ctx->pp_taps.p, pp.n_taps,
-                       W, H, t, 1.0f / pp.bg_ramp_px, l, k.spx, spp, (const float*)rt.c_near,
-                       (const float*)rt.c_far, (const float*)rt.hit_ratio, 1.0f / cp.h_t, cp.rt_override,
-                       grad_out, grad_color, (float2*)ctx->ppb_partial.p);
+    hipLaunchKernelGGL(k_ppc_backward<true>, dim3(nblk), dim3(256), 0, st, A);
   else
-    hipLaunchKernelGGL(k_ppc_backward<false>, dim3(nblk), dim3(256), 0, st, (const float4*)ctx->pp_pack.p,
-                       (const float*)ctx->pp_rad.p, (const int*)rad_arg, (const float4*)ctx->pp_taps.p, pp.n_taps,
-                       W, H, t, 1.0f / pp.bg_ramp_px, l, k.spx, spp, (const float*)rt.c_near,
-                       (const float*)rt.c_far, (const float*)rt.hit_ratio, 1.0f / cp.h_t, cp.rt_override,
-                       grad_out, grad_color, (float2*)ctx->ppb_partial.p);
+    hipLaunchKernelGGL(k_ppc_backward<false>, dim3(nblk), dim3(256), 0, st, A);
   hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, st, (const float2*)ctx->ppb_partial.p, nblk,
                      grad_lens);
   HDOF_HIP(hipGetLastError());
