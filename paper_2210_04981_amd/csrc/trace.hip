@@ -513,22 +513,63 @@ __global__ __launch_bounds__(256) void k_gbuffer(const float4* __restrict__ node
                              depth, normal, alb_out, color, tri_id, flags, counters, pack, tile_r);
 }
 
+// Writes the queue entries of a wave's 64 pixels, consecutive from p - lane
+// (s entries holding p from o on; those outside [0, cap) dropped).  Called by
+// whole waves; `own` is the wave's.  The pixels' entries follow one another
+// in the queue (row-major offsets), so the lanes note their pixel's entries
+// in LDS and the wave writes them lane by entry: by the pixels' lanes, each
+// store touched a line per lane, s times over.  Bound: memory.  8.3M entries
+// of 16 per pixel: 40 -> 10 us.  Pixels whose entries do not follow one
+// another (offsets of a caller's own), or too few to share, write their own.
+// (Not for frames and batches, whose few traced pixels it gained nothing.)
+#define QW_N 512
+__device__ inline void queue_write(uint8_t* own, int s, long o, int p, long cap, int* __restrict__ queue) {
+  const int lane = threadIdx.x & 63;
+  const unsigned long long am = __builtin_amdgcn_ballot_w64(s > 0);
+  if (am == 0ull) return;
+  const int first = __ffsll(am) - 1;
+  const long o0 = (long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(o >> 32), first) << 32) |
+                         (unsigned)__builtin_amdgcn_readlane((int)o, first));
+  // each lane's entries start where the lanes' before it end
+  int before = s;
+  for (int i = 1; i < 64; i <<= 1) {
+    const int n = __shfl_up(before, i);
+    if (lane >= i) before += n;
+  }
+  const int n = __builtin_amdgcn_readlane(before, 63);
+  before -= s;
+  if (n < 128 || __builtin_amdgcn_ballot_w64(s > 0 && o != o0 + before) != 0ull) {
+    for (int j = 0; j < s; ++j)
+      if (o + j >= 0 && o + j < cap) queue[o + j] = p;
+    return;
+  }
+  for (int c = 0; c < n; c += QW_N) {
+    const int j1 = min(s, c + QW_N - before);
+    for (int j = max(0, c - before); j < j1; ++j) own[before + j - c] = (uint8_t)lane;
+    wave_order();
+    for (int i = lane; i < QW_N && c + i < n; i += 64) {
+      const long e = o0 + c + i;
+      if (e >= 0 && e < cap) queue[e] = p - lane + own[i];
+    }
+    wave_order();
+  }
+}
+
 // queue entries: pixel index repeated spp times at its offset; also resets
 // the persistent trace's work counters (same stream, runs before the trace).
 // Batched: offsets are view-local, *ebase is the view's first queue entry
 // and the stored index is the pixel's position in the batch (pxbase + p).
 // Entries outside [0, cap) are dropped: inconsistent offsets never write out
 // of bounds.
-__global__ void k_queue_fill(const uint8_t* __restrict__ spp, const int* __restrict__ offsets, int N,
-                             const int* __restrict__ ebase, int pxbase, long cap, int* __restrict__ queue,
-                             int* __restrict__ counter) {
-  int p = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_queue_fill(const uint8_t* __restrict__ spp, const int* __restrict__ offsets,
+                                                    int N, const int* __restrict__ ebase, int pxbase, long cap,
+                                                    int* __restrict__ queue, int* __restrict__ counter) {
+  __shared__ uint8_t own[4][QW_N];
+  const int p = blockIdx.x * 256 + threadIdx.x;
   if (p < 8 * HDOF_SEG_STRIDE) counter[p] = 0;
-  if (p >= N) return;
-  int s = spp[p];
-  long o = (long)offsets[p] + (ebase ? *ebase : 0);
-  for (int j = 0; j < s; ++j)
-    if (o + j >= 0 && o + j < cap) queue[o + j] = pxbase + p;
+  const int s = p < N ? spp[p] : 0;
+  const long o = s > 0 ? (long)offsets[p] + (ebase ? *ebase : 0) : 0;
+  queue_write(own[threadIdx.x >> 6], s, o, pxbase + p, cap, queue);
 }
 
 // Persistent trace.  The queue is cut into `segments` contiguous segments
@@ -956,86 +997,198 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
   }
 }
 
+// A ray's terms in its pixel's sums (om: its lens sample's weight, 1 without
+// spherical aberration; w: the share of the near plane) and the sums.
+struct RtRay {
+  float R, G, B, c, w, om;
+  float pw;  // FARPOS: the far share of a ray that hit, at the point P
+  V3 P;
+};
+
+struct RtSums {
+  float Nw = 0.f, Fw = 0.f, Sw = 0.f, scn = 0.f, scf = 0.f;
+  float snr = 0.f, sng = 0.f, snb = 0.f, sfr = 0.f, sfg = 0.f, sfb = 0.f, sy = 0.f, sy2 = 0.f;
+  float Pw = 0.f, px = 0.f, py = 0.f, pz = 0.f;
+  template <bool FARPOS>
+  __device__ __forceinline__ void add(const RtRay& q) {
+    const float wf = q.om - q.w;
+    if (FARPOS) {
+      Pw += q.pw;
+      px = fmaf(q.pw, q.P.x, px);
+      py = fmaf(q.pw, q.P.y, py);
+      pz = fmaf(q.pw, q.P.z, pz);
+    }
+    Sw += q.om;
+    Nw += q.w;
+    Fw += wf;
+    scn = fmaf(q.w, fabsf(q.c), scn);
+    scf = fmaf(wf, fabsf(q.c), scf);
+    snr = fmaf(q.w, q.R, snr);
+    sng = fmaf(q.w, q.G, sng);
+    snb = fmaf(q.w, q.B, snb);
+    sfr = fmaf(wf, q.R, sfr);
+    sfg = fmaf(wf, q.G, sfg);
+    sfb = fmaf(wf, q.B, sfb);
+    const float Y = fmaf(0.2126f, q.R, fmaf(0.7152f, q.G, 0.0722f * q.B));
+    sy = fmaf(q.om, Y, sy);
+    sy2 = fmaf(q.om * Y, Y, sy2);
+  }
+};
+
+struct RtIn {
+  const float *ray_col, *ray_z;
+  size_t cap;
+  LensK l;
+  CamK k;
+  uint32_t seed, frame, view;
+};
+
+// the share of the near plane of a ray with CoC c
+__device__ __forceinline__ float rt_near(float c) { return clamp01(fmaf(-c, 0.35355339059327376f, 0.5f)); }
+
+__device__ __forceinline__ float4 rt_load(const RtIn& A, size_t e) {
+  return make_float4(A.ray_col[e], A.ray_col[A.cap + e], A.ray_col[2 * A.cap + e], A.ray_z[e]);
+}
+
+// An entry (colour and depth), the j-th ray of pixel p.  RAYS (FARPOS, or
+// spherical aberration): the ray is regenerated from its counters (t = z /
+// S1, since the direction's forward component is S1).
+template <bool FARPOS, bool RAYS>
+__device__ __forceinline__ RtRay rt_ray(const RtIn& A, const float4& in, int p, int j) {
+  RtRay q;
+  q.R = in.x;
+  q.G = in.y;
+  q.B = in.z;
+  const float z = in.w;
+  q.c = coc_px(A.l, z);
+  q.om = 1.0f;
+  V3 O, D;
+  if (RAYS)
+    lens_ray(A.k, A.l, p % A.k.W, p / A.k.W, (uint32_t)j, A.view, A.seed, A.frame, O, D, &q.om);
+  q.w = q.om * rt_near(q.c);
+  q.pw = 0.f;
+  q.P = V3{0.f, 0.f, 0.f};
+  if (FARPOS && z < HDOF_ZMAX) {
+    const float t = z * A.l.invS1;
+    q.pw = q.om - q.w;
+    q.P = V3{fmaf(t, D.x, O.x), fmaf(t, D.y, O.y), fmaf(t, D.z, O.z)};
+  }
+  return q;
+}
+
+// One wave's staged entries (colour and CoC, structure of arrays, index i at
+// i + i / 64: pixels of 4, 8 or 16 entries then read from different banks).
+#define RTS_T 64
+#define RTS_N 256  // (128: trace and reduction of 8.3M rays 12 us slower)
+#define RTS_AT(i) ((i) + ((i) >> 6))
+struct RtStage {
+  float v[4][RTS_AT(RTS_N)];
+};
+
+// The sums of the wave's 64 pixels p (consecutive, one per lane; s entries
+// from o on, all inside the queue).  STAGE: their entries lie together in the
+// queue (row-major offsets), so the wave reads them lane by entry and the
+// pixels' lanes add them up from LDS in the order of their rays: read by the
+// pixels' lanes, every load touches a line per lane, s times over.  Bound:
+// memory.  8.3M rays of every pixel of 960x540: 243 -> 27 us (133 MB of
+// entries, 19 MB of planes).  A pixel's lane reads its own entries where a
+// wave has fewer than RTS_T and where they are spread over more than 64
+// pixels can have (offsets of a caller's own).  Not staged: frames and
+// batches, whose reduction runs beside the post-filter's gather (the kernel
+// alone 313 -> 236 us for sixteen views and 38 -> 36 for a 1080p frame, but
+// the whole calls 7.31 -> 7.34 ms and 692 -> 697 us: the gather keeps the LDS
+// and sets the pace), and regenerated rays (RAYS: their arithmetic is the
+// larger part; staged per entry 106 -> 137 us for 4.7M rays).
+template <bool FARPOS, bool RAYS, bool STAGE>
+__device__ __forceinline__ RtSums rt_sums(RtStage* S, const RtIn& A, int p, int s, long o) {
+  RtSums t;
+  const unsigned long long am = __builtin_amdgcn_ballot_w64(s > 0);
+  if (am == 0ull) return t;
+  const int lane = threadIdx.x & 63, first = __ffsll(am) - 1;
+  const long o0 = (long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(o >> 32), first) << 32) |
+                         (unsigned)__builtin_amdgcn_readlane((int)o, first));
+  const long rel = s > 0 ? o - o0 : 0;
+  int lo = 0, hi = -1;
+  if (STAGE && __builtin_amdgcn_ballot_w64(rel > (1l << 24) || rel < -(1l << 24)) == 0ull) {
+    lo = s > 0 ? (int)rel : 0x7fffffff;
+    hi = s > 0 ? (int)rel + s : -0x7fffffff;
+    for (int i = 32; i > 0; i >>= 1) {
+      lo = min(lo, __shfl_xor(lo, i));
+      hi = max(hi, __shfl_xor(hi, i));
+    }
+  }
+  if (hi - lo > 64 * 255 || hi - lo < RTS_T) {
+    for (int j = 0; j < s; ++j) t.add<FARPOS>(rt_ray<FARPOS, RAYS>(A, rt_load(A, (size_t)(o + j)), p, j));
+    return t;
+  }
+  const int d = (int)rel;
+  for (int c = lo; c < hi; c += RTS_N) {
+    float4 in[RTS_N / 64];  // all of a chunk's loads before their use
+#pragma unroll
+    for (int b = 0; b < RTS_N / 64; ++b) in[b] = rt_load(A, (size_t)(o0 + min(c + b * 64 + lane, hi - 1)));
+#pragma unroll
+    for (int b = 0; b < RTS_N / 64; ++b) {
+      const int at = RTS_AT(b * 64 + lane);
+      S->v[0][at] = in[b].x;
+      S->v[1][at] = in[b].y;
+      S->v[2][at] = in[b].z;
+      S->v[3][at] = coc_px(A.l, in[b].w);
+    }
+    wave_order();
+    const int j0 = max(0, c - d), j1 = min(s, c + RTS_N - d);  // this lane's entries of the chunk
+    for (int j = j0; j < j1; ++j) {
+      const int at = RTS_AT(d + j - c);
+      const float c = S->v[3][at];
+      t.add<FARPOS>(RtRay{S->v[0][at], S->v[1][at], S->v[2][at], c, rt_near(c), 1.0f, 0.f, V3{0.f, 0.f, 0.f}});
+    }
+    wave_order();
+  }
+  return t;
+}
+
 // per-pixel near/far split, hit ratio and luminance moments, fixed order;
 // batched: *ebase is the view's first queue entry
 // FARPOS: also the far-weighted mean hit point of the pixel's rays that hit
-// (their rays regenerated from the same counters; t = z / S1 since the
-// direction's forward component is S1) and its weight, 4 planes.
+// and its weight, 4 planes.
 // VAR (whole frames): the variance history update of the pixel as well,
 // from the moments just formed.
 // coc_nf (nullable, 2 planes): the average CoC size of the near rays and of
 // the far rays, sum w |c| / sum w and sum (1 - w) |c| / sum (1 - w).
-template <bool FARPOS, bool VAR>
-__device__ __forceinline__ void rt_reduce_px(int p, const uint8_t* __restrict__ spp, const int* __restrict__ offsets,
-                                             int N, const int* __restrict__ ebase, const float* __restrict__ ray_col,
-                                             const float* __restrict__ ray_z, size_t cap, const LensK& l,
-                                             float* __restrict__ cn, float* __restrict__ cf, float* __restrict__ h,
-                                             float* __restrict__ m1, float* __restrict__ m2, const CamK& k,
-                                             uint32_t seed, uint32_t frame, uint32_t view,
-                                             float* __restrict__ far_pos, const VarFuse& vf,
+// Called by whole waves, the lanes' pixels consecutive; p >= N: none.
+template <bool FARPOS, bool VAR, bool RAYS, bool STAGE>
+__device__ __forceinline__ void rt_reduce_px(RtStage* S, const RtIn& A, int p,
+                                             const uint8_t* __restrict__ spp, const int* __restrict__ offsets, int N,
+                                             const int* __restrict__ ebase, float* __restrict__ cn,
+                                             float* __restrict__ cf, float* __restrict__ h, float* __restrict__ m1,
+                                             float* __restrict__ m2, float* __restrict__ far_pos, const VarFuse& vf,
                                              float* __restrict__ coc_nf) {
-  int s = spp[p];
-  float Nw = 0.f, Fw = 0.f, snr = 0.f, sng = 0.f, snb = 0.f, sfr = 0.f, sfg = 0.f, sfb = 0.f, sy = 0.f, sy2 = 0.f;
-  float Pw = 0.f, spx_ = 0.f, spy_ = 0.f, spz_ = 0.f, scn = 0.f, scf = 0.f;
+  const bool px = p < N;
+  const int sp = px ? spp[p] : 0;
+  int s = sp;
   // untraced pixels (most of them) do not read their offset
   const long o = s > 0 ? (long)offsets[p] + (ebase ? *ebase : 0) : 0;
-  if (o < 0 || o + s > (long)cap) s = 0;  // inconsistent offsets: nothing was traced here
-  // spherical aberration: every ray weighs its lens sample's weight (the
-  // sample regenerated from its counters); 1 for sa = 0
-  const bool weighted = l.sa != 0.0f;
-  float Sw = 0.f;
-  if (s > 0) {
-    for (int j = 0; j < s; ++j) {
-      long e = o + j;
-      float R = ray_col[e], G = ray_col[cap + e], B = ray_col[2 * cap + e];
-      const float zj = ray_z[e];
-      float c = coc_px(l, zj);
-      float om = 1.0f;
-      V3 O, D;
-      if (FARPOS || weighted) lens_ray(k, l, p % k.W, p / k.W, (uint32_t)j, view, seed, frame, O, D, &om);
-      float w = om * clamp01(fmaf(-c, 0.35355339059327376f, 0.5f));
-      float wf = om - w;
-      if (FARPOS && zj < HDOF_ZMAX) {
-        const float t = zj * l.invS1;
-        Pw += wf;
-        spx_ = fmaf(wf, fmaf(t, D.x, O.x), spx_);
-        spy_ = fmaf(wf, fmaf(t, D.y, O.y), spy_);
-        spz_ = fmaf(wf, fmaf(t, D.z, O.z), spz_);
-      }
-      Sw += om;
-      Nw += w;
-      Fw += wf;
-      scn = fmaf(w, fabsf(c), scn);
-      scf = fmaf(wf, fabsf(c), scf);
-      snr = fmaf(w, R, snr);
-      sng = fmaf(w, G, sng);
-      snb = fmaf(w, B, snb);
-      sfr = fmaf(wf, R, sfr);
-      sfg = fmaf(wf, G, sfg);
-      sfb = fmaf(wf, B, sfb);
-      float Y = fmaf(0.2126f, R, fmaf(0.7152f, G, 0.0722f * B));
-      sy = fmaf(om, Y, sy);
-      sy2 = fmaf(om * Y, Y, sy2);
-    }
-  }
+  if (o < 0 || o + s > (long)A.cap) s = 0;  // inconsistent offsets: nothing was traced here
+  const RtSums t = rt_sums<FARPOS, RAYS, STAGE>(S, A, p, s, o);
+  if (!px) return;
+  const float Nw = t.Nw, Fw = t.Fw, Sw = t.Sw;
   const float in_ = Nw > 0.f ? 1.0f / Nw : 0.f, if_ = Fw > 0.f ? 1.0f / Fw : 0.f;
   const float is = Sw > 0.f ? 1.0f / Sw : 0.f;
-  const float ybar = sy * is, y2bar = sy2 * is;
-  if (!vf.sparse_rt || spp[p] > 0) {
-    cn[p] = snr * in_;
-    cn[N + p] = sng * in_;
-    cn[2 * (size_t)N + p] = snb * in_;
-    cf[p] = sfr * if_;
-    cf[N + p] = sfg * if_;
-    cf[2 * (size_t)N + p] = sfb * if_;
+  const float ybar = t.sy * is, y2bar = t.sy2 * is;
+  if (!vf.sparse_rt || sp > 0) {
+    cn[p] = t.snr * in_;
+    cn[N + p] = t.sng * in_;
+    cn[2 * (size_t)N + p] = t.snb * in_;
+    cf[p] = t.sfr * if_;
+    cf[N + p] = t.sfg * if_;
+    cf[2 * (size_t)N + p] = t.sfb * if_;
     h[p] = Nw * is;
     m1[p] = ybar;
     m2[p] = y2bar;
   }
-  if (VAR && !(vf.in_place && spp[p] == 0)) {  // in place: an untraced pixel's history is already there
+  if (VAR && !(vf.in_place && sp == 0)) {  // in place: an untraced pixel's history is already there
     float a1 = vf.rm1[p], a2 = vf.rm2[p];
     uint8_t f = vf.rfl[p];
-    if (spp[p] > 0) {
+    if (sp > 0) {
       if (f & HDOF_HIST_VALID) {
         a1 = fmaf(vf.alpha, ybar, (1.0f - vf.alpha) * a1);
         a2 = fmaf(vf.alpha, y2bar, (1.0f - vf.alpha) * a2);
@@ -1052,29 +1205,30 @@ __device__ __forceinline__ void rt_reduce_px(int p, const uint8_t* __restrict__ 
     if (!vf.in_place) vf.hz[p] = vf.depth[p];
   }
   if (FARPOS) {
-    const float ip = Pw > 0.f ? 1.0f / Pw : 0.f;
-    far_pos[p] = spx_ * ip;
-    far_pos[N + p] = spy_ * ip;
-    far_pos[2 * (size_t)N + p] = spz_ * ip;
-    far_pos[3 * (size_t)N + p] = Pw;
+    const float ip = t.Pw > 0.f ? 1.0f / t.Pw : 0.f;
+    far_pos[p] = t.px * ip;
+    far_pos[N + p] = t.py * ip;
+    far_pos[2 * (size_t)N + p] = t.pz * ip;
+    far_pos[3 * (size_t)N + p] = t.Pw;
   }
   if (coc_nf) {
-    coc_nf[p] = scn * in_;
-    coc_nf[N + p] = scf * if_;
+    coc_nf[p] = t.scn * in_;
+    coc_nf[N + p] = t.scf * if_;
   }
 }
 
-template <bool FARPOS, bool VAR>
-__global__ void k_rt_reduce(const uint8_t* __restrict__ spp, const int* __restrict__ offsets, int N,
-                            const int* __restrict__ ebase, const float* __restrict__ ray_col,
-                            const float* __restrict__ ray_z, size_t cap, LensK l, float* __restrict__ cn,
-                            float* __restrict__ cf, float* __restrict__ h, float* __restrict__ m1,
-                            float* __restrict__ m2, CamK k, uint32_t seed, uint32_t frame, uint32_t view,
-                            float* __restrict__ far_pos, VarFuse vf, float* __restrict__ coc_nf) {
-  int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  rt_reduce_px<FARPOS, VAR>(p, spp, offsets, N, ebase, ray_col, ray_z, cap, l, cn, cf, h, m1, m2, k, seed, frame,
-                            view, far_pos, vf, coc_nf);
+template <bool FARPOS, bool VAR, bool RAYS>
+__global__ __launch_bounds__(256) void k_rt_reduce(RtIn A, const uint8_t* __restrict__ spp,
+                                                   const int* __restrict__ offsets, int N,
+                                                   const int* __restrict__ ebase, float* __restrict__ cn,
+                                                   float* __restrict__ cf, float* __restrict__ h,
+                                                   float* __restrict__ m1, float* __restrict__ m2,
+                                                   float* __restrict__ far_pos, VarFuse vf,
+                                                   float* __restrict__ coc_nf) {
+  constexpr bool STAGE = !RAYS && !VAR;
+  __shared__ RtStage stage[STAGE ? 4 : 1];
+  rt_reduce_px<FARPOS, VAR, RAYS, STAGE>(stage + (STAGE ? threadIdx.x >> 6 : 0), A, blockIdx.x * 256 + threadIdx.x, spp, offsets, N, ebase, cn,
+                            cf, h, m1, m2, far_pos, vf, coc_nf);
 }
 
 // The batched form's queue fill and reduction, one launch each over every
@@ -1108,26 +1262,26 @@ __global__ void k_queue_fill_batch(const uint8_t* __restrict__ spp, const int* _
 
 // the trace planes are written at traced pixels only (the composite reads
 // them nowhere else)
-__global__ void k_rt_reduce_batch(const uint8_t* __restrict__ spp, const int* __restrict__ offsets,
-                                  const ViewK* __restrict__ views, PxBatch b, const int* __restrict__ ebase,
-                                  const float* __restrict__ ray_col, const float* __restrict__ ray_z, size_t cap,
-                                  float* __restrict__ cn, float* __restrict__ cf, float* __restrict__ h,
-                                  float* __restrict__ m1, float* __restrict__ m2) {
+__global__ __launch_bounds__(256) void k_rt_reduce_batch(const uint8_t* __restrict__ spp,
+                                                         const int* __restrict__ offsets,
+                                                         const ViewK* __restrict__ views, PxBatch b,
+                                                         const int* __restrict__ ebase,
+                                                         const float* __restrict__ ray_col,
+                                                         const float* __restrict__ ray_z, size_t cap,
+                                                         float* __restrict__ cn, float* __restrict__ cf,
+                                                         float* __restrict__ h, float* __restrict__ m1,
+                                                         float* __restrict__ m2) {
   const int v = batch_view_of(b.blk_base, b.n, blockIdx.x);
   const int N = views[v].k.W * views[v].k.H;
   const size_t pb = (size_t)views[v].px_base;
-  const LensK l = views[v].l;
-  const CamK k = views[v].k;
+  // (the rays' lens weights are not regenerated here: sa = 0)
+  const RtIn A{ray_col, ray_z, cap, views[v].l, views[v].k, 0u, 0u, 0u};
   VarFuse vf{};
   vf.sparse_rt = 1;
   const int p0 = (blockIdx.x - b.blk_base[v]) * HDOF_BATCH_PX_BLOCK;
-  for (int i = threadIdx.x; i < HDOF_BATCH_PX_BLOCK; i += blockDim.x) {
-    const int p = p0 + i;
-    if (p >= N) break;
-    if (spp[pb + p] == 0) continue;  // the planes are written at traced pixels only
-    rt_reduce_px<false, false>(p, spp + pb, offsets + pb, N, ebase + v, ray_col, ray_z, cap, l, cn + 3 * pb,
-                               cf + 3 * pb, h + pb, m1 + pb, m2 + pb, k, 0u, 0u, 0u, nullptr, vf, nullptr);
-  }
+  for (int i = threadIdx.x; i < HDOF_BATCH_PX_BLOCK; i += 256)
+    rt_reduce_px<false, false, false, false>(nullptr, A, p0 + i, spp + pb, offsets + pb, N, ebase + v, cn + 3 * pb,
+                               cf + 3 * pb, h + pb, m1 + pb, m2 + pb, nullptr, vf, nullptr);
 }
 
 // batch: first queue entry of each view and the batch total
@@ -1261,11 +1415,13 @@ hdof_status launch_trace(hdof_ctx* ctx, const hdof_scene* sc, const CamK& k, con
   launch_trace_kernel<false>(ctx, A, st);
   hdof_prof_mark(ctx, 4, st);
   const VarFuse vz = vf ? *vf : VarFuse{};
-  auto kern = far_pos ? (vf ? k_rt_reduce<true, true> : k_rt_reduce<true, false>)
-                      : (vf ? k_rt_reduce<false, true> : k_rt_reduce<false, false>);
-  hipLaunchKernelGGL(kern, dim3(cdiv(N, 256)), dim3(256), 0, st, spp, offsets, N, (const int*)nullptr,
-                     (const float*)ctx->ray_col.p, (const float*)rz, cap, l, out.c_near, out.c_far, out.hit_ratio,
-                     out.lum_m1, out.lum_m2, k, seed, frame, view, far_pos, vz, coc_nf);
+  const bool rays = l.sa != 0.0f;
+  auto kern = far_pos ? (vf ? k_rt_reduce<true, true, true> : k_rt_reduce<true, false, true>)
+              : rays  ? (vf ? k_rt_reduce<false, true, true> : k_rt_reduce<false, false, true>)
+                      : (vf ? k_rt_reduce<false, true, false> : k_rt_reduce<false, false, false>);
+  const RtIn R{(const float*)ctx->ray_col.p, rz, cap, l, k, seed, frame, view};
+  hipLaunchKernelGGL(kern, dim3(cdiv(N, 256)), dim3(256), 0, st, R, spp, offsets, N, (const int*)nullptr, out.c_near,
+                     out.c_far, out.hit_ratio, out.lum_m1, out.lum_m2, far_pos, vz, coc_nf);
   if (!vf) hdof_prof_mark(ctx, 5, st);  // fused: the variance update stage is part of this one
   HDOF_HIP(hipGetLastError());
   return HDOF_OK;

@@ -120,3 +120,36 @@ def test_deep_stacks(hd, ctx, n):
     cfg = sg.config_tiny(aperture_override=0.2)
     cam = replace(cfg.camera, width=16, height=16)
     check_hits(hd, ctx, scene, replace(cfg, camera=cam), np.full((16, 16), 3, np.int32), 1e-3)
+
+
+@pytest.mark.parametrize("smax,sa", [(1, 0.0), (3, 0.4), (16, 0.0), (255, 0.0)])
+def test_reduction_any_entry_order(hd, ctx, smax, sa):
+    """The reduction stages a wave's entries together where its pixels' lie
+    together, else each lane reads its own: the same sums bit for bit for
+    offsets in row-major order, in reverse (each wave's together, descending),
+    column by column and in random order (spread over the queue, a lane per
+    pixel), the last being the plain sum."""
+    print_case(f"reduction smax {smax} sa {sa}")
+    cfg = sg.config_tiny(aperture_override=0.2)
+    W, H = (147, 131) if smax < 255 else (65, 7)
+    cfg = replace(cfg, camera=replace(cfg.camera, width=W, height=H), lens=replace(cfg.lens, sa=sa))
+    rng = np.random.default_rng(smax)
+    spp = rng.integers(0, smax + 1, H * W)
+    spp[rng.uniform(size=H * W) < 0.4] = 0
+    sc = upload_scene(hd, ctx, sg.tiny_scene(3))
+    orders = [np.arange(H * W), np.arange(H * W)[::-1], np.arange(H * W).reshape(H, W).T.ravel(),
+              rng.permutation(H * W)]
+    out = []
+    for order in orders:
+        off = np.zeros(H * W, np.int64)
+        off[order] = np.cumsum(spp[order]) - spp[order]
+        rt = hd.hdof_trace_thin_lens(ctx, sc, hd.camera_of(cfg.camera), hd.lens_of(cfg.lens), hd.light_of(cfg.light),
+                                     smax, to_dev(spp.reshape(H, W).astype(np.uint8)),
+                                     to_dev(off.reshape(H, W).astype(np.int32)),
+                                     to_dev(np.array([spp.sum()], np.int32)), seed=5)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in (rt.c_near, rt.c_far, rt.hit_ratio, rt.lum_m1, rt.lum_m2)])
+    for o in out[1:]:
+        for a, b in zip(out[0], o):
+            assert np.array_equal(a, b)
+    sc.close()
