@@ -90,23 +90,62 @@ void pp_taps_ensure(hdof_ctx* ctx, int n, const LensK& l, hipStream_t st) {
   ctx->pp_taps_sa = l.sa;
 }
 
-__global__ void k_pp_dilate(const float* __restrict__ tile_r, int TW, int TH, int K, float r_cap,
-                            float* __restrict__ rad) {
-  int tx = blockIdx.x * blockDim.x + threadIdx.x, ty = blockIdx.y;
-  if (tx >= TW) return;
-  float m = 0.0f;
-  for (int dy = -K; dy <= K; ++dy) {
-    int yy = ty + dy;
-    if (yy < 0 || yy >= TH) continue;
-    for (int dx = -K; dx <= K; ++dx) {
-      int xx = tx + dx;
-      if (xx < 0 || xx >= TW) continue;
-      m = fmaxf(m, tile_r[yy * TW + xx]);
+// The largest radius within K tiles of each tile, capped; ARG: also the pixel
+// that sets it (-1 when capped or zero; the lowest of equal ones).  A block
+// makes 32x8 tiles: their neighbourhood in LDS, the maximum along the rows,
+// then along the columns, 2 (2 K + 1) reads a tile instead of (2 K + 1)^2
+// dependent ones from memory (1280x720, 8-pixel tiles, K = 8: 35 -> 5 us;
+// 1080p, 16-pixel tiles with their pixels, K = 4: 15 -> 5; the filter of
+// 333x187 pixels with 4-pixel tiles, K = 16: 139 -> 32).  More than
+// DIL_K tiles (a cap above 64 pixels on 4-pixel tiles) are read one by one.
+#define DIL_K 16
+#define DIL_W 32
+#define DIL_H 8
+template <bool ARG>
+__global__ __launch_bounds__(256) void k_pp_dilate(const float* __restrict__ tile_r, const int* __restrict__ tile_arg,
+                                                   int TW, int TH, int K, float r_cap, float* __restrict__ rad,
+                                                   int* __restrict__ rad_arg) {
+  __shared__ float in[(DIL_H + 2 * DIL_K) * (DIL_W + 2 * DIL_K)], mid[(DIL_H + 2 * DIL_K) * DIL_W];
+  __shared__ int ina[ARG ? (DIL_H + 2 * DIL_K) * (DIL_W + 2 * DIL_K) : 1], mida[ARG ? (DIL_H + 2 * DIL_K) * DIL_W : 1];
+  const int tid = threadIdx.x, lx = tid & (DIL_W - 1), ly = tid / DIL_W;
+  const int bx = blockIdx.x * DIL_W, by = blockIdx.y * DIL_H, tx = bx + lx, ty = by + ly;
+  float m = -1.0f;
+  int mi = 0x7fffffff;
+  const auto take = [&](float v, int vi) {
+    if (v > m || (ARG && v == m && vi < mi)) {
+      m = v;
+      mi = vi;
     }
+  };
+  if (K <= DIL_K) {
+    const int IW = DIL_W + 2 * K, IH = DIL_H + 2 * K;
+    for (int i = tid; i < IW * IH; i += 256) {
+      const int r = i / IW, xx = bx - K + i - r * IW, yy = by - K + r;
+      const bool in_grid = xx >= 0 && xx < TW && yy >= 0 && yy < TH;
+      in[i] = in_grid ? tile_r[yy * TW + xx] : -1.0f;
+      if (ARG) ina[i] = in_grid ? tile_arg[yy * TW + xx] : 0x7fffffff;
+    }
+    __syncthreads();
+    for (int r = ly; r < IH; r += DIL_H) {
+      m = -1.0f;
+      mi = 0x7fffffff;
+      for (int d = 0; d <= 2 * K; ++d) take(in[r * IW + lx + d], ARG ? ina[r * IW + lx + d] : 0);
+      mid[r * DIL_W + lx] = m;
+      if (ARG) mida[r * DIL_W + lx] = mi;
+    }
+    __syncthreads();
+    m = -1.0f;
+    mi = 0x7fffffff;
+    for (int d = 0; d <= 2 * K; ++d) take(mid[(ly + d) * DIL_W + lx], ARG ? mida[(ly + d) * DIL_W + lx] : 0);
+  } else if (tx < TW && ty < TH) {
+    for (int yy = max(0, ty - K); yy <= min(TH - 1, ty + K); ++yy)
+      for (int xx = max(0, tx - K); xx <= min(TW - 1, tx + K); ++xx)
+        take(tile_r[yy * TW + xx], ARG ? tile_arg[yy * TW + xx] : 0);
   }
-  rad[ty * TW + tx] = fminf(r_cap, m);
+  if (tx >= TW || ty >= TH) return;
+  rad[ty * TW + tx] = fminf(r_cap, ARG ? m : fmaxf(m, 0.0f));
+  if (ARG) rad_arg[ty * TW + tx] = (m < r_cap && m > 0.0f) ? mi : -1;
 }
-
 
 // ---------------------------------------------------------------- gather
 // Tap weights are carried in CoC-diameter units: for a tap with bilinear CoC
@@ -705,7 +744,11 @@ __global__ __launch_bounds__(256) void k_pp_gather16q_batch(const float4* __rest
 }
 
 // Tiles of 4 or 8 pixels: per-lane radius and per-lane tap geometry, every
-// texel clamped to the edge.
+// texel clamped to the edge.  Bound: the texel loads (a 64-lane load of
+// float4s at four rows' places takes a CU about 30 clocks): 48 taps, 1280x720,
+// 8-pixel tiles 90 us.  (A wave's texels staged in LDS are as many LDS reads:
+// 84, and 5 us slower on small images and 6 % on 4-pixel tiles; four pixels of
+// a column per lane, 10 texels for 16: 150, their footprints leave the L1.)
 __global__ __launch_bounds__(256) void k_pp_gather_any(const float4* __restrict__ pack, const float* __restrict__ rad,
                                                        const float4* __restrict__ taps, int n_taps, int W, int H,
                                                        int tile, float inv_ramp, float* __restrict__ out) {
@@ -977,31 +1020,6 @@ __global__ __launch_bounds__(256) void k_ppb_pack(const float* __restrict__ colo
     tile_r[(y / tile) * TW + x / tile] = m;
     tile_arg[(y / tile) * TW + x / tile] = mi;
   }
-}
-
-// dilated radius and the pixel that sets it (-1 when capped or zero)
-__global__ void k_ppb_dilate(const float* __restrict__ tile_r, const int* __restrict__ tile_arg, int TW, int TH,
-                             int K, float r_cap, float* __restrict__ rad, int* __restrict__ rad_arg) {
-  int tx = blockIdx.x * blockDim.x + threadIdx.x, ty = blockIdx.y;
-  if (tx >= TW) return;
-  float m = -1.0f;
-  int mi = 0x7fffffff;
-  for (int dy = -K; dy <= K; ++dy) {
-    int yy = ty + dy;
-    if (yy < 0 || yy >= TH) continue;
-    for (int dx = -K; dx <= K; ++dx) {
-      int xx = tx + dx;
-      if (xx < 0 || xx >= TW) continue;
-      float v = tile_r[yy * TW + xx];
-      int vi = tile_arg[yy * TW + xx];
-      if (v > m || (v == m && vi < mi)) {
-        m = v;
-        mi = vi;
-      }
-    }
-  }
-  rad[ty * TW + tx] = fminf(r_cap, m);
-  rad_arg[ty * TW + tx] = (m < r_cap && m > 0.0f) ? mi : -1;
 }
 
 __global__ void k_fill_f(float* __restrict__ p, size_t n, float v) {
@@ -1678,11 +1696,15 @@ hdof_status postfilter_run(hdof_ctx* ctx, const PPScratch& S, const float* color
     hipLaunchKernelGGL(k_pp_pack, dim3(cdiv(W, 16) * cdiv(H, 16)), dim3(256), 0, st, color, depth, k, l, t,
                        S.pack, S.tile);
   if (t != 16)
-    hipLaunchKernelGGL(k_pp_dilate, dim3(cdiv(TW, 64), TH), dim3(64), 0, st, (const float*)S.tile, TW,
-                       TH, K, pp.r_cap, S.rad);
+    hipLaunchKernelGGL(k_pp_dilate<false>, dim3(cdiv(TW, DIL_W), cdiv(TH, DIL_H)), dim3(256), 0, st,
+                       (const float*)S.tile, (const int*)nullptr, TW, TH, K, pp.r_cap, S.rad, (int*)nullptr);
   hdof_prof_mark(ctx, 8, st);
   if (t == 16) {
-    const bool sa = l.sa != 0.0f;
+    // Below four waves per SIMD the quad form (a wave per tile) leaves the
+    // chip waiting for its own loads and LDS: the four-wave form then (333x187,
+    // 252 tiles, filter alone: 46 against 21 us; 853x479: 63 / 52; 1280x720,
+    // 3600 tiles: 93 / 94; 1600x900, 5700: 130 / 135; 1080p: 157 / 178).
+    const bool sa = l.sa != 0.0f, few = TW * TH < 4096;
     FuseK fz{};
     if (fuse && fuse->untraced_only) {
       fz.out = fuse->out;
@@ -1701,20 +1723,21 @@ hdof_status postfilter_run(hdof_ctx* ctx, const PPScratch& S, const float* color
       fz = FuseK{fuse->spp, fuse->rt.c_near, fuse->rt.c_far, fuse->rt.hit_ratio, 1.0f / fuse->cp.h_t,
                  fuse->cp.rt_override, fuse->out, fuse->pps,
                  fuse->pps && fuse->cp.spec_y > 0.0f ? 1.0f / fuse->cp.spec_y : 0.0f};
-      auto kern = sa ? k_pp_gather16q<1, true> : k_pp_gather16q<1, false>;
-      hipLaunchKernelGGL(kern, dim3((TW * TH + 3) / 4), dim3(256), 0, st, (const float4*)S.pack,
+      auto kern = few ? (sa ? k_pp_gather16<1, true> : k_pp_gather16<1, false>)
+                      : (sa ? k_pp_gather16q<1, true> : k_pp_gather16q<1, false>);
+      hipLaunchKernelGGL(kern, dim3(few ? TW * TH : (TW * TH + 3) / 4), dim3(256), 0, st, (const float4*)S.pack,
                          (const float*)S.tile, K, pp.r_cap, (const float4*)S.taps, pp.n_taps, W, H,
                          1.0f / pp.bg_ramp_px, out, fz);
     } else {
-      auto kern = sa ? k_pp_gather16q<0, true> : k_pp_gather16q<0, false>;
-      hipLaunchKernelGGL(kern, dim3((TW * TH + 3) / 4), dim3(256), 0, st, (const float4*)S.pack,
+      auto kern = few ? (sa ? k_pp_gather16<0, true> : k_pp_gather16<0, false>)
+                      : (sa ? k_pp_gather16q<0, true> : k_pp_gather16q<0, false>);
+      hipLaunchKernelGGL(kern, dim3(few ? TW * TH : (TW * TH + 3) / 4), dim3(256), 0, st, (const float4*)S.pack,
                          (const float*)S.tile, K, pp.r_cap, (const float4*)S.taps, pp.n_taps, W, H,
                          1.0f / pp.bg_ramp_px, out, fz);
     }
   } else {
-    hipLaunchKernelGGL(k_pp_gather_any, dim3(cdiv(W, 16), cdiv(H, 16)), dim3(256), 0, st,
-                       (const float4*)S.pack, (const float*)S.rad,
-                       (const float4*)S.taps, pp.n_taps, W, H, t, 1.0f / pp.bg_ramp_px, out);
+    hipLaunchKernelGGL(k_pp_gather_any, dim3(cdiv(W, 16), cdiv(H, 16)), dim3(256), 0, st, (const float4*)S.pack,
+                       (const float*)S.rad, (const float4*)S.taps, pp.n_taps, W, H, t, 1.0f / pp.bg_ramp_px, out);
     if (fuse && !fuse->untraced_only) {
       HDOF_HIP(hipGetLastError());
       return launch_composite(ctx, color, out, depth, fuse->spp, fuse->rt, k, l, fuse->cp, fuse->out, st,
@@ -1891,8 +1914,8 @@ hdof_status launch_ppc_backward(hdof_ctx* ctx, const float* color, const float* 
   int* rad_arg = tile_arg + (size_t)TW * TH;
   hipLaunchKernelGGL(k_ppb_pack, dim3(nblk), dim3(256), 0, st, color, depth, k, l, t, (float4*)ctx->pp_pack.p,
                      (float*)ctx->ppb_coc.p, (float*)ctx->pp_tile.p, tile_arg);
-  hipLaunchKernelGGL(k_ppb_dilate, dim3(cdiv(TW, 64), TH), dim3(64), 0, st, (const float*)ctx->pp_tile.p,
-                     (const int*)tile_arg, TW, TH, K, pp.r_cap, (float*)ctx->pp_rad.p, rad_arg);
+  hipLaunchKernelGGL(k_pp_dilate<true>, dim3(cdiv(TW, DIL_W), cdiv(TH, DIL_H)), dim3(256), 0, st,
+                     (const float*)ctx->pp_tile.p, (const int*)tile_arg, TW, TH, K, pp.r_cap, (float*)ctx->pp_rad.p, rad_arg);
   hipLaunchKernelGGL(k_fill_f, dim3(cdiv(3 * (long)N, 256)), dim3(256), 0, st, grad_color, 3 * N, 0.0f);
   const PpbArgs A{(const float4*)ctx->pp_pack.p, (const float*)ctx->ppb_coc.p, (const float*)ctx->pp_rad.p, rad_arg,
                   (const float4*)ctx->pp_taps.p, pp.n_taps, W, H, t, 1.0f / pp.bg_ramp_px, l, k.spx, spp, rt.c_near,

@@ -299,6 +299,27 @@ def test_postfilter_matches_oracle(hd, ctx, which):
     assert err.max() < COL_TOL, (err.max(), np.unravel_index(err.argmax(), err.shape))
 
 
+@pytest.mark.parametrize("W,H,tile,r_cap", [
+    (5, 3, 4, 64.0), (124, 28, 4, 64.0), (132, 36, 4, 63.0), (128, 33, 4, 65.0), (129, 65, 8, 64.0), (257, 129, 8, 9.0),
+    (1023, 1025, 16, 64.0)])
+def test_postfilter_dilation_and_forms(hd, ctx, W, H, tile, r_cap):
+    """Tile grids around the dilation's 32x8 blocks, caps up to its 16 staged
+    tiles and past them (65 pixels on 4-pixel tiles); and enough 16-pixel
+    tiles (4160) for the form with a wave per tile, whose remainder block and
+    border tiles are partly outside."""
+    print_case(f"postfilter {W}x{H} tile {tile} cap {r_cap}")
+    cfg = sg.config_1080p(W, H)
+    z = f32(_mixed_depth(H, W, 12, W))
+    col = f32(np.random.default_rng(H).uniform(0, 1, (3, H, W)))
+    pp = sg.PPParams(n_taps=24, tile=tile, r_cap=r_cap, bg_ramp_px=1.0)
+    ref = oracle.postfilter(cfg.camera, cfg.lens, col, z, pp)
+    got = hd.hdof_postfilter(ctx, to_dev(col, torch.float32), to_dev(z, torch.float32), hd.camera_of(cfg.camera),
+                             hd.lens_of(cfg.lens), hd.pp_params_of(pp))
+    torch.cuda.synchronize()
+    err = np.abs(got.cpu().numpy() - ref)
+    assert err.max() < COL_TOL, (err.max(), np.unravel_index(err.argmax(), err.shape))
+
+
 def test_postfilter_zero_aperture_exact(hd, ctx):
     print_case("postfilter A=0")
     cfg = sg.config_tiny(aperture_override=0.0)
