@@ -775,17 +775,80 @@ __global__ __launch_bounds__(256) void k_pp_gather_any(const float4* __restrict_
   g.store(out, N, p);
 }
 
+// One wave's taps (wave, wave + 4, ...) of the specular gather for 8x8 pixels
+// of one radius R.  Per tap the pixels read the same 9x9 texels, of which
+// only the luminance and the CoC matter: the wave stages them in its own
+// two-buffer LDS ring a tap ahead; lane i forms the geometry of its i-th tap.
+#define PPS_SIDE 9
+#define PPS_TEX (PPS_SIDE * PPS_SIDE)
+template <bool INTERIOR>
+__device__ __forceinline__ void spec_taps8(float2 (*stg)[PPS_TEX], const float4* __restrict__ pack,
+                                           const float* __restrict__ ys, const float4* __restrict__ taps, int n_taps,
+                                           int wave, float R, int xw, int yw, int W, int H, int lane, GatherAcc& g) {
+  const int n = (n_taps - wave + 3) >> 2;
+  if (n <= 0) return;
+  const __amdgpu_buffer_rsrc_t rp =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float4*>(pack), (short)0, W * H * 16, HDOF_BUFFER_WORD3);
+  const __amdgpu_buffer_rsrc_t ry =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(ys), (short)0, W * H * 4, HDOF_BUFFER_WORD3);
+  int sx[2], sy[2], vo[2];  // the lane's two texels of a tap, relative to its corner
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int i = min(s * 64 + lane, PPS_TEX - 1);
+    sy[s] = i / PPS_SIDE;
+    sx[s] = i - sy[s] * PPS_SIDE;
+    vo[s] = sy[s] * W + sx[s];
+  }
+  const float4 u = taps[min(wave + 4 * lane, n_taps - 1)];
+  const float ox = R * u.x, oy = R * u.y;
+  const float fx = floorf(ox), fy = floorf(oy);
+  const float ax = ox - fx, ay = oy - fy, bx = 1.0f - ax, by = 1.0f - ay;
+  const float w00 = bx * by, w10 = ax * by, w01 = bx * ay, w11 = ax * ay, d = 0.5f - R * u.z;
+  const int gx = xw + (int)fx, gy = yw + (int)fy, corner = gy * W + gx;
+  const auto rl = [](float v, int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i)); };
+  const auto texel = [&](int s, int i) {
+    if (INTERIOR) {
+      const int c = __builtin_amdgcn_readlane(corner, i);
+      return make_float2(__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ry, vo[s] * 4, c * 4, 0)),
+                         __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rp, vo[s] * 16 + 12, c * 16, 0)));
+    }
+    const size_t q = (size_t)clampi(__builtin_amdgcn_readlane(gy, i) + sy[s], 0, H - 1) * W +
+                     clampi(__builtin_amdgcn_readlane(gx, i) + sx[s], 0, W - 1);
+    return make_float2(ys[q], pack[q].w);
+  };
+  const int at = (lane >> 3) * PPS_SIDE + (lane & 7);
+  stg[0][lane] = texel(0, 0);
+  if (lane < PPS_TEX - 64) stg[0][64 + lane] = texel(1, 0);
+  for (int k = 0; k < n; ++k) {
+    wave_lds_sync();  // tap k's texels stored; tap k - 1's reads done
+    const int kn = k + 1 < n ? k + 1 : k;
+    const float2 t0 = texel(0, kn), t1 = texel(1, kn);
+    const float2* a = stg[k & 1] + at;
+    const float2 q00 = a[0], q10 = a[1], q01 = a[PPS_SIDE], q11 = a[PPS_SIDE + 1];
+    g.tap(rl(w00, k), rl(w10, k), rl(w01, k), rl(w11, k), rl(d, k), make_float4(q00.x, 0.f, 0.f, q00.y),
+          make_float4(q10.x, 0.f, 0.f, q10.y), make_float4(q01.x, 0.f, 0.f, q01.y),
+          make_float4(q11.x, 0.f, 0.f, q11.y), rl(u.w, k));
+    float2* const o = stg[(k & 1) ^ 1];
+    o[lane] = t0;
+    if (lane < PPS_TEX - 64) o[64 + lane] = t1;
+  }
+}
+
 // The post-filtered specular luminance (the specular bokeh rule of the
 // composite): the post-filter's gather, radius, taps and weights, applied to
 // the G-buffer's specular luminance plane.  With spp given only traced
-// pixels gather (the rule reads no other), the rest are 0.  Texels are
-// fetched directly: a frame traces a few percent of its pixels.  One 8x8
-// block (a ray-mask tile) per 256 threads, four lanes per pixel splitting
-// its taps (tap j on lane j mod 4, sums joined by lane exchanges), so the
-// few traced tiles get four times the memory parallelism of a lane per
-// pixel; a block without a traced pixel writes 0 and leaves.  Blocks run in
-// launch order, round-robin over the XCDs (the traced pixels cluster along
-// a few silhouettes, which XCD-contiguous ranges would give to one XCD).
+// pixels gather (the rule reads no other), the rest are 0.  One 8x8 block (a
+// ray-mask tile) per 256 threads, a pixel per lane, the four waves splitting
+// the taps (tap j on wave j mod 4, sums joined in LDS), so the few traced
+// tiles of a frame get four times the parallelism of a lane per pixel; a
+// block without a traced pixel writes 0 and leaves.  A block of one radius
+// (tiles of 8 or 16 pixels) stages its texels (spec_taps8), else every lane
+// reads its own.  Bound: latency.  2560x1440 frame: 259 us with four lanes a
+// pixel, eight loads and their addresses per tap, 165 so (16x16 pixels per
+// block, the traced quarters one after another: 202).
+// Blocks run in launch order, round-robin over the XCDs (the traced pixels
+// cluster along a few silhouettes, which XCD-contiguous ranges would give to
+// one XCD).
 // Radius: tile 16, the dilated radius of the block's 16-pixel tile from
 // tile_r; otherwise the pixel's tile entry of the dilated radii.
 __global__ __launch_bounds__(256) void k_pp_spec(const float4* __restrict__ pack, const float* __restrict__ ys,
@@ -794,15 +857,16 @@ __global__ __launch_bounds__(256) void k_pp_spec(const float4* __restrict__ pack
                                                  const float4* __restrict__ taps, int n_taps, int W, int H,
                                                  float inv_ramp, float* __restrict__ out) {
   __shared__ float wred[4];
+  __shared__ float2 ring[4][2][PPS_TEX], sum[4][64];
   const int BW = (W + 7) >> 3;
-  const int bx = blockIdx.x % BW, by = blockIdx.x / BW;
-  const int pi = threadIdx.x >> 2, sub = threadIdx.x & 3;
-  const int x = bx * 8 + (pi & 7), y = by * 8 + (pi >> 3);
+  const int bx = blockIdx.x % BW, by = blockIdx.x / BW, xw = bx * 8, yw = by * 8;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int x = xw + (lane & 7), y = yw + (lane >> 3);
   const bool in = x < W && y < H;
   const size_t p = in ? (size_t)y * W + x : 0;
   const bool act = in && (!spp || spp[p] > 0);
-  if (!__syncthreads_or(act)) {
-    if (in && sub == 0) out[p] = 0.0f;
+  if (__builtin_amdgcn_ballot_w64(act) == 0ull) {  // (the waves have the same pixels)
+    if (in && wave == 0) out[p] = 0.0f;
     return;
   }
   float R;
@@ -810,53 +874,37 @@ __global__ __launch_bounds__(256) void k_pp_spec(const float4* __restrict__ pack
     R = block_dilated_radius(tile_r, (W + 15) >> 4, (H + 15) >> 4, bx >> 1, by >> 1, K, r_cap, wred);
   } else {
     const int TW = (W + tile - 1) / tile;
-    R = in ? rad[(y / tile) * TW + x / tile] : 0.0f;
-  }
-  if (!act) {  // the pixel's four lanes leave together
-    if (in && sub == 0) out[p] = 0.0f;
-    return;
+    R = rad[(min(y, H - 1) / tile) * TW + min(x, W - 1) / tile];
   }
   GatherAcc g;
   g.init(make_float4(ys[p], 0.0f, 0.0f, pack[p].w), R, n_taps, inv_ramp);
-  if (sub != 0) g.ar = g.ws = 0.0f;  // the centre counts once
-  // this lane's taps sub, sub + 4, ... in groups of four: a group's loads
-  // are all issued before its sums (a tap past the end accepts nothing)
-  for (int j0 = sub; j0 < n_taps; j0 += 16) {
-    float4 v[4][4];
-    float wb[4][4], d[4], om[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = min(j0 + 4 * q, n_taps - 1);
+  if (wave != 0) g.ar = g.ws = 0.0f;  // the centre counts once
+  if (tile >= 8) {
+    R = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(R)));
+    const int E = (int)ceilf(R);
+    if (xw - E - 1 >= 0 && xw + 8 + E < W && yw - E - 1 >= 0 && yw + 8 + E < H && (long long)W * H * 16 < (1ll << 31))
+      spec_taps8<true>(ring[wave], pack, ys, taps, n_taps, wave, R, xw, yw, W, H, lane, g);
+    else
+      spec_taps8<false>(ring[wave], pack, ys, taps, n_taps, wave, R, xw, yw, W, H, lane, g);
+  } else if (act) {
+    for (int j = wave; j < n_taps; j += 4) {
       const float4 u = taps[j];
-      om[q] = u.w;
       const float ox = R * u.x, oy = R * u.y;
       const float fx = floorf(ox), fy = floorf(oy);
       const float ax = ox - fx, ay = oy - fy, bxw = 1.0f - ax, byw = 1.0f - ay;
-      wb[q][0] = bxw * byw;
-      wb[q][1] = ax * byw;
-      wb[q][2] = bxw * ay;
-      wb[q][3] = ax * ay;
-      d[q] = j0 + 4 * q < n_taps ? 0.5f - R * u.z : -1e30f;
       const int xa = x + (int)fx, ya = y + (int)fy;
       const int xa_ = clampi(xa, 0, W - 1), xb_ = clampi(xa + 1, 0, W - 1);
-      const int ya_ = clampi(ya, 0, H - 1), yb_ = clampi(ya + 1, 0, H - 1);
-      const size_t i00 = (size_t)ya_ * W + xa_, i10 = (size_t)ya_ * W + xb_;
-      const size_t i01 = (size_t)yb_ * W + xa_, i11 = (size_t)yb_ * W + xb_;
-      v[q][0] = make_float4(ys[i00], 0.0f, 0.0f, pack[i00].w);
-      v[q][1] = make_float4(ys[i10], 0.0f, 0.0f, pack[i10].w);
-      v[q][2] = make_float4(ys[i01], 0.0f, 0.0f, pack[i01].w);
-      v[q][3] = make_float4(ys[i11], 0.0f, 0.0f, pack[i11].w);
+      const size_t ra = (size_t)clampi(ya, 0, H - 1) * W, rb = (size_t)clampi(ya + 1, 0, H - 1) * W;
+      const auto at = [&](size_t i) { return make_float4(ys[i], 0.0f, 0.0f, pack[i].w); };
+      g.tap(bxw * byw, ax * byw, bxw * ay, ax * ay, 0.5f - R * u.z, at(ra + xa_), at(ra + xb_), at(rb + xa_),
+            at(rb + xb_), u.w);
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      g.tap(wb[q][0], wb[q][1], wb[q][2], wb[q][3], d[q], v[q][0], v[q][1], v[q][2], v[q][3], om[q]);
   }
-  float ar = g.ar, ws = g.ws;
-  ar += __shfl_xor(ar, 1);
-  ws += __shfl_xor(ws, 1);
-  ar += __shfl_xor(ar, 2);
-  ws += __shfl_xor(ws, 2);
-  if (sub == 0) out[p] = ar / ws;
+  sum[wave][lane] = make_float2(g.ar, g.ws);
+  __syncthreads();
+  if (wave != 0 || !in) return;
+  const float2 a = sum[0][lane], b = sum[1][lane], c = sum[2][lane], d = sum[3][lane];
+  out[p] = act ? ((a.x + b.x) + (c.x + d.x)) / ((a.y + b.y) + (c.y + d.y)) : 0.0f;
 }
 
 // pps (nullable): the post-filtered specular luminance; inv_sy = 1 / spec_y

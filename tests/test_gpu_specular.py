@@ -189,3 +189,9 @@ def test_frame_with_specular_rule(hd, ctx, tile):
         hd.hdof_postfilter_composite_backward(ctx, k.gb.color, k.gb.depth, k.spp, k.rt, cam, lens, on.pp, on.comp,
                                               torch.ones(3, H, W, device=DEV), grad)
     sc.close()
+
+
+@pytest.mark.parametrize("masked", [False, True])
+def test_postfilter_specular_four_pixel_tiles(hd, ctx, masked):
+    """Tiles of 4 pixels: radii differ within a block, every lane reads its own texels."""
+    test_postfilter_specular_matches_oracle(hd, ctx, 4, masked)
