@@ -412,10 +412,18 @@ __global__ __launch_bounds__(256) void k_ploc_merge(const int* __restrict__ mate
   osz[pos] = sz;
 }
 
+// a block barrier that orders LDS accesses only: the nodes' stores stay in flight
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // The remaining rounds of at most PLOC_TAIL clusters in one block, which
 // keeps them in LDS: most rounds of a build have few clusters, and two
 // launches each would cost more than their work.  A cluster's search is
-// shared by up to eight threads once the clusters leave that many idle.
+// shared by up to eight threads once the clusters leave that many idle; the
+// barriers do not wait for the nodes' stores (127 -> 104 us).
 // Stops at one cluster, or at a round without a merge.
 #define PLOC_TAIL 1024
 __global__ __launch_bounds__(PLOC_TAIL) void k_ploc_tail(const int* __restrict__ cid, const float4* __restrict__ cbox,
@@ -474,7 +482,7 @@ __global__ __launch_bounds__(PLOC_TAIL) void k_ploc_tail(const int* __restrict__
       }
       if (i < m && sub == 0) nn[i] = bj;
     }
-    __syncthreads();
+    lds_barrier();
     int j = -1;
     if (t < m) {
       j = nn[t];
@@ -483,7 +491,7 @@ __global__ __launch_bounds__(PLOC_TAIL) void k_ploc_tail(const int* __restrict__
     const bool lead = t < m && j > t, keep = t < m && !(j >= 0 && t > j);
     const unsigned long long km = __ballot(keep), lm = __ballot(lead);
     if (lane == 0) wave_n[wave] = make_int2(__popcll(km), __popcll(lm));
-    __syncthreads();
+    lds_barrier();
     int2 before = make_int2(0, 0), all = make_int2(0, 0);
     for (int w = 0; w < PLOC_TAIL / 64; ++w) {
       const int2 c = wave_n[w];
@@ -517,7 +525,7 @@ __global__ __launch_bounds__(PLOC_TAIL) void k_ploc_tail(const int* __restrict__
     if (all.y == 0) break;
     m = all.x;
     next -= all.y;
-    __syncthreads();
+    lds_barrier();
   }
   if (t == 0) *state = make_int2(m, next);
 }
@@ -807,13 +815,16 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
   } else {
     // rounds over grids sized by the last count the host has read, as many
     // at a time as should leave PLOC_TAIL clusters (a round leaves between
-    // 0.75 and 0.82 of them on the scenes measured); one block does the rest
+    // 0.75 and 0.83 of them on the scenes measured); one block does the rest.
+    // A round too many costs 9 us, one too few a wait of the host: counting
+    // with 1 / 1.25 a round, 200k triangles built in 700 us and 600k in 1140,
+    // with 1 / 1.2 in 660 and 1050
     int m = n, cur = 0;
     while (m > 1) {
       const int nblk = cdiv(m, 256), m0 = m;
       if (m > PLOC_TAIL) {
         const int scanned = nblk > 8192;
-        const int rounds = (int)ceil(log((double)m / PLOC_TAIL) / log(1.25));
+        const int rounds = (int)ceil(log((double)m / PLOC_TAIL) / log(1.2));
         for (int r = 0; r < rounds; ++r) {
           hipLaunchKernelGGL(k_ploc_find, dim3(nblk), dim3(PLOC_FIND_THREADS), 0, st, (const float4*)cbox[cur],
                              (const int2*)(state + cur), mate, cnt);
