@@ -65,6 +65,26 @@ struct HistIn {
 
 __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
+// Two neighbouring outputs of a Gaussian pass: a from the window's first
+// 2 GR + 1 values, b from the next one on, or equal to a (step false).
+template <int GR, class At>
+__device__ __forceinline__ void blur2(const MaskK& mk, bool step, float4& a, float4& b, At at) {
+  a = b = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int t = 0; t <= 2 * GR + 1; ++t) {
+    const float4 v = at(t);
+    if (t <= 2 * GR) {
+      const float w = mk.taps[t];
+      a = make_float4(fmaf(w, v.x, a.x), fmaf(w, v.y, a.y), fmaf(w, v.z, a.z), fmaf(w, v.w, a.w));
+    }
+    if (t > 0) {
+      const float w = mk.taps[t - 1];
+      b = make_float4(fmaf(w, v.x, b.x), fmaf(w, v.y, b.y), fmaf(w, v.z, b.z), fmaf(w, v.w, b.w));
+    }
+  }
+  if (!step) b = a;
+}
+
 template <int GR>
 __device__ __forceinline__ void mask_score_block(const float* __restrict__ depth, const float* __restrict__ normal,
                                                  const CamK& k, const MaskK& mk, const HistIn& hi,
@@ -90,38 +110,26 @@ __device__ __forceinline__ void mask_score_block(const float* __restrict__ depth
     in[ly][lx] = make_float4(fminf(depth[p], HDOF_ZMAX), normal[p], normal[N + p], normal[2 * N + p]);
   }
   __syncthreads();
-  // x pass on every staged row for the 18 columns the Sobel needs; a column
-  // outside the image takes the value of the clamped column
-  for (int i = tid; i < NIN * BL; i += 256) {
-    const int ly = i / BL, ox = i - ly * BL;
-    const int lx0 = clampi(x0 - 1 + ox, 0, W - 1) - x0 + 1;
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int t = 0; t <= 2 * GR; ++t) {
-      const float4 v = in[ly][lx0 + t];
-      const float w = mk.taps[t];
-      a.x = fmaf(w, v.x, a.x);
-      a.y = fmaf(w, v.y, a.y);
-      a.z = fmaf(w, v.z, a.z);
-      a.w = fmaf(w, v.w, a.w);
-    }
+  // x pass on every staged row for the 18 columns the Sobel needs, two
+  // neighbouring ones per thread from one window of reads; a column outside
+  // the image takes the value of the clamped column (the neighbour's)
+  static_assert(BL % 2 == 0, "pairs");
+  for (int i = tid; i < NIN * (BL / 2); i += 256) {
+    const int ly = i / (BL / 2), ox = 2 * (i - ly * (BL / 2));
+    const int la = clampi(x0 - 1 + ox, 0, W - 1) - x0 + 1, lb = clampi(x0 + ox, 0, W - 1) - x0 + 1;
+    float4 a, b;
+    blur2<GR>(mk, lb != la, a, b, [&](int t) { return in[ly][min(la + t, NIN - 1)]; });
     xb[ly][ox] = a;
+    xb[ly][ox + 1] = b;
   }
   __syncthreads();
-  for (int i = tid; i < BL * BL; i += 256) {
-    const int oy = i / BL, ox = i - oy * BL;
-    const int ly0 = clampi(y0 - 1 + oy, 0, H - 1) - y0 + 1;
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int t = 0; t <= 2 * GR; ++t) {
-      const float4 v = xb[ly0 + t][ox];
-      const float w = mk.taps[t];
-      a.x = fmaf(w, v.x, a.x);
-      a.y = fmaf(w, v.y, a.y);
-      a.z = fmaf(w, v.z, a.z);
-      a.w = fmaf(w, v.w, a.w);
-    }
+  for (int i = tid; i < BL * (BL / 2); i += 256) {
+    const int oy = 2 * (i / BL), ox = i - (oy / 2) * BL;
+    const int la = clampi(y0 - 1 + oy, 0, H - 1) - y0 + 1, lb = clampi(y0 + oy, 0, H - 1) - y0 + 1;
+    float4 a, b;
+    blur2<GR>(mk, lb != la, a, b, [&](int t) { return xb[min(la + t, NIN - 1)][ox]; });
     yb[oy][ox] = a;
+    yb[oy + 1][ox] = b;
   }
   __syncthreads();
   const int tx = tid & 15, ty = tid >> 4;
