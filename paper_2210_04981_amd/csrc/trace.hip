@@ -193,8 +193,33 @@ __device__ inline void test_leaf(const Ray& r, const float4* __restrict__ tris, 
   for (int k = 0; k < cnt; ++k) tri_test(r, tris, first + k, b);
 }
 
+// Whether the ray meets the box of cnt triangles from the first on before
+// tmax (r: inv and oinv).  The half boxes of a walk are wider than a leaf's
+// own, and at the very edge of a triangle, a rounding either way, this test
+// decides whether the ray meets the triangle.
+__device__ inline bool tris_box_hit(const Ray& r, const float4* __restrict__ tris, int first, int cnt, float tmax) {
+  V3 lo = V3{INFINITY, INFINITY, INFINITY}, hi = V3{-INFINITY, -INFINITY, -INFINITY};
+  for (int k = 0; k < cnt; ++k) {
+    const float4 a = tris[3 * (first + k)], q = tris[3 * (first + k) + 1], c = tris[3 * (first + k) + 2];
+    lo = V3{fminf(lo.x, fminf(fminf(a.x, q.x), c.x)), fminf(lo.y, fminf(fminf(a.y, q.y), c.y)),
+            fminf(lo.z, fminf(fminf(a.z, q.z), c.z))};
+    hi = V3{fmaxf(hi.x, fmaxf(fmaxf(a.x, q.x), c.x)), fmaxf(hi.y, fmaxf(fmaxf(a.y, q.y), c.y)),
+            fmaxf(hi.z, fmaxf(fmaxf(a.z, q.z), c.z))};
+  }
+  float tn;
+  return box_hit(r, lo.x, hi.x, lo.y, hi.y, lo.z, hi.z, tmax, tn);
+}
+
 // this lane's bit of a wave's mask
 __device__ __forceinline__ bool lane_of(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// the lanes of a wave's mask (__popcll's 64-bit result is compared by the
+// vector ALU)
+__device__ __forceinline__ int lanes(unsigned long long m) {
+  int n;
+  asm("s_bcnt1_i32_b64 %0, %1" : "=s"(n) : "s"(m) : "scc");
+  return n;
+}
 
 // The same tests of a leaf that the whole wave visits, for the lanes of mask
 // m: the records are scalar loads, and but for two branches that the wave
@@ -253,10 +278,11 @@ struct Work {
 
 // What a wave of the persistent trace keeps in LDS: 64 ray slots (structure
 // of arrays, a slot's fields SLOT_* of a ray that waits or is walked, then
-// its hit in place of the inverse direction), the slots no lane has taken
-// yet, and the lanes' stacks (entry i of lane t at stk[i + 1][t], below it
-// TRAV_DONE; one row more takes what a full stack is written in vain).
+// its hit in place of the shear), the slots no lane has taken yet, and the
+// lanes' stacks (entry i of lane t at stk[i + 1][t], below it TRAV_DONE; one
+// row more takes what a full stack is written in vain).
 enum { SLOT_O, SLOT_D = 3, SLOT_INV = 6, SLOT_SX = 9, SLOT_SY, SLOT_AXES, SLOT_S1, SLOT_ENTRY, SLOT_DONE, SLOT_N };
+#define SLOT_HIT SLOT_SX  // of a finished ray: distance, triangle, its input index
 struct PoolLds {
   float f[SLOT_N][64];
   int list[64];
@@ -269,6 +295,16 @@ struct PoolLds {
 __device__ __forceinline__ void wave_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+}
+
+// Slot i's ray, to be walked (state 0; 2: with its leaves' boxes tested).
+__device__ __forceinline__ void slot_ray(PoolLds& L, int i, V3 O, V3 D, int state) {
+  const RayPre q = ray_pre(O, D);
+  const float f[SLOT_S1] = {O.x,     O.y,     O.z,  D.x,  D.y, D.z, q.inv.x,
+                            q.inv.y, q.inv.z, q.Sx, q.Sy, __int_as_float(q.axes)};
+#pragma unroll
+  for (int k = 0; k < SLOT_S1; ++k) L.f[k][i] = f[k];
+  L.f[SLOT_DONE][i] = __int_as_float(state);
 }
 
 __device__ __forceinline__ V3 slot_v3(const PoolLds& L, int f, int i) { return V3{L.f[f][i], L.f[f + 1][i], L.f[f + 2][i]}; }
@@ -748,8 +784,10 @@ __device__ __forceinline__ const TraceArgs* fresh_args() {
 // takes box steps while HDOF_MIN_BOX lanes have them to take, then the leaf
 // step of the lanes that wait at a leaf (until the last lane, 8 or 20:
 // 509 / 442 / 489 us).
+// (five waves per SIMD: at 98 registers the batched form had four, and its
+// batch took 7.37 ms instead of 7.27)
 template <bool COUNT, bool BATCH>
-__global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_trace(TraceArgs A) {
+__global__ __launch_bounds__(HDOF_TRACE_BLOCK, 5) void k_trace(TraceArgs A) {
   __shared__ PoolLds lds[HDOF_TRACE_BLOCK / 64];
   __shared__ int pxb[BATCH ? HDOF_MAX_VIEWS + 1 : 1];
   int spill[HDOF_SPILL_STACK];
@@ -779,37 +817,58 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
   int seg = blockIdx.x % A.segments, tried = 0;
   int next = 0, count = 0;  // the waiting slots are list[next .. count)
   // the lane's ray: its slot (-1: none), the entry to visit next (a node, or
-  // a leaf code), the stack's top (row tp / 64 of stk, row 0 its bottom), the
+  // a leaf code), the stack's top (a row of stk, row 0 its bottom), the
   // closest hit
-  int slot = -1, tp = lane;
+  // (as a byte offset from lds: the stack is addressed with no arithmetic)
+  const int tp0 = (int)((t >> 6) * sizeof(PoolLds) + offsetof(PoolLds, stk)) + 4 * lane;
+  const int tp_full = tp0 + 256 * HDOF_LDS_STACK;  // the last row's
+  const auto stk = [&](int at) -> int& { return *(int*)((char*)lds + at); };
+  int slot = -1, tp = tp0;
   unsigned cur = TRAV_DONE;
   Best b = Best{INFINITY, -1, 0x7fffffff};
+  unsigned long long strict = 0ull;  // lanes that test their leaves' boxes
   // box steps since a ray of the wave was last done, and what they are bounded by
   unsigned stall = 0;
   const unsigned stall_max = (unsigned)min(64ll * (A.n_nodes + 1ll), 0xfffffff0ll);
   Work wk{0, 0};
-  int* const stk = &L.stk[0][0];
-  stk[lane] = (int)TRAV_DONE;
+  stk(tp0) = (int)TRAV_DONE;
   for (;;) {
     const unsigned long long idle = __builtin_amdgcn_ballot_w64(slot < 0);
     const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     if (next >= count && (int)__popcll(idle) >= (drained ? 64 : refill)) {
       wave_order();
       const TraceArgs& B = *fresh_args();
-      if (held && __float_as_int(L.f[SLOT_DONE][lane]) == 1) {
-        const Best h = Best{L.f[SLOT_INV][lane], __float_as_int(L.f[SLOT_INV + 1][lane]),
-                            __float_as_int(L.f[SLOT_INV + 2][lane])};
-        store_ray(B, slot_v3(L, SLOT_O, lane), slot_v3(L, SLOT_D, lane), h, L.f[SLOT_S1][lane],
-                  __float_as_int(L.f[SLOT_ENTRY][lane]));
-        held = false;
+      bool redo = false;
+      const int state = __float_as_int(L.f[SLOT_DONE][lane]);
+      if (held && (state & 1)) {
+        const Best h = Best{L.f[SLOT_HIT][lane], __float_as_int(L.f[SLOT_HIT + 1][lane]),
+                            __float_as_int(L.f[SLOT_HIT + 2][lane])};
+        const V3 O = slot_v3(L, SLOT_O, lane), D = slot_v3(L, SLOT_D, lane);
+        // A hit on a triangle whose leaf's box the ray misses (at an edge) is
+        // none for a walk by full boxes.  A ray that misses the triangle's
+        // own box is walked again with every leaf's box tested, as full boxes
+        // do, so the hits are those of full boxes (without it 4 of 18M rays
+        // differed; the check costs the trace 1 to 2 %).
+        if (state == 1 && h.tri >= 0) {
+          Ray q;
+          q.inv = slot_v3(L, SLOT_INV, lane);
+          q.oinv = V3{-O.x * q.inv.x, -O.y * q.inv.y, -O.z * q.inv.z};
+          redo = !tris_box_hit(q, B.tris, h.tri, 1, INFINITY);
+        }
+        if (!redo) store_ray(B, O, D, h, L.f[SLOT_S1][lane], __float_as_int(L.f[SLOT_ENTRY][lane]));
+        held = redo;
       }
-      if (drained) break;
+      const bool any_redo = __builtin_amdgcn_ballot_w64(redo) != 0ull;
+      if (any_redo && redo) slot_ray(L, lane, slot_v3(L, SLOT_O, lane), slot_v3(L, SLOT_D, lane), 2);
+      if (drained && !any_redo) break;
       const unsigned long long fm = __builtin_amdgcn_ballot_w64(!held);
       int want = (int)__popcll(fm);
       const int nseg = B.segments;
       const int lo = (int)((long)total * seg / nseg), hi = (int)((long)total * (seg + 1) / nseg);
       int base = 0;
-      if (single) {
+      if (drained) {  // only rays to be walked again
+        want = 0;
+      } else if (single) {
         // the wave's only batch: its share of the segment
         const int nw = waves_of(kept, nseg, seg);
         base = lo + (int)((long)(hi - lo) * share / nw);
@@ -831,15 +890,13 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
         float S1;
         got = entry_ray<BATCH>(B, pxb, e, hi, O, D, S1);
         if (got) {
-          const RayPre q = ray_pre(O, D);
-          const float f[SLOT_N] = {O.x,  O.y,  O.z,  D.x, D.y,
-                                   D.z,  q.inv.x, q.inv.y, q.inv.z, q.Sx,
-                                   q.Sy, __int_as_float(q.axes), S1, __int_as_float(e), __int_as_float(0)};
-#pragma unroll
-          for (int i = 0; i < SLOT_N; ++i) L.f[i][lane] = f[i];
+          L.f[SLOT_S1][lane] = S1;
+          L.f[SLOT_ENTRY][lane] = __int_as_float(e);
+          slot_ray(L, lane, O, D, 0);
           held = true;
         }
       }
+      got = got || redo;
       const unsigned long long gm = __builtin_amdgcn_ballot_w64(got);
       if (got) L.list[__popcll(gm & lt_mask)] = lane;
       next = 0;
@@ -848,12 +905,14 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
     }
     if (next < count) {  // hand the waiting slots to the idle lanes
       const int i = next + (int)__popcll(idle & lt_mask);
-      if (slot < 0 && i < count) {
+      const bool fresh = slot < 0 && i < count;
+      if (fresh) {
         slot = L.list[i];
         b = Best{INFINITY, -1, 0x7fffffff};
         cur = 0;  // root
-        tp = lane;
+        tp = tp0;
       }
+      strict |= __builtin_amdgcn_ballot_w64(fresh && __float_as_int(L.f[SLOT_DONE][slot < 0 ? lane : slot]) == 2);
       next = min(count, next + (int)__popcll(idle));
     }
     const int sl = slot < 0 ? lane : slot;
@@ -866,7 +925,7 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
       for (;;) {
         const bool inner = !(cur & HDOF_LEAF_BIT);
         const unsigned long long im = __builtin_amdgcn_ballot_w64(inner);
-        if (im == 0ull || (im != busy && (int)__popcll(im) < HDOF_MIN_BOX)) break;
+        if (lanes(im) < (im == busy ? 1 : HDOF_MIN_BOX)) break;
         // each internal node is entered at most once per ray: more steps
         // than the wave's rays can take before one of them is done mean a
         // malformed tree, and the rays stop here
@@ -883,10 +942,9 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
           const char* nd = (const char*)A.hnodes + (cur << 4);
           const float4 n0 = *(const float4*)nd, n1 = *(const float4*)(nd + 16);
           const float3 n2 = *(const float3*)(nd + 32);
-          const bool deep = __builtin_amdgcn_ballot_w64(tp >= HDOF_LDS_STACK * 64) != 0ull;
-          int ti = tp;
-          if (deep) ti = min(tp, HDOF_LDS_STACK * 64 + lane);  // the lane's own column of the last row
-          unsigned top = (unsigned)stk[ti];
+          const bool deep = __builtin_amdgcn_ballot_w64(tp >= tp_full) != 0ull;
+          const int ti = min(tp, tp_full);
+          unsigned top = (unsigned)stk(ti);
           const V3 base = V3{fmaf(n0.x, sinv.x, r.oinv.x), fmaf(n0.y, sinv.y, r.oinv.y), fmaf(n0.z, sinv.z, r.oinv.z)};
           float t0, t1;
           const unsigned long long h0 = __builtin_amdgcn_ballot_w64(
@@ -899,37 +957,39 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
           const bool near0 = lane_of(h0 & (~h1 | le)), both = lane_of(h0 & h1), any = lane_of(h0 | h1);
           const unsigned c0 = __float_as_uint(n2.z), c1 = __float_as_uint(n0.w);
           const unsigned far = near0 ? c1 : c0;
-          stk[ti + 64] = (int)far;
+          stk(ti + 256) = (int)far;
           if (deep) {  // entries in the spill array
-            const int e = (tp >> 6) - HDOF_LDS_STACK;
+            const int e = (tp - tp_full) >> 8;
             if (e > 0) top = (unsigned)spill[e - 1];
             if (both && e >= 0) {
               if (e < HDOF_SPILL_STACK)
                 spill[e] = (int)far;
               else
-                atomicOr(A.flags, HDOF_FLAG_STACK_OVERFLOW), tp -= 64;
+                atomicOr(A.flags, HDOF_FLAG_STACK_OVERFLOW), tp -= 256;
             }
           }
           cur = any ? (near0 ? c0 : c1) : top;
-          tp += both ? 64 : 0;
-          tp -= any ? 0 : 64;
+          tp += both ? 256 : 0;
+          tp -= any ? 0 : 256;
         }
       }
       if ((cur & HDOF_LEAF_BIT) && cur != TRAV_DONE) {
-        unsigned top = (unsigned)stk[min(tp, HDOF_LDS_STACK * 64 + lane)];
-        test_leaf(r, A.tris, cur, b);
+        unsigned top = (unsigned)stk(min(tp, tp_full));
+        if (strict == 0ull || !lane_of(strict) ||
+            tris_box_hit(r, A.tris, (int)(cur & HDOF_LEAF_FIRST_MASK), (int)((cur >> 27) & 0xF) + 1, b.t))
+          test_leaf(r, A.tris, cur, b);
         if (COUNT) wk.tests += (int)((cur >> 27) & 0xF) + 1;
-        const int e = (tp >> 6) - HDOF_LDS_STACK;
+        const int e = (tp - tp_full) >> 8;
         if (e > 0) top = (unsigned)spill[e - 1];
         cur = top;
-        tp -= 64;
+        tp -= 256;
       }
       const bool done = slot >= 0 && cur == TRAV_DONE;
       if (done) {  // the stack is empty: the ray's hit goes to its slot
-        L.f[SLOT_INV][slot] = b.t;
-        L.f[SLOT_INV + 1][slot] = __int_as_float(b.tri);
-        L.f[SLOT_INV + 2][slot] = __int_as_float(b.id);
-        L.f[SLOT_DONE][slot] = __int_as_float(1);
+        L.f[SLOT_HIT][slot] = b.t;
+        L.f[SLOT_HIT + 1][slot] = __int_as_float(b.tri);
+        L.f[SLOT_HIT + 2][slot] = __int_as_float(b.id);
+        L.f[SLOT_DONE][slot] = __int_as_float(strict != 0ull && lane_of(strict) ? 3 : 1);
         slot = -1;
         if (COUNT) {
           atomicAdd(&A.counters[3], 1ull);
@@ -938,7 +998,9 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, HDOF_TRACE_WAVES_PER_EU) void k_t
           wk = Work{0, 0};
         }
       }
-      if (__builtin_amdgcn_ballot_w64(done) != 0ull) stall = 0;
+      const unsigned long long dm = __builtin_amdgcn_ballot_w64(done);
+      if (dm != 0ull) stall = 0;
+      strict &= ~dm;
       // (also met by a wave that was given no ray at all)
       const int nidle = (int)__popcll(__builtin_amdgcn_ballot_w64(slot < 0));
       if (nidle >= (next < count ? HDOF_HAND_OUT : (drained ? 64 : refill))) break;

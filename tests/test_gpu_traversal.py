@@ -153,3 +153,34 @@ def test_reduction_any_entry_order(hd, ctx, smax, sa):
         for a, b in zip(out[0], o):
             assert np.array_equal(a, b)
     sc.close()
+
+
+@pytest.mark.parametrize("eye,yaw,S1", [((0.17, 0.03, -0.1), -3.0, 4.0), ((0.05, 0.1, 0.0), 3.0, 0.7)])
+def test_half_boxes_find_the_hits_of_full_boxes(hd, ctx, eye, yaw, S1):
+    """33M rays by the per-lane walk (half-precision boxes) and by the
+    wave-coherent one (the full boxes): the same triangles and depths.  At the
+    very edge of a triangle its leaf's box decides, and the wider half boxes
+    must not add hits there."""
+    print_case(f"half boxes against full boxes {eye} {yaw} {S1}")
+    W, H, smax = 1920, 1080, 16
+    cfg = sg.config_1080p(W, H)
+    cfg = replace(cfg, camera=sg.look_camera(eye, yaw, W, H), lens=replace(cfg.lens, focus_distance=S1))
+    sc = upload_scene(hd, ctx, sg.living_room_scene(0))
+    n = W * H * smax
+    spp = torch.full((H, W), smax, dtype=torch.uint8, device=DEV)
+    off = (torch.arange(H * W, dtype=torch.int32, device=DEV) * smax).view(H, W)
+    total = torch.tensor([n], dtype=torch.int32, device=DEV)
+    got = []
+    for wave in (0, 1):
+        hd.hdof_set_tuning(ctx, wave=wave)
+        rid = torch.full((n,), -7, dtype=torch.int32, device=DEV)
+        rz = torch.zeros(n, dtype=torch.float32, device=DEV)
+        hd.hdof_trace_thin_lens(ctx, sc, hd.camera_of(cfg.camera), hd.lens_of(cfg.lens), hd.light_of(cfg.light), smax,
+                                spp, off, total, seed=11, ray_tri_id=rid, ray_depth=rz)
+        got.append((rid, rz))
+    hd.hdof_set_tuning(ctx)
+    torch.cuda.synchronize()
+    diff = int((got[0][0] != got[1][0]).sum())
+    assert diff == 0, f"{diff} of {n} rays"
+    assert torch.equal(got[0][1], got[1][1])
+    sc.close()
