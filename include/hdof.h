@@ -512,11 +512,11 @@ void hdof_batch_destroy(hdof_batch* batch);
  * G-buffer) and applies the composite once both are done, the results
  * being the same as with 0; overlap_ray_quantum >= 1: while overlapped, the
  * trace keeps, on average, one block per CU for every overlap_ray_quantum
- * rays of the frame (at least one per CU, and one for every 64 rays up to 7
- * per CU or up to the whole queue in one batch per wave; at most
- * blocks_per_cu; the count is read on the device, the other blocks return
- * at once), so a light trace leaves CUs to the gather and a heavy one keeps
- * them.  Defaults {10, 64, 8, 0, 1,
+ * rays of the frame (at least one per CU; in a frame of at least 3 rays per
+ * 8 pixels also one for every 64 rays up to 7 per CU or up to the whole
+ * queue in one batch per wave; at most blocks_per_cu; the count is read on
+ * the device, the other blocks return at once), so a light trace leaves CUs
+ * to the gather and a heavy one keeps them.  Defaults {10, 64, 8, 0, 1,
  * 140000}: ten two-wave blocks per CU (more are slower: the trace is bound
  * by its per-CU cache working set and latency, not by resident waves). */
 #define HDOF_WAVE_AUTO_TRIS (1 << 19)

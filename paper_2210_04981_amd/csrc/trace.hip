@@ -729,12 +729,16 @@ __global__ __launch_bounds__(256) void k_gbuffer_batch(const float4* __restrict_
 // which the frame then waits for.  (Frames of 640x360 with 218k rays at 1.6 /
 // 3.6 / 10 blocks per CU: 337 / 279 / 250 us; 1400x1050 with 693k at 5 / 7 /
 // 10: 483 / 454 / 462; 400x300 with 73k at 1 / 3.6 / 4.5: 157 / 117 / 119.)
+// Below 3 rays per 8 pixels the frame waits for the gather, not for the
+// trace (1080p with 571k rays at 4.1 / 7 blocks per CU: 358 / 379 us; the
+// frames above have 0.47 to 0.95 rays per pixel).
 // The first blocks are kept, so every queue segment keeps its blocks.
 __device__ inline int kept_blocks(const TraceArgs& A, int total) {
   const long all = (long)A.bpc * A.n_cu;
   if (A.ray_quantum <= 0) return (int)all;
   const long light = ((long)total * A.n_cu + A.ray_quantum - 1) / A.ray_quantum;
-  const long most = total <= HDOF_TRACE_BLOCK * all ? all : 7l * A.n_cu;
+  const bool few = 8l * total < 3l * A.v0.k.W * A.v0.k.H;
+  const long most = few ? 0 : (total <= HDOF_TRACE_BLOCK * all ? all : 7l * A.n_cu);
   return (int)min(all, max(max((long)A.n_cu, light), min(most, (long)total / 64)));
 }
 
