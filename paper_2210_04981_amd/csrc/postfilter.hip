@@ -1099,6 +1099,9 @@ static_assert(17 + 2 * PPB_WIN_E <= 64, "a window row per wave");
 #endif
 #define PPB_WIN (17 + 2 * PPB_WIN_E)            // the window's side
 #define PPB_WS ((PPB_WIN + 3) / 8 * 8 + 4)      // its row stride: the four rows a wave adds to at a time lie in different banks
+// that of a smaller window, which leaves a footprint's space behind its channels
+#define PPB_FAR_E 17
+static_assert((17 + 2 * PPB_FAR_E) * PPB_WS + PPG_SIDE * PPG_SIDE <= PPB_WIN * PPB_WS, "a footprint behind it");
 #define PPB_SUMS 9
 enum { S_W, S_C, S_A, S_R, S_GW, S_GC, S_GA, S_GR, S_GM };
 
@@ -1363,12 +1366,44 @@ __device__ __forceinline__ void image_add(float* __restrict__ gc, const float (&
   }
 }
 
+// The same of a wave's whole footprint, 17x17 texels, whose corner is image
+// texel (x0, y0): through LDS (foot: the wave's 289 floats), so its rows are
+// added in their order.  What the atomics cost is the 64-byte pieces of rows
+// they touch: 35 so, 50 with the last column apart.
+__device__ __forceinline__ void image_add_foot(float* __restrict__ gc, float* foot, const float (&r)[5], int x0, int y0,
+                                               int W, int H, float ax, bool firstc, bool lastc, bool lastr) {
+  const int lane = threadIdx.x & 63;
+  float* const s = foot + (lane >> 4) * 4 * PPG_SIDE + (lane & 15);
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    const float left = row_left(r[q]);
+    const float t = fmaf(ax, firstc ? 0.f : left, (1.f - ax) * r[q]);
+    if (q < 4 || lastr) {
+      s[q * PPG_SIDE] = t;
+      if (lastc) s[q * PPG_SIDE + 1] = ax * r[q];
+    }
+  }
+  // (other lanes' texels are read next, see win_add)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const int t = i * 64 + lane, row = (t * 241) >> 12, col = t - row * PPG_SIDE;  // (t / 17 for t < 320)
+    const float v = t < PPG_SIDE * PPG_SIDE ? foot[t] : 0.f;
+    float* const gr = gc + __umul24((unsigned)clampi(y0 + row, 0, H - 1), (unsigned)W);
+    if (v != 0.f) atomicAdd(gr + clampi(x0 + col, 0, W - 1), v);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Pass 2 of one channel for n <= PPB_G taps: their weights times the pixels'
 // kc (and kup of the pixel above the lane's first), joined along the column.
 template <bool UNI, class Geo>
 __device__ __forceinline__ void ppb_scatter(const float4* wts, int lane, int n, const float (&kc)[4], float kup, int E,
-                                            float* win, float* __restrict__ gc, int x, int yb, int W, int H,
-                                            bool firstc, bool lastc, bool lastr, int mine, int nt, Geo geo) {
+                                            float* win, float* foot, float* __restrict__ gc, int x0, int y0, int W,
+                                            int H, bool firstc, bool lastc, bool lastr, int mine, int nt, Geo geo) {
+  const int x = x0 + (lane & 15), yb = y0 + (lane >> 4) * 4;
   float4 w4[PPB_G];
   float wu[PPB_G];
 #pragma unroll
@@ -1386,7 +1421,9 @@ __device__ __forceinline__ void ppb_scatter(const float4* wts, int lane, int n, 
                           fmaf(by, post[2], ay * post[1]), fmaf(by, post[3], ay * post[2]), ay * post[3]};
       const bool in = tg.ix >= -E && tg.ix <= E && tg.iy >= -E && tg.iy <= E;
       if (!UNI || in) win_add(win + tg.iy * PPB_WS + tg.ix, r, tg.ax, in, firstc, lastc, lastr, mine, nt);
-      if (UNI ? !in : __builtin_amdgcn_ballot_w64(!in) != 0ull)
+      if (UNI && !in)
+        image_add_foot(gc, foot, r, x0 + tg.ix, y0 + tg.iy, W, H, tg.ax, firstc, lastc, lastr);
+      if (!UNI && __builtin_amdgcn_ballot_w64(!in) != 0ull)
         image_add(gc, r, x + tg.ix, yb + tg.iy, W, H, tg.ax, !in, firstc, lastc, lastr);
     }
   }
@@ -1404,7 +1441,8 @@ __device__ __forceinline__ void ppb_scatter(const float4* wts, int lane, int n, 
 // from the CoC plane: 48 weights of 256 pixels would take 48 KB of LDS),
 // transposed to the texels of every tap: the lanes' posts are joined to the
 // tile's footprint in registers and added to the block's LDS window if the
-// tap's offset is at most PPB_WIN_E (flushed once with global atomics; window
+// tap's offset lies in it (up to PPB_WIN_E, or PPB_FAR_E where some lie
+// beyond; flushed once with global atomics; window
 // texels are image texels clamped to the edge, as in the gather), or to the
 // image.  Of PPB_G taps at a time three waves add a channel each to the
 // window, without barriers between the taps, and the fourth forms half of
@@ -1413,7 +1451,10 @@ __device__ __forceinline__ void ppb_scatter(const float4* wts, int lane, int n, 
 // channels in turns with a barrier each: 0.74.)
 // Bound at 1080p, 48 taps, 16-pixel tiles: vector arithmetic (65 %), the rest
 // waiting for LDS and, on the quarter of the tiles with R of 46, for global
-// atomics (0.14 ms): 0.92 -> 0.68 ms.  1708x923 with 4-pixel tiles, whose
+// atomics (0.14 ms): 0.92 -> 0.68 ms.  With most tiles beyond the window
+// (the 1080p interior) the atomics bound it: 1.35 -> 1.28 ms, 1.51 with the
+// footprint's last column apart; all blocks at the same group of taps cost
+// 2 % more.  1708x923 with 4-pixel tiles, whose
 // radii differ within a block: 5.0 -> 1.8 ms, of it 1.5 the tiles' turns.
 // The window's limit: a third block per CU fits up to 20 (24: 0.2 ms slower).
 struct PpbArgs {
@@ -1575,7 +1616,10 @@ __device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk
     }
   }
   // the window: texel (r, s) of a channel is image texel (y0 - E + r, x0 - E + s)
-  const int E = min(PPB_WIN_E, ER), wd = 17 + 2 * E;
+  // (UNI: a window of E > PPB_FAR_E has room for every tap, with one texel for
+  // the offsets' rounding)
+  const bool far = ER >= PPB_WIN_E;
+  const int E = UNI && far ? PPB_FAR_E : min(PPB_WIN_E, ER + 1), wd = 17 + 2 * E;
   constexpr int PL = PPB_WIN * PPB_WS;  // a channel's plane
   float* const gp = (float*)wts;
   __syncthreads();  // all sums read
@@ -1608,11 +1652,16 @@ __device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk
     const int mine = (ly / tl) * (16 / tl) + lx / tl;
     float* const win = buf + wave * PL + (ly + E) * PPB_WS + lx + E;
     float* const gc = gcol + wave * N;
+    // blocks with taps outside the window start at different groups of taps:
+    // their atomics land on different texels at a time
+    const int ng = (n_taps + PPB_G - 1) / PPB_G, rot = far ? (blk * 17) % ng : 0;
+    float* const foot = buf + wave * PL + (17 + 2 * PPB_FAR_E) * PPB_WS;
     // (UNI) lane i keeps the geometry and distance term of tap kl + i
     TapGeo lg{0, 0, 0.f, 0.f};
     float ld = 0.f;
-    for (int k0 = 0, kl = 0, b = 0; k0 < n_taps; k0 += PPB_G, b ^= 1) {
-      if (UNI && (k0 == 0 || k0 + PPB_G > kl + 64)) {
+    for (int i = 0, kl = -64; i < ng; ++i) {
+      const int k0 = PPB_G * (i + rot < ng ? i + rot : i + rot - ng), b = i & 1;
+      if (UNI && (k0 < kl || k0 + PPB_G > kl + 64)) {
         kl = k0;
         const float4 u = taps[min(k0 + lane, n_taps - 1)];
         lg = tap_geo(R, u);
@@ -1620,10 +1669,10 @@ __device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk
       }
       const auto geo = [&](int j) {
         if (!UNI) return tap_geo(R, taps[k0 + j]);
-        const int i = k0 - kl + j;
-        return TapGeo{__builtin_amdgcn_readlane(lg.ix, i), __builtin_amdgcn_readlane(lg.iy, i),
-                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lg.ax), i)),
-                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lg.ay), i))};
+        const int e = k0 - kl + j;
+        return TapGeo{__builtin_amdgcn_readlane(lg.ix, e), __builtin_amdgcn_readlane(lg.iy, e),
+                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lg.ax), e)),
+                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lg.ay), e))};
       };
       // the fourth wave, which has no channel, forms half of the weights
       const int n = min(PPB_G, n_taps - k0), j1 = wave < 3 ? wave + 1 : PPB_G;
@@ -1636,7 +1685,7 @@ __device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk
       }
       lds_barrier();
       if (wave < 3)
-        ppb_scatter<UNI>(wts[b], lane, n, kc, kup, E, win, gc, x, yb, W, H, firstc, lastc, lastr, mine, nt, geo);
+        ppb_scatter<UNI>(wts[b], lane, n, kc, kup, E, win, foot, gc, x0, y0, W, H, firstc, lastc, lastr, mine, nt, geo);
     }
   }
   __syncthreads();
