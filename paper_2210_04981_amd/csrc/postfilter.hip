@@ -1095,13 +1095,14 @@ static_assert(17 + 2 * PPB_WIN_E <= 64, "a window row per wave");
 #define PPB_MINW 1
 #endif
 #ifndef PPB_G
-#define PPB_G 6                                 // taps whose weights are exchanged at a time
+#define PPB_G 5                                 // taps whose weights are exchanged at a time
 #endif
 #define PPB_WIN (17 + 2 * PPB_WIN_E)            // the window's side
 #define PPB_WS ((PPB_WIN + 3) / 8 * 8 + 4)      // its row stride: the four rows a wave adds to at a time lie in different banks
 // that of a smaller window, which leaves a footprint's space behind its channels
-#define PPB_FAR_E 17
-static_assert((17 + 2 * PPB_FAR_E) * PPB_WS + PPG_SIDE * PPG_SIDE <= PPB_WIN * PPB_WS, "a footprint behind it");
+#define PPB_FAR_E 19
+#define PPB_PLANE (((17 + 2 * PPB_FAR_E) * PPB_WS + PPG_SIDE * PPG_SIDE + 3) / 4 * 4)  // a channel's
+static_assert(PPB_WIN * PPB_WS <= PPB_PLANE, "either window");
 #define PPB_SUMS 9
 enum { S_W, S_C, S_A, S_R, S_GW, S_GC, S_GA, S_GR, S_GM };
 
@@ -1445,18 +1446,19 @@ __device__ __forceinline__ void ppb_scatter(const float4* wts, int lane, int n, 
 // beyond; flushed once with global atomics; window
 // texels are image texels clamped to the edge, as in the gather), or to the
 // image.  Of PPB_G taps at a time three waves add a channel each to the
-// window, without barriers between the taps, and the fourth forms half of
-// the weights.  (LDS float atomics would let every wave add to all channels,
+// window, without barriers between the taps, and the fourth forms two of
+// the weights, the others one each.  (LDS float atomics would let every wave add to all channels,
 // but take 190 clocks each: 4.1 ms for the 1080p image below; four waves'
 // channels in turns with a barrier each: 0.74.)
 // Bound at 1080p, 48 taps, 16-pixel tiles: vector arithmetic (65 %), the rest
 // waiting for LDS and, on the quarter of the tiles with R of 46, for global
 // atomics (0.14 ms): 0.92 -> 0.68 ms.  With most tiles beyond the window
-// (the 1080p interior) the atomics bound it: 1.35 -> 1.28 ms, 1.51 with the
+// (the 1080p interior) the atomics bound it: 1.35 -> 1.27 ms, 1.51 with the
 // footprint's last column apart; all blocks at the same group of taps cost
 // 2 % more.  1708x923 with 4-pixel tiles, whose
 // radii differ within a block: 5.0 -> 1.8 ms, of it 1.5 the tiles' turns.
 // The window's limit: a third block per CU fits up to 20 (24: 0.2 ms slower).
+// Groups of 5 taps leave the smaller window 19; of 6, 17: 1 to 3 % slower.
 struct PpbArgs {
   const float4* pack;
   const float *coc, *rad;
@@ -1478,7 +1480,7 @@ struct PpbArgs {
 struct PpbLds {
   // the waves' rings of staged texels, then their sums, then the window and
   // behind it two buffers of the weights of a group of taps
-  static constexpr int WIN = 3 * PPB_WIN * PPB_WS, WTS = 2 * PPB_G * 256, SUMS = 4 * PPB_SUMS * 256,
+  static constexpr int WIN = 3 * PPB_PLANE, WTS = 2 * PPB_G * 256, SUMS = 4 * PPB_SUMS * 256,
                        RING = 4 * 2 * 4 * PPG_TAPSZ;
   static constexpr int MAX1 = SUMS > RING ? SUMS : RING;
   float buf[WIN + WTS > MAX1 ? WIN + WTS : MAX1];
@@ -1620,7 +1622,7 @@ __device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk
   // the offsets' rounding)
   const bool far = ER >= PPB_WIN_E;
   const int E = UNI && far ? PPB_FAR_E : min(PPB_WIN_E, ER + 1), wd = 17 + 2 * E;
-  constexpr int PL = PPB_WIN * PPB_WS;  // a channel's plane
+  constexpr int PL = PPB_PLANE;  // a channel's plane
   float* const gp = (float*)wts;
   __syncthreads();  // all sums read
 #pragma unroll
@@ -1674,7 +1676,7 @@ __device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk
                       __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lg.ax), e)),
                       __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lg.ay), e))};
       };
-      // the fourth wave, which has no channel, forms half of the weights
+      // the fourth wave, which has no channel, forms the weights that are left
       const int n = min(PPB_G, n_taps - k0), j1 = wave < 3 ? wave + 1 : PPB_G;
       for (int j = wave; j < j1 && j < n; ++j) {
         const float d = UNI ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ld), k0 - kl + j))

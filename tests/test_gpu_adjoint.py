@@ -139,7 +139,7 @@ def test_autograd_function_and_focus_fit(hd, ctx):
 def test_backward_tiles_windows_and_groups(hd, ctx, W, H, tile, r_cap, n_taps, A, flat):
     """Ragged images; radii below, at and above the largest one a block's
     window takes (20); small tiles of unequal and (flat) of equal radius,
-    which take the 16-pixel tiles' path; tap counts around the groups of six
+    which take the 16-pixel tiles' path; tap counts around the groups of taps
     and the 64 whose geometry a wave keeps."""
     print_case(f"adjoint {W}x{H} tile {tile} cap {r_cap} taps {n_taps} A {A} flat {flat}")
     rng = np.random.default_rng(W + tile + n_taps)
