@@ -17,6 +17,7 @@
 #include <utility>
 
 #include "hdof_internal.h"
+#include "ploc.h"
 
 #define RS_THREADS 256
 #define RS_ITEMS 4
@@ -424,8 +425,8 @@ __device__ __forceinline__ void lds_barrier() {
 // launches each would cost more than their work.  A cluster's search is
 // shared by up to eight threads once the clusters leave that many idle; the
 // barriers do not wait for the nodes' stores (127 -> 104 us).
-// Stops at one cluster, or at a round without a merge.
-#define PLOC_TAIL 1024
+// Stops at one cluster, or at a round without a merge; the clusters left by
+// its merges are not written back (see ploc_step).
 __global__ __launch_bounds__(PLOC_TAIL) void k_ploc_tail(const int* __restrict__ cid, const float4* __restrict__ cbox,
                                                          const int2* __restrict__ csz, int2* __restrict__ state,
                                                          int* __restrict__ bl, int* __restrict__ br,
@@ -847,8 +848,8 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
         break;
       }
       m = h.x;
-      if (m < 1 || m >= m0 || h.y != m - 2) {  // every merge takes one cluster and one node
-        status = hdof_set_error(HDOF_ERR_HIP, "BVH clustering made no progress (%d clusters)", m0);
+      if (ploc_step(m0, m, h.y) == PLOC_STALLED) {
+        status = hdof_set_error(HDOF_ERR_HIP, "BVH clustering made no progress (%d clusters)", m);
         break;
       }
     }

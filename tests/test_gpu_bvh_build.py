@@ -75,3 +75,21 @@ def test_equal_triangles(hd, ctx):
     ctx.sync()
     assert set(np.unique(gb.tri_id.cpu().numpy())) <= {-1, 0}
     sc.close()
+
+
+@pytest.mark.parametrize("n,what", [(2, "inf"), (300, "inf"), (1500, "inf"), (300, "far"), (3000, "far")])
+def test_geometry_that_does_not_cluster_is_refused(hd, ctx, n, what):
+    """An infinite vertex, or two groups so far apart that the area of their
+    union overflows: rounds make progress, then none merges.  The build is
+    refused and the context builds on."""
+    print_case(f"refused build: {n} triangles, {what}")
+    scene = soup(n, n, 0.05)
+    v = scene.verts.copy()
+    if what == "inf":
+        v[n // 3, 4] = np.inf
+    else:
+        v *= np.float32(1e13)
+        v.reshape(n, 3, 3)[n // 2:, :, :2] += np.float32(1e20)
+    with pytest.raises(hd.HdofError, match="no progress"):
+        upload_scene(hd, ctx, sg.Scene(v, scene.albedo))
+    check(hd, ctx, soup(400, 9, 0.1))
