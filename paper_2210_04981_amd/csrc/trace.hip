@@ -995,8 +995,8 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, 5) void k_trace(TraceArgs A) {
         L.f[SLOT_HIT + 2][slot] = __int_as_float(b.id);
         L.f[SLOT_DONE][slot] = __int_as_float(strict != 0ull && lane_of(strict) ? 3 : 1);
         slot = -1;
-        if (COUNT) {
-          atomicAdd(&A.counters[3], 1ull);
+        if (COUNT) {  // a second walk is no other ray, but its work counts
+          if (!lane_of(strict)) atomicAdd(&A.counters[3], 1ull);
           atomicAdd(&A.counters[4], (unsigned long long)wk.visits);
           atomicAdd(&A.counters[5], (unsigned long long)wk.tests);
           wk = Work{0, 0};

@@ -184,3 +184,37 @@ def test_half_boxes_find_the_hits_of_full_boxes(hd, ctx, eye, yaw, S1):
     assert diff == 0, f"{diff} of {n} rays"
     assert torch.equal(got[0][1], got[1][1])
     sc.close()
+
+
+def far_room(hd, ctx, shift=0.0, ground=0.0, w=320, h=180, smax=8):
+    """The living room moved along (1, 1, 1), or on a ground plane far wider
+    than itself: its scene, and the arguments of a trace of every pixel."""
+    cfg = sg.config_1080p(w, h)
+    scene = sg.living_room_scene(0)
+    verts, albedo = scene.verts, scene.albedo
+    if ground:
+        g, y = ground, float(verts.reshape(-1, 3)[:, 1].min()) - 0.05
+        q = np.array([(-g, y, -g), (g, y, -g), (g, y, g), (-g, y, g)], np.float32)
+        verts = np.concatenate([verts, q[[0, 1, 2]].reshape(1, 9), q[[0, 2, 3]].reshape(1, 9)])
+        albedo = np.concatenate([albedo, np.full((2, 3), 0.5, albedo.dtype)])
+    cam = replace(cfg.camera, eye=(np.asarray(cfg.camera.eye) + shift).astype(np.float32))
+    sc = upload_scene(hd, ctx, sg.Scene((verts + np.float32(shift)).astype(np.float32), albedo))
+    spp = torch.full((h, w), smax, dtype=torch.uint8, device=DEV)
+    off = (torch.arange(h * w, dtype=torch.int32, device=DEV) * smax).view(h, w)
+    total = torch.tensor([h * w * smax], dtype=torch.int32, device=DEV)
+    return sc, (hd.camera_of(cam), hd.lens_of(cfg.lens), hd.light_of(cfg.light), smax, spp, off, total), h * w * smax
+
+
+@pytest.mark.parametrize("wave", [0, 1])
+def test_counted_rays_are_the_queue(hd, ctx, wave):
+    """A ray that is walked a second time (its hit lies at the very edge of a
+    triangle; far from the origin every hundredth does) is one ray."""
+    print_case(f"counters, wave {wave}")
+    sc, args, n = far_room(hd, ctx, 1000.0)
+    hd.hdof_set_tuning(ctx, wave=wave)
+    hd.hdof_counters_begin(ctx)
+    hd.hdof_trace_thin_lens(ctx, sc, *args, seed=3)
+    c = hd.hdof_counters_end(ctx)
+    hd.hdof_set_tuning(ctx)
+    assert c["trace_rays"] == n and c["trace_visits"] >= n, c
+    sc.close()
