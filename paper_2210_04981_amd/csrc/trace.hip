@@ -126,7 +126,12 @@ __device__ inline bool box_hit_signed(const Ray& r, float nx, float fx, float ny
 // Half-precision boxes: a pair of planes (minimum, maximum) in units about
 // the node's centre.  Rotated by 16 where the ray runs against the axis, a
 // pair has the plane the ray enters through in its low half, and an fma
-// that takes a half operand gives its distance.
+// that takes a half operand gives its distance.  A node that box_hit enters
+// by its full boxes is entered here: with e = 2^-24, a plane's distance t
+// there has one rounding (e t), here two, of the centre's distance and of
+// the sum (2 e t, and e times the plane's offset from the centre, which the
+// planes' margin covers), so both sides of the comparison may be 3 e nearer
+// or farther and the 7 e of box_hit become 13 e: 1 + 2^-20.
 __device__ inline float half_dist(unsigned pair, int hi, float sinv, float base) {
   unsigned short u = (unsigned short)(hi ? pair >> 16 : pair);
   _Float16 h;
@@ -144,7 +149,7 @@ __device__ inline bool box_hit_half(unsigned x, unsigned y, unsigned z, V3 sinv,
   const float tmx = fminf(fminf(half_dist(x, 1, sinv.x, base.x), half_dist(y, 1, sinv.y, base.y)),
                           fminf(half_dist(z, 1, sinv.z, base.z), tmax));
   tnear = tmin;
-  return tmin <= tmx * 1.0000004f;
+  return tmin <= tmx * 1.00000095f;
 }
 
 struct Best {
@@ -852,7 +857,10 @@ __global__ __launch_bounds__(HDOF_TRACE_BLOCK, 5) void k_trace(TraceArgs A) {
         // none for a walk by full boxes.  A ray that misses the triangle's
         // own box is walked again with every leaf's box tested, as full boxes
         // do, so the hits are those of full boxes (without it 4 of 18M rays
-        // differed; the check costs the trace 1 to 2 %).
+        // differed; the check costs the trace 1 to 2 %).  Far from the origin
+        // the full boxes' own rounding decides more hits, and two walks by
+        // them in another order differ too: 5 of 461k rays at 10^4 units, as
+        // many as differ here.
         if (state == 1 && h.tri >= 0) {
           Ray q;
           q.inv = slot_v3(L, SLOT_INV, lane);
