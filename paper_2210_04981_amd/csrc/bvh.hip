@@ -39,20 +39,37 @@ __device__ inline void block_min6(float v[6], float (*red)[RS_THREADS / 64]) {
   for (int a = 0; a < 6; ++a) v[a] = fminf(fminf(red[a][0], red[a][1]), fminf(red[a][2], red[a][3]));
 }
 
+// Per block: the centroids' bounds, and of its triangles of finite extent the
+// number and the sum of the exponents of their largest extents.
 __global__ __launch_bounds__(RS_THREADS) void k_centroid_bounds(const float* __restrict__ v, int n,
-                                                                float* __restrict__ part) {
+                                                                float* __restrict__ part, int2* __restrict__ sizes) {
   __shared__ float red[6][RS_THREADS / 64];
+  __shared__ int2 size_red[RS_THREADS / 64];
+  int2 sz = make_int2(0, 0);
   float m[6] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
   for (int i = blockIdx.x * RS_THREADS + threadIdx.x; i < n; i += gridDim.x * RS_THREADS) {
     const float* t = v + 9 * (size_t)i;
+    float ext = 0.0f;
     for (int a = 0; a < 3; ++a) {
       float c = (t[a] + t[3 + a] + t[6 + a]) * (1.0f / 3.0f);
       m[a] = fminf(m[a], c);
       m[3 + a] = fminf(m[3 + a], -c);
+      ext = fmaxf(ext, fmaxf(fmaxf(t[a], t[3 + a]), t[6 + a]) - fminf(fminf(t[a], t[3 + a]), t[6 + a]));
+    }
+    if (ext > 0.0f && ext < INFINITY) {
+      int e;
+      frexpf(ext, &e);
+      sz.x += 1, sz.y += e;
     }
   }
+  for (int o = 32; o > 0; o >>= 1) sz.x += __shfl_xor(sz.x, o), sz.y += __shfl_xor(sz.y, o);
+  if ((threadIdx.x & 63) == 0) size_red[threadIdx.x >> 6] = sz;
   block_min6(m, red);
   if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = m[threadIdx.x];
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < RS_THREADS / 64; ++w) sz.x += size_red[w].x, sz.y += size_red[w].y;
+    sizes[blockIdx.x] = sz;
+  }
 }
 
 __device__ inline uint64_t spread21(uint64_t x) {
@@ -66,17 +83,25 @@ __device__ inline uint64_t spread21(uint64_t x) {
 }
 
 // Morton codes of the centroids in the bounds that the partial ones reduce
-// to; the albedo's copy too
+// to; the albedo's copy and the mean exponent of the triangles' extents too
 __global__ __launch_bounds__(RS_THREADS) void k_morton(const float* __restrict__ v, int n,
-                                                       const float* __restrict__ part, int nparts,
+                                                       const float* __restrict__ part,
+                                                       const int2* __restrict__ sizes, int nparts,
                                                        const float* __restrict__ albedo, uint64_t* __restrict__ keys,
-                                                       int* __restrict__ vals, float* __restrict__ alb_out) {
+                                                       int* __restrict__ vals, float* __restrict__ alb_out,
+                                                       int* __restrict__ mean) {
   __shared__ float red[6][RS_THREADS / 64];
   float m[6] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
   for (int k = threadIdx.x; k < nparts; k += RS_THREADS)
     for (int a = 0; a < 6; ++a) m[a] = fminf(m[a], part[6 * k + a]);
   block_min6(m, red);
   const int i0 = blockIdx.x * RS_THREADS, i = i0 + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    long count = 0, sum = 0;
+    for (int k = threadIdx.x; k < nparts; k += 64) count += sizes[k].x, sum += sizes[k].y;
+    for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o), sum += __shfl_xor(sum, o);
+    if (threadIdx.x == 0) *mean = count > 0 ? (int)floorf((float)sum / (float)count) : 1000;
+  }
   for (int k = 0; k < 3; ++k) {
     const size_t j = 3 * (size_t)i0 + k * RS_THREADS + threadIdx.x;
     if (j < 3 * (size_t)n) alb_out[j] = albedo[j];
@@ -617,16 +642,25 @@ __device__ inline unsigned leaf_code(int first, int count) {
 }
 
 // ---- half-precision nodes -----------------------------------------------------
-// The scene's box unit: a power of two of which the root box's largest
-// extent is at most 2^14, so that box planes relative to their node's centre
-// are halves well inside the range of normal numbers.
-__device__ inline float box_unit(const float* __restrict__ root) {
+// The scene's box unit, a power of two.  Box planes relative to their node's
+// centre are halves, of 11 bits from 2^-14 to 2^16 units and of fixed steps
+// of 2^-24 below.  The root's largest extent is at most 2^14 units, unless
+// that would leave triangles of the usual size (the geometric mean of their
+// extents, 2^mean) below 2^-10 units, in a scene with a ground or a sky a
+// million times wider than the rest: then they have that size, and planes
+// beyond 2^16 units from their node's centre, of the few nodes that hold the
+// far geometry, are infinite (every ray passes them).  Node visits and
+// triangle tests per ray of a room on a ground of 1e8 / 1e10 / 1e14 units:
+// 59 / 637 / 34006 with the root's extent alone, 57 / 48 / 48 so and by fp32
+// boxes.  At most 2^27: a ray's inverse direction, up to 1e30, is multiplied
+// by the unit.
+__device__ inline float box_unit(const float* __restrict__ root, int mean) {
   float ext = 0.0f;
   for (int a = 0; a < 3; ++a) ext = fmaxf(ext, root[3 + a] - root[a]);
   int e = 0;
   frexpf(ext, &e);  // ext < 2^e
-  e = ext > 0.0f && ext < INFINITY ? max(-100, min(100, e - 14)) : 0;
-  return ldexpf(1.0f, e);
+  e = ext > 0.0f && ext < INFINITY ? e - 14 : 0;
+  return ldexpf(1.0f, max(-100, min(27, min(e, mean + 10))));
 }
 
 // the box plane d above its node's centre in units, rounded outwards (dir -1 or 1)
@@ -680,10 +714,11 @@ __global__ void k_emit_nodes(int nint, const int* __restrict__ bl, const int* __
                              const int2* __restrict__ bsz, const float* __restrict__ bbox,
                              const float* __restrict__ lbox, const int* __restrict__ leaf_off,
                              const int* __restrict__ node_off, const int* __restrict__ node_idx,
-                             float* __restrict__ unit, float4* __restrict__ nodes, float4* __restrict__ hnodes) {
+                             const int* __restrict__ mean, float* __restrict__ unit, float4* __restrict__ nodes,
+                             float4* __restrict__ hnodes) {
   int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= nint) return;
-  const float u = box_unit(bbox);  // node 0 is the root
+  const float u = box_unit(bbox, *mean);  // node 0 is the root
   if (a == 0) *unit = u;
   if (a != 0 && bsz[a].x <= HDOF_BVH_LEAF) return;
   int ch[2] = {bl[a], br[a]};
@@ -713,9 +748,9 @@ __global__ void k_emit_nodes(int nint, const int* __restrict__ bl, const int* __
 }
 
 // one triangle: a root whose second child box is empty
-__global__ void k_single_root(const float* __restrict__ lbox, float* __restrict__ unit, float4* __restrict__ nodes,
-                              float4* __restrict__ hnodes) {
-  const float u = box_unit(lbox);
+__global__ void k_single_root(const float* __restrict__ lbox, const int* __restrict__ mean, float* __restrict__ unit,
+                              float4* __restrict__ nodes, float4* __restrict__ hnodes) {
+  const float u = box_unit(lbox, *mean);
   *unit = u;
   emit_half(hnodes, lbox, lbox, leaf_code(0, 1), leaf_code(0, 1), u);
   float4* o = nodes;
@@ -761,7 +796,8 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
   sc->bytes = (int64_t)sizeof(float4) * (7 * (int64_t)nint + 3 * (int64_t)n) + 12 * (int64_t)n;
   // build scratch, one buffer of the context
   off = 0;
-  size_t o_bounds = carve(sizeof(float) * 6 * nbounds);
+  size_t o_bounds = carve(sizeof(float) * 6 * nbounds), o_sizes = carve(sizeof(int2) * nbounds);
+  size_t o_mean = carve(sizeof(int));
   size_t o_k0 = carve(sizeof(uint64_t) * n), o_k1 = carve(sizeof(uint64_t) * n);
   size_t o_v0 = carve(sizeof(int) * n), o_v1 = carve(sizeof(int) * n);
   size_t o_hist = carve(sizeof(int) * 256 * (size_t)nb), o_dig = carve(sizeof(int) * 256);
@@ -780,6 +816,8 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
   if (status != HDOF_OK) return status;
   char* s = (char*)ctx->bvh_scratch.p;
   float* bounds = (float*)(s + o_bounds);
+  int2* sizes = (int2*)(s + o_sizes);
+  int* mean = (int*)(s + o_mean);
   uint64_t* k0 = (uint64_t*)(s + o_k0);
   uint64_t* k1 = (uint64_t*)(s + o_k1);
   int* v0 = (int*)(s + o_v0);
@@ -799,9 +837,9 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
   int *loff = (int*)(s + o_loff), *noff = (int*)(s + o_noff), *nidx = (int*)(s + o_nidx);
   int* ndep = (int*)(s + o_ndep);
 
-  hipLaunchKernelGGL(k_centroid_bounds, dim3(nbounds), dim3(RS_THREADS), 0, st, verts, n, bounds);
+  hipLaunchKernelGGL(k_centroid_bounds, dim3(nbounds), dim3(RS_THREADS), 0, st, verts, n, bounds, sizes);
   hipLaunchKernelGGL(k_morton, dim3(cdiv(n, RS_THREADS)), dim3(RS_THREADS), 0, st, verts, n, (const float*)bounds,
-                     nbounds, albedo, k0, v0, sc->albedo);
+                     (const int2*)sizes, nbounds, albedo, k0, v0, sc->albedo, mean);
   for (int pass = 0; pass < 8; ++pass) {
     int shift = 8 * pass;
     hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(RS_THREADS), 0, st, k0, n, shift, nb, hist);
@@ -816,7 +854,8 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
   hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, sc->depth_out, 1, n == 1 ? 2 : 1);
   if (n == 1) {
     hipLaunchKernelGGL(k_place_tris, dim3(1), dim3(64), 0, st, verts, (const int*)v0, (const int*)nullptr, n, sc->tris);
-    hipLaunchKernelGGL(k_single_root, dim3(1), dim3(1), 0, st, (const float*)lbox, sc->unit, sc->nodes, sc->hnodes);
+    hipLaunchKernelGGL(k_single_root, dim3(1), dim3(1), 0, st, (const float*)lbox, (const int*)mean,
+                       sc->unit, sc->nodes, sc->hnodes);
   } else {
     // rounds over grids sized by the last count the host has read, as many
     // at a time as should leave PLOC_TAIL clusters (a round leaves between
@@ -869,7 +908,8 @@ hdof_status launch_bvh_build(hdof_ctx* ctx, const float* verts, const float* alb
                          (const int*)loff, n, sc->tris);
       hipLaunchKernelGGL(k_emit_nodes, dim3(cdiv(nint, 256)), dim3(256), 0, st, nint, (const int*)bl,
                          (const int*)br, (const int2*)bsz, (const float*)bbox, (const float*)lbox,
-                         (const int*)loff, (const int*)noff, (const int*)nidx, sc->unit, sc->nodes, sc->hnodes);
+                         (const int*)loff, (const int*)noff, (const int*)nidx, (const int*)mean, sc->unit, sc->nodes,
+                         sc->hnodes);
     }
   }
   hipError_t e = hipGetLastError();

@@ -239,7 +239,7 @@ def both_forms(hd, ctx, sc, args, n):
 
 @pytest.mark.parametrize("shift,ground,full,share", [
     (0.0, 0.0, 34.37, 0.0), (1e4, 0.0, 38.60, 1e-4), (1e5, 0.0, 40.58, 5e-4), (0.0, 1e4, 51.18, 0.0),
-    (0.0, 1e5, 43.68, 0.0), (0.0, 1e8, 56.96, 0.0)])
+    (0.0, 1e5, 43.68, 0.0), (0.0, 1e8, 56.96, 0.0), (0.0, 1e10, 48.31, 0.0), (0.0, 1e14, 48.31, 0.0)])
 def test_far_geometry_keeps_the_boxes_tight(hd, ctx, shift, ground, full, share):
     """A room far from the origin, or on a ground far wider than itself: the
     half boxes stay as tight as the room's size asks, and the hits are those
@@ -256,3 +256,30 @@ def test_far_geometry_keeps_the_boxes_tight(hd, ctx, shift, ground, full, share)
     print(f"work per ray {work:.2f} against {full}, {differ} rays differ")
     assert work <= 1.25 * full
     assert differ <= share * n
+
+
+def test_rays_along_an_axis_in_a_vast_scene(hd, ctx):
+    """No aperture and an odd width: the middle column's rays have a direction
+    component of exactly 0, whose inverse is clamped to 1e30.  Geometry of 1e7
+    units' size inside 1e13: the scene's box unit times that inverse has to
+    stay finite."""
+    print_case("half boxes: axis rays, vast scene")
+    rng = np.random.default_rng(1)
+    c = rng.uniform(0, 1, (4000, 1, 3)) * [6e7, 6e7, 1e8] + [3e7, 3e7, 2e7]
+    v = (c + rng.uniform(-3e6, 3e6, (4000, 3, 3))).reshape(-1, 9)
+    g, y = 1e13, -1e6
+    q = np.array([(-g, y, -g), (g, y, -g), (g, y, g), (-g, y, g)])
+    v = np.concatenate([v, q[[0, 1, 2]].reshape(1, 9), q[[0, 2, 3]].reshape(1, 9)]).astype(np.float32)
+    sc = upload_scene(hd, ctx, sg.Scene(v, np.full((len(v), 3), 0.5, np.float32)))
+    W, H, smax = 65, 65, 1
+    cfg = sg.config_1080p(W, H)
+    cam = sg.look_camera((8.2e7, 7.1e7, 0.0), 0.0, W, H)
+    lens = replace(cfg.lens, aperture=0.0, focus_distance=1e7)
+    spp = torch.ones((H, W), dtype=torch.uint8, device=DEV)
+    off = torch.arange(H * W, dtype=torch.int32, device=DEV).view(H, W)
+    args = (hd.camera_of(cam), hd.lens_of(lens), hd.light_of(cfg.light), smax, spp, off,
+            torch.tensor([H * W], dtype=torch.int32, device=DEV))
+    (half, full), _ = both_forms(hd, ctx, sc, args, H * W)
+    sc.close()
+    assert int((full[0] >= 0).sum()) > H * W // 4
+    assert torch.equal(half[0], full[0]) and torch.equal(half[1], full[1])
