@@ -1155,6 +1155,13 @@ __device__ __forceinline__ RtRay rt_ray(const RtIn& A, const float4& in, int p, 
 #define RTS_T 64
 #define RTS_N 256  // (128: trace and reduction of 8.3M rays 12 us slower)
 #define RTS_AT(i) ((i) + ((i) >> 6))
+// Above RTS_SPP entries a pixel few of the wave's lanes have entries in a
+// chunk, and add them one by one: worth it only where other waves fill the
+// time.  Counts of 255, pixels' lanes / staged: 64x64 pixels 240 / 2790 us,
+// 320x180 401 / 2195, 480x270 2282 / 1202, 640x360 3611 / 2027; 32: 17 / 52,
+// 35 / 36, 288 / 31, 426 / 44; 16: 9 / 10, 11 / 11, 24 / 12, 93 / 16.
+#define RTS_SPP 16
+#define RTS_BLOCKS 256  // of 256 pixels: a wave for each SIMD
 struct RtStage {
   float v[4][RTS_AT(RTS_N)];
 };
@@ -1166,8 +1173,9 @@ struct RtStage {
 // pixels' lanes, every load touches a line per lane, s times over.  Bound:
 // memory.  8.3M rays of every pixel of 960x540: 243 -> 27 us (133 MB of
 // entries, 19 MB of planes).  A pixel's lane reads its own entries where a
-// wave has fewer than RTS_T and where they are spread over more than 64
-// pixels can have (offsets of a caller's own).  Not staged: frames and
+// wave has fewer than RTS_T, where they are spread over more than 64
+// pixels can have (offsets of a caller's own), and where a small image has
+// many per pixel.  Not staged: frames and
 // batches, whose reduction runs beside the post-filter's gather (the kernel
 // alone 313 -> 236 us for sixteen views and 38 -> 36 for a 1080p frame, but
 // the whole calls 7.31 -> 7.34 ms and 692 -> 697 us: the gather keeps the LDS
@@ -1191,7 +1199,7 @@ __device__ __forceinline__ RtSums rt_sums(RtStage* S, const RtIn& A, int p, int 
       hi = max(hi, __shfl_xor(hi, i));
     }
   }
-  if (hi - lo > 64 * 255 || hi - lo < RTS_T) {
+  if (hi - lo > 64 * 255 || hi - lo < RTS_T || (hi - lo > 64 * RTS_SPP && gridDim.x < RTS_BLOCKS)) {
     for (int j = 0; j < s; ++j) t.add<FARPOS>(rt_ray<FARPOS, RAYS>(A, rt_load(A, (size_t)(o + j)), p, j));
     return t;
   }

@@ -283,3 +283,28 @@ def test_rays_along_an_axis_in_a_vast_scene(hd, ctx):
     sc.close()
     assert int((full[0] >= 0).sum()) > H * W // 4
     assert torch.equal(half[0], full[0]) and torch.equal(half[1], full[1])
+
+
+@pytest.mark.parametrize("W,H", [(256, 255), (256, 256)])
+@pytest.mark.parametrize("count", [16, 17, 70])
+def test_reduction_of_many_rays_a_pixel(hd, ctx, W, H, count):
+    """Either side of the counts and image sizes from which a small image's
+    pixels read their own entries: the same sums bit for bit as for entries
+    in random order, which every lane reads for itself."""
+    print_case(f"reduction {W}x{H}, {count} rays a pixel")
+    cfg = sg.config_tiny(aperture_override=0.2)
+    cfg = replace(cfg, camera=replace(cfg.camera, width=W, height=H))
+    sc = upload_scene(hd, ctx, sg.tiny_scene(3))
+    n, out = W * H, []
+    for order in (np.arange(n), np.random.default_rng(count).permutation(n)):
+        off = np.zeros(n, np.int64)
+        off[order] = np.arange(n) * count
+        rt = hd.hdof_trace_thin_lens(ctx, sc, hd.camera_of(cfg.camera), hd.lens_of(cfg.lens), hd.light_of(cfg.light),
+                                     count, torch.full((H, W), count, dtype=torch.uint8, device=DEV),
+                                     to_dev(off.reshape(H, W).astype(np.int32)),
+                                     to_dev(np.array([n * count], np.int32)), seed=5)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in (rt.c_near, rt.c_far, rt.hit_ratio, rt.lum_m1, rt.lum_m2)])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    sc.close()
