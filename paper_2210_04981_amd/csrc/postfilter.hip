@@ -1799,11 +1799,16 @@ hdof_status postfilter_run(hdof_ctx* ctx, const PPScratch& S, const float* color
                        (const float*)S.tile, (const int*)nullptr, TW, TH, K, pp.r_cap, S.rad, (int*)nullptr);
   hdof_prof_mark(ctx, 8, st);
   if (t == 16) {
-    // Below four waves per SIMD the quad form (a wave per tile) leaves the
-    // chip waiting for its own loads and LDS: the four-wave form then (333x187,
-    // 252 tiles, filter alone: 46 against 21 us; 853x479: 63 / 52; 1280x720,
-    // 3600 tiles: 93 / 94; 1600x900, 5700: 130 / 135; 1080p: 157 / 178).
-    const bool sa = l.sa != 0.0f, few = TW * TH < 4096;
+    // The quad form (a wave per tile, blocks of four) rises in steps of four
+    // tiles per CU, the four-wave form evenly: it is the faster one below
+    // 11 tiles per CU and on the first half of the next step, 12 to 14
+    // (filter alone, quad / four-wave form, us: 333x187, 1 tile per CU,
+    // 46 / 21; 853x479, 6.3, 63 / 52; 1120x640, 10.9, 71 / 68; 1024x720, 11.3,
+    // 71 / 73; 1024x768, 12.0, 71 / 74; 1040x768, 12.2, 84 / 77; 1136x800,
+    // 13.9, 84 / 83; 1280x720, 14.1, 84 / 87; 1024x1024, 16, 84 / 95; 1600x900,
+    // 22.3, 130 / 135; 1080p, 31.9, 157 / 178).
+    const int nt = TW * TH, cu = ctx->n_cu;
+    const bool sa = l.sa != 0.0f, few = nt < 11 * cu || (nt > 12 * cu && nt < 14 * cu);
     FuseK fz{};
     if (fuse && fuse->untraced_only) {
       fz.out = fuse->out;

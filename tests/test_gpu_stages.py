@@ -320,6 +320,28 @@ def test_postfilter_dilation_and_forms(hd, ctx, W, H, tile, r_cap):
     assert err.max() < COL_TOL, (err.max(), np.unravel_index(err.argmax(), err.shape))
 
 
+@pytest.mark.parametrize("W,H", [(1024, 688), (1024, 703), (1024, 768), (1009, 784), (1024, 880), (1024, 895)])
+def test_postfilter_form_does_not_show(hd, ctx, W, H):
+    """Tile counts around the lines between the form with a wave per tile and
+    the one with four: the rows that a larger image shares, which has a wave
+    per tile, are the same bit for bit."""
+    print_case(f"postfilter forms {W}x{H}")
+    big = 1200  # 75 x 64 tiles: a wave per tile
+    cfg = sg.config_1080p(W, H)
+    z = f32(_mixed_depth(big, W, 12, 5))
+    col = f32(np.random.default_rng(5).uniform(0, 1, (3, big, W)))
+    pp = hd.pp_params_of(sg.PPParams(n_taps=24, tile=16, r_cap=24.0, bg_ramp_px=1.0))
+    out = []
+    for h in (H, big):
+        c = sg.config_1080p(W, h)
+        out.append(hd.hdof_postfilter(ctx, to_dev(np.ascontiguousarray(col[:, :h]), torch.float32),
+                                      to_dev(np.ascontiguousarray(z[:h]), torch.float32), hd.camera_of(c.camera),
+                                      hd.lens_of(cfg.lens), pp))
+    torch.cuda.synchronize()
+    keep = H - H % 16 - 48  # the last rows gather across the smaller image's border
+    assert torch.equal(out[0][:, :keep], out[1][:, :keep])
+
+
 def test_postfilter_zero_aperture_exact(hd, ctx):
     print_case("postfilter A=0")
     cfg = sg.config_tiny(aperture_override=0.0)
