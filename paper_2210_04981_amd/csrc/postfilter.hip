@@ -1400,7 +1400,9 @@ __device__ __forceinline__ void image_add_foot(float* __restrict__ gc, float* fo
 
 // Pass 2 of one channel for n <= PPB_G taps: their weights times the pixels'
 // kc (and kup of the pixel above the lane's first), joined along the column.
-template <bool UNI, class Geo>
+// T16 false (small tiles): a tap that a pixel does not accept takes nothing
+// from it, whatever its gradient (0 times infinity).
+template <bool UNI, bool T16, class Geo>
 __device__ __forceinline__ void ppb_scatter(const float4* wts, int lane, int n, const float (&kc)[4], float kup, int E,
                                             float* win, float* foot, float* __restrict__ gc, int x0, int y0, int W,
                                             int H, bool firstc, bool lastc, bool lastr, int mine, int nt, Geo geo) {
@@ -1416,9 +1418,10 @@ __device__ __forceinline__ void ppb_scatter(const float4* wts, int lane, int n, 
   for (int j = 0; j < PPB_G; ++j) {
     if (j < n) {
       const TapGeo tg = geo(j);
-      const float post[4] = {kc[0] * w4[j].x, kc[1] * w4[j].y, kc[2] * w4[j].z, kc[3] * w4[j].w};
+      const auto part = [](float k, float w) { return T16 || w != 0.f ? k * w : 0.f; };
+      const float post[4] = {part(kc[0], w4[j].x), part(kc[1], w4[j].y), part(kc[2], w4[j].z), part(kc[3], w4[j].w)};
       const float ay = tg.ay, by = 1.f - ay;
-      const float r[5] = {fmaf(by, post[0], ay * (kup * wu[j])), fmaf(by, post[1], ay * post[0]),
+      const float r[5] = {fmaf(by, post[0], ay * part(kup, wu[j])), fmaf(by, post[1], ay * post[0]),
                           fmaf(by, post[2], ay * post[1]), fmaf(by, post[3], ay * post[2]), ay * post[3]};
       const bool in = tg.ix >= -E && tg.ix <= E && tg.iy >= -E && tg.iy <= E;
       if (!UNI || in) win_add(win + tg.iy * PPB_WS + tg.ix, r, tg.ax, in, firstc, lastc, lastr, mine, nt);
@@ -1496,7 +1499,7 @@ __device__ __forceinline__ int ppb_tile(const PpbArgs& A, int x, int y) {
 // One block.  UNI: one radius R for all its pixels (a tile of 16 pixels, or
 // smaller tiles of equal radius): the taps' geometry is the wave's, their
 // texels are staged and the footprint is one of 16x16 pixels.
-template <bool UNI>
+template <bool UNI, bool T16>
 __device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk, float R) {
   const float4* __restrict__ pack = A.pack;
   const float* __restrict__ coc = A.coc;
@@ -1687,7 +1690,7 @@ __device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk
       }
       lds_barrier();
       if (wave < 3)
-        ppb_scatter<UNI>(wts[b], lane, n, kc, kup, E, win, foot, gc, x0, y0, W, H, firstc, lastc, lastr, mine, nt, geo);
+        ppb_scatter<UNI, T16>(wts[b], lane, n, kc, kup, E, win, foot, gc, x0, y0, W, H, firstc, lastc, lastr, mine, nt, geo);
     }
   }
   __syncthreads();
@@ -1717,7 +1720,7 @@ __global__ __launch_bounds__(256, PPB_MINW) void k_ppc_backward(PpbArgs A) {
   __shared__ __attribute__((aligned(16))) PpbLds lds;
   const int TWb = (A.W + 15) >> 4, blk = xcd_block(blockIdx.x, TWb * ((A.H + 15) >> 4));
   if (T16) {
-    ppb_block<true>(A, lds, blk, A.rad[blk]);
+    ppb_block<true, true>(A, lds, blk, A.rad[blk]);
     return;
   }
   // lanes of a tile that lies partly outside the image have its radius too
@@ -1729,9 +1732,9 @@ __global__ __launch_bounds__(256, PPB_MINW) void k_ppc_backward(PpbArgs A) {
   const float R0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(R)));
   if (ti < 0) R = R0;
   if (__builtin_amdgcn_ballot_w64(R != R0) == 0ull)
-    ppb_block<true>(A, lds, blk, R0);
+    ppb_block<true, false>(A, lds, blk, R0);
   else
-    ppb_block<false>(A, lds, blk, R);
+    ppb_block<false, false>(A, lds, blk, R);
 }
 
 // block partials summed in a fixed order (deterministic), in double

@@ -156,3 +156,26 @@ def test_backward_tiles_windows_and_groups(hd, ctx, W, H, tile, r_cap, n_taps, A
     assert np.max(np.abs(gc - rc)) <= 1e-5 * np.max(np.abs(rc)), np.max(np.abs(gc - rc)) / np.max(np.abs(rc))
     assert abs(gl[0] - rs) <= 1e-3 * abs(rs), (gl[0], rs)
     assert abs(gl[1] - ra) <= 1e-3 * abs(ra), (gl[1], ra)
+
+
+@pytest.mark.parametrize("tile", [4, 8])
+@pytest.mark.parametrize("flat", [False, True])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_a_broken_gradient_stays_with_the_taps_it_reaches(hd, ctx, tile, flat, value):
+    """One pixel's incoming gradient is not finite: only the texels that the
+    pixel's accepted taps read get none either (a pixel of small tiles passes
+    nothing through a tap that it does not accept), the same texels that a
+    finite gradient of that pixel alone reaches."""
+    print_case(f"adjoint of a broken gradient, tile {tile} flat {flat} {value}")
+    args = list(_small(3))
+    args[1] = sg.Lens(0.05, float(np.float32(0.3)), 2.0)
+    args[8] = sg.PPParams(n_taps=48, tile=tile, r_cap=12.0, bg_ramp_px=1.0)
+    if flat:
+        args[3] = np.full_like(args[3], 3.5)
+    args[4], args[10] = np.zeros_like(args[4]), np.zeros_like(args[10])
+    args[10][:, 21, 40] = 1.0
+    one, _ = _gpu_backward(hd, ctx, *args)
+    args[10][:, 21, 40] = value
+    broken, _ = _gpu_backward(hd, ctx, *args)
+    assert (~np.isfinite(broken)).any() and np.sum(one != 0) > 3 * 9
+    assert not (~np.isfinite(broken) & (one == 0)).any(), (np.sum(~np.isfinite(broken)), np.sum(one != 0))
