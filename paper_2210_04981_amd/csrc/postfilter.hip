@@ -1320,7 +1320,9 @@ __device__ __forceinline__ float row_left(float v) {
 // of it): a lane's rows r[0..3] and, in the tile's last rows, r[4], joined
 // with the left neighbour's (one rounded sum per tap and texel), and the
 // tile's last column.  Lanes of one tile meet in no texel, and a wave's LDS
-// accesses run in order; the `nt` tiles of a block take turns.
+// accesses run in order; the `nt` tiles of a block take turns (mine: this
+// lane's tile's, none above), UNI: one tile.
+template <bool UNI>
 __device__ __forceinline__ void win_add(float* w, const float (&r)[5], float ax, bool on, bool firstc, bool lastc,
                                         bool lastr, int mine, int nt) {
   float v[5];
@@ -1330,7 +1332,7 @@ __device__ __forceinline__ void win_add(float* w, const float (&r)[5], float ax,
     v[j] = fmaf(ax, firstc ? 0.f : left, (1.f - ax) * r[j]);
   }
   for (int t = 0; t < nt; ++t) {
-    if (on && (nt == 1 || mine == t)) {
+    if (on && (UNI || mine == t)) {
       float a[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) a[j] = w[j * PPB_WS];
@@ -1424,7 +1426,7 @@ __device__ __forceinline__ void ppb_scatter(const float4* wts, int lane, int n, 
       const float r[5] = {fmaf(by, post[0], ay * part(kup, wu[j])), fmaf(by, post[1], ay * post[0]),
                           fmaf(by, post[2], ay * post[1]), fmaf(by, post[3], ay * post[2]), ay * post[3]};
       const bool in = tg.ix >= -E && tg.ix <= E && tg.iy >= -E && tg.iy <= E;
-      if (!UNI || in) win_add(win + tg.iy * PPB_WS + tg.ix, r, tg.ax, in, firstc, lastc, lastr, mine, nt);
+      if (!UNI || in) win_add<UNI>(win + tg.iy * PPB_WS + tg.ix, r, tg.ax, in, firstc, lastc, lastr, mine, nt);
       if (UNI && !in)
         image_add_foot(gc, foot, r, x0 + tg.ix, y0 + tg.iy, W, H, tg.ax, firstc, lastc, lastr);
       if (!UNI && __builtin_amdgcn_ballot_w64(!in) != 0ull)
@@ -1651,10 +1653,20 @@ __device__ __forceinline__ void ppb_block(const PpbArgs& A, PpbLds& lds, int blk
   lds_barrier();
   // pass 2: the weights again (value only) and the transpose of gpp * weight
   if (some && scat) {
-    const int tl = UNI ? 16 : tile, nt = UNI ? 1 : (16 / tl) * (16 / tl);
+    const int tl = UNI ? 16 : tile, all = (16 / tl) * (16 / tl);
     const bool firstc = (lx & (tl - 1)) == 0, lastc = (lx & (tl - 1)) == tl - 1;
     const bool lastr = (ly & (tl - 1)) == tl - 4;
-    const int mine = (ly / tl) * (16 / tl) + lx / tl;
+    // turns for the tiles that have a gradient in the wave's channel: of a
+    // sparse one few have (one pixel in 1517 of 1280x720, 4-pixel tiles: 456
+    // us with a turn for each, 207 so)
+    int mine = (ly / tl) * (16 / tl) + lx / tl, nt = 1;
+    if (!UNI) {
+      const bool any = kc[0] != 0.f || kc[1] != 0.f || kc[2] != 0.f || kc[3] != 0.f;
+      unsigned turns = 0;
+      for (int t = 0; t < all; ++t) turns |= __builtin_amdgcn_ballot_w64(any && mine == t) != 0ull ? 1u << t : 0u;
+      mine = turns >> mine & 1 ? __popc(turns & ((1u << mine) - 1u)) : all;
+      nt = __popc(turns);
+    }
     float* const win = buf + wave * PL + (ly + E) * PPB_WS + lx + E;
     float* const gc = gcol + wave * N;
     // blocks with taps outside the window start at different groups of taps:
