@@ -787,10 +787,12 @@ __device__ __forceinline__ void spec_taps8(float2 (*stg)[PPS_TEX], const float4*
                                            int wave, float R, int xw, int yw, int W, int H, int lane, GatherAcc& g) {
   const int n = (n_taps - wave + 3) >> 2;
   if (n <= 0) return;
+  // (INTERIOR: the image's bytes were checked to fit an int; the other form reads by pointer)
+  const int px = INTERIOR ? W * H : 0;
   const __amdgpu_buffer_rsrc_t rp =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float4*>(pack), (short)0, W * H * 16, HDOF_BUFFER_WORD3);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float4*>(pack), (short)0, px * 16, HDOF_BUFFER_WORD3);
   const __amdgpu_buffer_rsrc_t ry =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(ys), (short)0, W * H * 4, HDOF_BUFFER_WORD3);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(ys), (short)0, px * 4, HDOF_BUFFER_WORD3);
   int sx[2], sy[2], vo[2];  // the lane's two texels of a tap, relative to its corner
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
