@@ -179,3 +179,43 @@ def test_a_broken_gradient_stays_with_the_taps_it_reaches(hd, ctx, tile, flat, v
     broken, _ = _gpu_backward(hd, ctx, *args)
     assert (~np.isfinite(broken)).any() and np.sum(one != 0) > 3 * 9
     assert not (~np.isfinite(broken) & (one == 0)).any(), (np.sum(~np.isfinite(broken)), np.sum(one != 0))
+
+
+@pytest.mark.parametrize("W,H,tile,n_taps", [(150, 90, 8, 24), (150, 90, 4, 24), (147, 61, 4, 13), (93, 70, 8, 7)])
+def test_backward_of_mixed_radii_beyond_the_window(hd, ctx, W, H, tile, n_taps):
+    """Small tiles whose radii differ within a block and pass 20 pixels, the
+    reach of a block's window: taps beyond it are added to the image, lane by
+    lane.  CoC diameters rise from 28 to 56 pixels across the image (a tile's
+    dilated radius then differs from its neighbour's), with a near patch of
+    the other sign.  Bounds as in the other parity cases: at half the radii
+    of the 48-pixel case the CoC's rounding, relative to the CoC, is half."""
+    print_case(f"adjoint mixed radii {W}x{H} tile {tile} taps {n_taps}")
+    rng = np.random.default_rng(W + H + tile)
+    cam, lens = sg.look_camera((0, 0, 0), 0.0, W, H), sg.Lens(0.05, 1.0, 2.0)
+    yy, xx = np.mgrid[0:H, 0:W]
+    c = 28.0 + 24.0 * xx / W + 4.0 * yy / H
+    c[H // 2:H // 2 + 12, W // 2:W // 2 + 12] = -30.0
+    spx = W / (2.0 * float(cam.tan_half_fov_x))
+    z = 1.0 / (1.0 / lens.focus_distance - c / (lens.aperture * spx))
+    assert z.min() > 0.1
+    r = np.abs(c) / 2
+    TH, TW, K = -(-H // tile), -(-W // tile), -(-64 // tile)
+    rt = np.zeros((TH * tile, TW * tile))
+    rt[:H, :W] = r
+    rt = rt.reshape(TH, tile, TW, tile).max((1, 3))
+    rad = np.array([[rt[max(0, y - K):y + K + 1, max(0, x - K):x + K + 1].max() for x in range(TW)] for y in range(TH)])
+    b = 16 // tile
+    mixed = [np.ptp(rad[y:y + b, x:x + b]) > 1e-3 and rad[y:y + b, x:x + b].max() > 21
+             for y in range(0, TH, b) for x in range(0, TW, b)]
+    assert np.mean(mixed) > 0.25, np.mean(mixed)
+    spp = rng.integers(0, 3, (H, W)).astype(np.int32)
+    hit = np.where(spp > 0, rng.uniform(0, 1, (H, W)), 0.0)
+    col, cn, cf = (f32(rng.uniform(0, 1, (3, H, W))) for _ in range(3))
+    args = (cam, lens, col, f32(z), spp, cn, cf, f32(hit),
+            sg.PPParams(n_taps=n_taps, tile=tile, r_cap=64.0, bg_ramp_px=1.0), sg.CompositeParams(),
+            f32(rng.normal(size=(3, H, W))))
+    gc, gl = _gpu_backward(hd, ctx, *args)
+    rc, rs, ra = orc.pp_composite_backward(*args)
+    assert np.max(np.abs(gc - rc)) <= 1e-5 * np.max(np.abs(rc)), np.max(np.abs(gc - rc)) / np.max(np.abs(rc))
+    assert abs(gl[0] - rs) <= 1e-3 * abs(rs), (gl[0], rs)
+    assert abs(gl[1] - ra) <= 1e-3 * abs(ra), (gl[1], ra)
