@@ -27,7 +27,8 @@
  *  - Every call only enqueues work on `stream` (a hipStream_t; NULL = the
  *    null stream) and returns; results are ready when the stream is.
  *    No call synchronises the host except hdof_create, hdof_destroy,
- *    hdof_scene_destroy, hdof_scene_stats, hdof_history_reset and hdof_sync.
+ *    hdof_build_bvh, hdof_scene_destroy, hdof_scene_stats,
+ *    hdof_history_reset and hdof_sync.
  *  - Arguments are validated before anything is enqueued; a failing call
  *    enqueues nothing and returns a status; hdof_last_error() then holds a
  *    message for the calling thread.  Nothing throws across this ABI.
@@ -219,8 +220,13 @@ hdof_status hdof_scene_set_specular(hdof_scene* scene, const float* d_spec, hdof
  * bottom-up by PLOC (nearest neighbour by merged-box surface area within a
  * window of the Morton order), nodes placed depth-first, leaves of at most 4
  * triangles.  d_verts: n_tris x 9 floats (v0.xyz v1.xyz v2.xyz);
- * d_albedo: n_tris x 3 floats.  The inputs are read on `stream` and may be
- * freed once the stream has passed this call.  n_tris in [1, 2^26].
+ * d_albedo: n_tris x 3 floats.  The inputs are read on `stream`; the call
+ * waits for the build and may then be followed by their release.  n_tris in
+ * [1, 2^26].  Geometry that does not cluster (an infinite vertex, extents
+ * whose areas overflow float32) is refused with HDOF_ERR_HIP.
+ * Memory: the scene holds 172 bytes per triangle; the build uses about 260
+ * more, which the context keeps for its next build, up to 288 MiB (one
+ * million triangles), until hdof_destroy, and gives back at once above that.
  * *out is owned by the caller and freed with hdof_scene_destroy. */
 hdof_status hdof_build_bvh(hdof_ctx* ctx, const float* d_verts, const float* d_albedo,
                            int32_t n_tris, hdof_scene** out, hdof_stream stream);

@@ -646,14 +646,13 @@ __device__ inline unsigned leaf_code(int first, int count) {
 // centre are halves, of 11 bits from 2^-14 to 2^16 units and of fixed steps
 // of 2^-24 below.  The root's largest extent is at most 2^14 units, unless
 // that would leave triangles of the usual size (the geometric mean of their
-// extents, 2^mean) below 2^-10 units, in a scene with a ground or a sky a
-// million times wider than the rest: then they have that size, and planes
-// beyond 2^16 units from their node's centre, of the few nodes that hold the
-// far geometry, are infinite (every ray passes them).  Node visits and
-// triangle tests per ray of a room on a ground of 1e8 / 1e10 / 1e14 units:
-// 59 / 637 / 34006 with the root's extent alone, 57 / 48 / 48 so and by fp32
-// boxes.  At most 2^27: a ray's inverse direction, up to 1e30, is multiplied
-// by the unit.
+// extents, 2^mean) below 2^-10 units, in a scene whose ground or sky is more
+// than 2^24 times as wide: then they have that size, and planes beyond 2^16
+// units from their node's centre, of the few nodes that hold the far
+// geometry, are infinite (every ray passes them).  Node visits and triangle
+// tests per ray of a room on a ground of 1e8 / 1e10 / 1e14 units: 59 / 637 /
+// 34006 with the root's extent alone, 57 / 48 / 48 so and by fp32 boxes.  At
+// most 2^27: a ray's inverse direction, up to 1e30, is multiplied by the unit.
 __device__ inline float box_unit(const float* __restrict__ root, int mean) {
   float ext = 0.0f;
   for (int a = 0; a < 3; ++a) ext = fmaxf(ext, root[3 + a] - root[a]);

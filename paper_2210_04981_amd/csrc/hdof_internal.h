@@ -53,8 +53,9 @@
 #define HDOF_LEAF_BIT 0x80000000u
 #define HDOF_LEAF_FIRST_MASK 0x07FFFFFFu
 
-// build scratch that a context keeps between builds (about 260 bytes per
-// triangle: one million triangles)
+// build scratch that a context keeps between builds until it is destroyed
+// (about 260 bytes per triangle: one million triangles); a larger build's is
+// freed at its end
 #define HDOF_BVH_KEEP_BYTES ((size_t)288 << 20)
 
 struct hdof_scene {
@@ -99,7 +100,7 @@ struct hdof_ctx {
   int pp_taps_n = 0;  // tap count the table currently holds
   int pp_taps_blades = 0;
   float pp_taps_rot = 0.0f, pp_taps_sa = 0.0f;  // and the aperture it was built for
-  // adjoint scratch: CoC per unit aperture, tile / radius arg pixels, block partials
+  // adjoint scratch: tile / radius arg pixels, block partials, the signed CoCs by themselves
   Buf ppb_args, ppb_partial, ppb_coc;
   // variance history (previous frame) and its reprojection into this frame
   int hist_w = 0, hist_h = 0;

@@ -734,9 +734,15 @@ __global__ __launch_bounds__(256) void k_gbuffer_batch(const float4* __restrict_
 // which the frame then waits for.  (Frames of 640x360 with 218k rays at 1.6 /
 // 3.6 / 10 blocks per CU: 337 / 279 / 250 us; 1400x1050 with 693k at 5 / 7 /
 // 10: 483 / 454 / 462; 400x300 with 73k at 1 / 3.6 / 4.5: 157 / 117 / 119.)
-// Below 3 rays per 8 pixels the frame waits for the gather, not for the
-// trace (1080p with 571k rays at 4.1 / 7 blocks per CU: 358 / 379 us; the
-// frames above have 0.47 to 0.95 rays per pixel).
+// Below 3 rays per 8 pixels the lower bounds but the first are left out.
+// Large frames then wait for the gather, and more blocks beside it slow them
+// (without / with the bounds, us: 1080p, 571k rays, 358 / 379; 370k, 337 /
+// 365; 1440p, 0.10 to 0.34 rays per pixel, 543 / 570, 599 / 629, 696 / 714,
+// 699 / 702).  The line is one of that size: smaller frames below it wait for
+// the trace all the same and would gain by the bounds (960x540 with 141k
+// rays 309 / 234, 168k 247 / 196; 1280x720 with 187k 332 / 271, 310k 367 /
+// 286; 1080p with 287k rays of a wider scene 435 / 409).  The frames above
+// the line have 0.39 to 3.8 rays per pixel.
 // The first blocks are kept, so every queue segment keeps its blocks.
 __device__ inline int kept_blocks(const TraceArgs& A, int total) {
   const long all = (long)A.bpc * A.n_cu;
